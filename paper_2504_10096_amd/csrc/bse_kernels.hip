@@ -625,52 +625,82 @@ __global__ void __launch_bounds__(kThreads)
   }
 }
 
-// out[i] = sum over the blocks of panel row P = i / R of their row partials
-//        + sum over the blocks of panel column P of their column partials.
-// The nb + 1 terms of a row (row partials Q = P..nb-1, then column partials
-// Q = 0..P, slice by slice) are cut into four consecutive ranges: lane l of
-// wave w sums range w of row blockIdx.x * 64 + l in order, and the four
-// range sums are added in wave order (fixed order: deterministic).  A
-// workgroup covers 64 rows of one panel (R is a multiple of 64), so the
-// loop bounds are uniform per wave; a thread per row with the whole loop
-// left too few loads in flight.
-__global__ void __launch_bounds__(kThreads)
-    mv_reduce_kernel(const double2* __restrict__ rowpart, const double2* __restrict__ colpart,
-                     int R, int NS, int nb, int64_t n, double2* __restrict__ out, const double* __restrict__ dc,
-                     double dsg, const double2* __restrict__ xa, int conja) {
-  __shared__ double2 sh[4][64];
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int64_t i = (int64_t)blockIdx.x * 64 + lane;
-  double sx = 0.0, sy = 0.0;
-  if (i < n) {
-    const int P = (int)(i / R), r = (int)(i % R);
-    const int nrow = nb - P;
-    const int len = nrow + (P + 1) * NS;
-    const int t0 = (int)((int64_t)len * wave / 4), t1 = (int)((int64_t)len * (wave + 1) / 4);
-    const int64_t pstart = (int64_t)P * nb - (int64_t)P * (P - 1) / 2;
-    for (int t = t0; t < (t1 < nrow ? t1 : nrow); ++t) {  // row partials, Q = P + t
-      const double2 v = rowpart[(size_t)(pstart + t) * R + r];
-      sx += v.x;
-      sy += v.y;
-    }
-    for (int t = (t0 > nrow ? t0 : nrow); t < t1; ++t) {  // column partials, u = Q NS + slice
-      const int u = t - nrow;
-      const int Q = NS == 1 ? u : u / NS, sl = u - Q * NS;
-      const int64_t qs = (int64_t)Q * nb - (int64_t)Q * (Q - 1) / 2;
-      const double2 v = colpart[((size_t)(qs + (P - Q)) * NS + sl) * R + r];
-      sx += v.x;
-      sy += v.y;
-    }
+// Partial sums of one output: row i = P R + r takes the row partials of blocks
+// (P, Q >= P) and the column partials of blocks (Q <= P, P), slice by slice,
+// nb + 1 terms for NS = 1.  They are cut into W consecutive ranges: lane l of
+// wave w sums range w of row blockIdx.x * 64 + l in order, the W range sums
+// are added in wave order (fixed order: deterministic).  A workgroup covers
+// 64 rows of one panel (R is a multiple of 64), so the loop bounds are uniform
+// per wave.
+//
+// The sums are a latency chain, not a bandwidth problem: one thread per row
+// with all its terms left 41 x 2 workgroups of serial loads at N = 10368
+// (82 terms; 54 us beside 163 us for the read of the triangles).  Read and sum
+// of two full-H vectors there: 219 us before, 178 us with 16 waves per 64 rows.
+// W = 16 up to kReduceWide rows, where 64-row workgroups of four waves do not
+// fill the chip, if each wave has a term (nb >= 16); W = 4 otherwise (N = 320,
+// six terms: 11.5 us per small pass with four waves, 12.8 us with 16).
+constexpr int64_t kReduceWide = 32768;
+inline bool reduce_wide(const Layout& L) { return L.n <= kReduceWide && L.nb >= 16; }
+template <int W>
+__device__ __forceinline__ void part_range(const double2* __restrict__ rp, const double2* __restrict__ cp, int R,
+                                           int NS, int nb, int P, int r, int wave, double& sx, double& sy) {
+  const int nrow = nb - P;
+  const int len = nrow + (P + 1) * NS;
+  const int t0 = (int)((int64_t)len * wave / W), t1 = (int)((int64_t)len * (wave + 1) / W);
+  const int64_t pstart = (int64_t)P * nb - (int64_t)P * (P - 1) / 2;
+  const int te = t1 < nrow ? t1 : nrow;
+#pragma unroll 4
+  for (int t = t0; t < te; ++t) {  // row partials, Q = P + t
+    const double2 v = rp[(size_t)(pstart + t) * R + r];
+    sx += v.x;
+    sy += v.y;
   }
+#pragma unroll 4
+  for (int t = (t0 > nrow ? t0 : nrow); t < t1; ++t) {  // column partials, u = Q NS + slice
+    const int u = t - nrow;
+    const int Q = NS == 1 ? u : u / NS, sl = u - Q * NS;
+    const int64_t qs = (int64_t)Q * nb - (int64_t)Q * (Q - 1) / 2;
+    const double2 v = cp[((size_t)(qs + (P - Q)) * NS + sl) * R + r];
+    sx += v.x;
+    sy += v.y;
+  }
+}
+
+// Sum over the waves of one value pair per lane, in wave order; the result is
+// valid in wave 0.
+template <int W>
+__device__ __forceinline__ double2 wave_order_sum(double2 (*sh)[64], int wave, int lane, double sx, double sy) {
+  __syncthreads();  // the array may still be read for the previous output
   sh[wave][lane] = make_double2(sx, sy);
   __syncthreads();
-  if (wave == 0 && i < n) {
-    double2 t = sh[0][lane];
+  double2 t = make_double2(0.0, 0.0);
+  if (wave == 0) {
+    t = sh[0][lane];
 #pragma unroll
-    for (int w = 1; w < 4; ++w) {
+    for (int w = 1; w < W; ++w) {
       t.x += sh[w][lane].x;
       t.y += sh[w][lane].y;
     }
+  }
+  return t;
+}
+
+// One-vector pass: out[i] = the sum of row i's partials (+ the diagonal
+// correction on the A input).
+template <int W>
+__global__ void __launch_bounds__(64 * W)
+    mv_reduce_kernel(const double2* __restrict__ rowpart, const double2* __restrict__ colpart,
+                     int R, int NS, int nb, int64_t n, double2* __restrict__ out, const double* __restrict__ dc,
+                     double dsg, const double2* __restrict__ xa, int conja) {
+  __shared__ double2 sh[W][64];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int64_t i0 = (int64_t)blockIdx.x * 64, i = i0 + lane;
+  double sx = 0.0, sy = 0.0;
+  // partial rows past n exist (the blocks are padded)
+  part_range<W>(rowpart, colpart, R, NS, nb, (int)(i0 / R), (int)(i0 % R) + lane, wave, sx, sy);
+  double2 t = wave_order_sum<W>(sh, wave, lane, sx, sy);
+  if (wave == 0 && i < n) {
     if (dc) {  // diagonal correction on the A input
       const double f = dsg * dc[i];
       const double2 x = xa[i];
@@ -1260,47 +1290,31 @@ __global__ void __launch_bounds__(kThreads)
 // Sum of the partials of mh_block_kernel (pairs != 0: output 2q goes to the
 // top of column q of MV, output 2q+1 conjugated and times bsign to its
 // bottom; bsign = 1: M v, -1: H v) or of mk_block_kernel (pairs == 0:
-// output q to column q).  Grid (ceil(n / 256), outputs).  sd != 0 (the
+// output q to column q).  Grid (ceil(n / 64), outputs).  sd != 0 (the
 // streaming full-H kernel): outputs 2q, 2q+1 are K1 u_q and K2 w_q; the
-// thread of vector q (grid (ceil(n / 256), vectors)) sums both and writes
+// workgroup of vector q (grid (ceil(n / 64), vectors)) sums both and writes
 // the top (K1 u + K2 w) / 2 and the conjugated bottom (K1 u - K2 w) / 2.
-__global__ void __launch_bounds__(kThreads)
+template <int W>
+__global__ void __launch_bounds__(64 * W)
     mh_reduce_kernel(const double2* __restrict__ rowpart, const double2* __restrict__ colpart, int R, int NS,
                      int nb, int64_t nblk, int64_t n, double2* __restrict__ MV, int64_t ldv, int64_t ldh,
                      double bsign, int pairs, const double* __restrict__ dc, double dsg,
                      const double2* __restrict__ X, int64_t ldx, int64_t ldhx, int sd) {
-  const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (i >= n) return;
-  const int P = (int)(i / R), r = (int)(i % R);
-  const int64_t pstart = (int64_t)P * nb - (int64_t)P * (P - 1) / 2;
-  // the row's sum of output o over its blocks: rows of blocks (P, Q >= P),
-  // columns of blocks (Q <= P, P), in a fixed order
-  auto osum = [&](int o, double& sx, double& sy) {
-    const double2* rp = rowpart + (size_t)o * nblk * R;
-    const double2* cp = colpart + (size_t)o * nblk * NS * R;
-    sx = 0.0;
-    sy = 0.0;
-    for (int Q = P; Q < nb; ++Q) {
-      const double2 v = rp[(size_t)(pstart + (Q - P)) * R + r];
-      sx += v.x;
-      sy += v.y;
-    }
-    for (int Q = 0; Q <= P; ++Q) {
-      const int64_t b = (int64_t)Q * nb - (int64_t)Q * (Q - 1) / 2 + (P - Q);
-      for (int sl = 0; sl < NS; ++sl) {
-        const double2 v = cp[((size_t)b * NS + sl) * R + r];
-        sx += v.x;
-        sy += v.y;
-      }
-    }
-  };
+  __shared__ double2 sh[W][64];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int64_t i0 = (int64_t)blockIdx.x * 64, i = i0 + lane;
+  const int P = (int)(i0 / R), r = (int)(i0 % R) + lane;
+  const size_t rs = (size_t)nblk * R, cs = rs * NS;
   if (sd) {
     const int q = blockIdx.y;
-    double s1x, s1y, s2x, s2y;
-    osum(2 * q, s1x, s1y);
-    osum(2 * q + 1, s2x, s2y);
-    double tx = 0.5 * (s1x + s2x), ty = 0.5 * (s1y + s2y);  // top
-    double cx = 0.5 * (s1x - s2x), cy = 0.5 * (s1y - s2y);  // conjugated bottom
+    double s1x = 0.0, s1y = 0.0, s2x = 0.0, s2y = 0.0;
+    part_range<W>(rowpart + 2 * q * rs, colpart + 2 * q * cs, R, NS, nb, P, r, wave, s1x, s1y);
+    part_range<W>(rowpart + (2 * q + 1) * rs, colpart + (2 * q + 1) * cs, R, NS, nb, P, r, wave, s2x, s2y);
+    const double2 k1 = wave_order_sum<W>(sh, wave, lane, s1x, s1y);
+    const double2 k2 = wave_order_sum<W>(sh, wave, lane, s2x, s2y);
+    if (wave != 0 || i >= n) return;
+    double tx = 0.5 * (k1.x + k2.x), ty = 0.5 * (k1.y + k2.y);  // top
+    double cx = 0.5 * (k1.x - k2.x), cy = 0.5 * (k1.y - k2.y);  // conjugated bottom
     if (dc) {
       const double f = dsg * dc[i];
       const double2 x = X[(size_t)q * ldx + i];
@@ -1315,8 +1329,12 @@ __global__ void __launch_bounds__(kThreads)
     return;
   }
   const int o = blockIdx.y;
-  double sx, sy;
-  osum(o, sx, sy);
+  double sx = 0.0, sy = 0.0;
+  part_range<W>(rowpart + o * rs, colpart + o * cs, R, NS, nb, P, r, wave, sx, sy);
+  const double2 t = wave_order_sum<W>(sh, wave, lane, sx, sy);
+  if (wave != 0 || i >= n) return;
+  sx = t.x;
+  sy = t.y;
   // diagonal correction: output o multiplies A by x_o (mk) or, for the fused
   // full-H product, by x_q (top) and conj(y_q) (the conjugate of the bottom)
   if (dc) {
@@ -1344,6 +1362,19 @@ __global__ void __launch_bounds__(kThreads)
     MV[(size_t)q * ldv + ldh + i] = make_double2(bsign * sx, -bsign * sy);
   else
     MV[(size_t)q * ldv + i] = make_double2(sx, sy);
+}
+
+// ny: outputs (or, sd, vectors) summed
+void launch_mh_reduce(const Layout& L, int ny, int ns, const double2* rowpart, const double2* colpart, double2* MV,
+                      int64_t ldv, int64_t ldh, double bsign, int pairs, const MatPtrs& m, const double2* X,
+                      int64_t ldx, int64_t ldhx, int sd, hipStream_t s) {
+  const dim3 grid((unsigned)((L.n + 63) / 64), (unsigned)ny);
+  if (reduce_wide(L))
+    hipLaunchKernelGGL(mh_reduce_kernel<16>, grid, dim3(1024), 0, s, rowpart, colpart, L.R, ns, L.nb, L.nblk, L.n,
+                       MV, ldv, ldh, bsign, pairs, m.dc, m.dsign, X, ldx, ldhx, sd);
+  else
+    hipLaunchKernelGGL(mh_reduce_kernel<4>, grid, dim3(256), 0, s, rowpart, colpart, L.R, ns, L.nb, L.nblk, L.n, MV,
+                       ldv, ldh, bsign, pairs, m.dc, m.dsign, X, ldx, ldhx, sd);
 }
 
 template <int R, int AR>
@@ -2403,8 +2434,13 @@ hipError_t matvec(const Layout& L, Arith ar, BMode bm, const MatPtrs& m, const d
   }
   const double2* rowpart = part;
   const double2* colpart = part + (size_t)L.nblk * L.R;
-  hipLaunchKernelGGL(mv_reduce_kernel, dim3((unsigned)((L.n + 63) / 64)), dim3(kThreads), 0, s, rowpart, colpart,
-                     L.R, mv_slices(L), L.nb, L.n, out, m.dc, m.dsign, va, conja);
+  const dim3 rgrid((unsigned)((L.n + 63) / 64));
+  if (reduce_wide(L))
+    hipLaunchKernelGGL(mv_reduce_kernel<16>, rgrid, dim3(1024), 0, s, rowpart, colpart, L.R, mv_slices(L), L.nb, L.n,
+                       out, m.dc, m.dsign, va, conja);
+  else
+    hipLaunchKernelGGL(mv_reduce_kernel<4>, rgrid, dim3(256), 0, s, rowpart, colpart, L.R, mv_slices(L), L.nb, L.n,
+                       out, m.dc, m.dsign, va, conja);
   return hipGetLastError();
 }
 
@@ -2463,9 +2499,7 @@ hipError_t mh_apply(const Layout& L, Arith ar, const MatPtrs& m, int nh, const d
   const double2* rowpart = part;
   const double2* colpart = part + (size_t)2 * nh * L.nblk * L.R;
   const int sd = L.R >= 128;  // the streaming kernel's sum / difference outputs
-  hipLaunchKernelGGL(mh_reduce_kernel, dim3((unsigned)((L.n + kThreads - 1) / kThreads), (unsigned)(sd ? nh : 2 * nh)),
-                     dim3(kThreads), 0, s, rowpart, colpart, L.R, ns, L.nb, L.nblk, L.n, MV, ldv, ldh, bsign, 1,
-                     m.dc, m.dsign, V, ldv, ldh, sd);
+  launch_mh_reduce(L, sd ? nh : 2 * nh, ns, rowpart, colpart, MV, ldv, ldh, bsign, 1, m, V, ldv, ldh, sd, s);
   return hipGetLastError();
 }
 
@@ -2556,9 +2590,7 @@ hipError_t mk_apply(const Layout& L, Arith ar, BMode bm, const MatPtrs& m, int n
   const int ns = L.R < mk_rows(nv) ? 1 : L.R / mk_rows(nv);
   const double2* rowpart = part;
   const double2* colpart = part + (size_t)nv * L.nblk * L.R;
-  hipLaunchKernelGGL(mh_reduce_kernel, dim3((unsigned)((L.n + kThreads - 1) / kThreads), (unsigned)nv),
-                     dim3(kThreads), 0, s, rowpart, colpart, L.R, ns, L.nb, L.nblk, L.n, out, ldo, (int64_t)0, 1.0,
-                     0, m.dc, m.dsign, V, ldv, (int64_t)0, 0);
+  launch_mh_reduce(L, nv, ns, rowpart, colpart, out, ldo, 0, 1.0, 0, m, V, ldv, 0, 0, s);
   return hipGetLastError();
 }
 
