@@ -24,11 +24,6 @@ __device__ __forceinline__ double wave_sum(double v) {
   for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
   return v;
 }
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int off = 32; off >= 1; off >>= 1) v += __shfl_xor(v, off, 64);
-  return v;
-}
 
 // Block-wide sum (256 threads) in a fixed order: deterministic.
 __device__ double block_sum(double v, double* sh) {
@@ -48,106 +43,30 @@ __device__ double block_sum(double v, double* sh) {
 typedef double nd2 __attribute__((ext_vector_type(2)));
 typedef float nf2 __attribute__((ext_vector_type(2)));
 
+typedef float nf4 __attribute__((ext_vector_type(4)));
+
+// arithmetic type of a pass
 template <int AR>
-struct Elem;
-template <>
-struct Elem<AR_C128> {
+struct Elem {
   using T = double;
-  __device__ static __forceinline__ void load(const void* p, const void*, size_t i, double& re,
-                                              double& im) {
-    const nd2 v = __builtin_nontemporal_load(static_cast<const nd2*>(p) + i);
-    re = v.x;
-    im = v.y;
-  }
 };
 template <>
 struct Elem<AR_HI> {
   using T = float;
-  __device__ static __forceinline__ void load(const void* p, const void*, size_t i, float& re,
-                                              float& im) {
-    const nf2 v = __builtin_nontemporal_load(static_cast<const nf2*>(p) + i);
-    re = v.x;
-    im = v.y;
-  }
-};
-template <>
-struct Elem<AR_HI64> {
-  using T = double;
-  __device__ static __forceinline__ void load(const void* p, const void*, size_t i, double& re,
-                                              double& im) {
-    const nf2 v = __builtin_nontemporal_load(static_cast<const nf2*>(p) + i);
-    re = (double)v.x;
-    im = (double)v.y;
-  }
-};
-template <>
-struct Elem<AR_HILO> {
-  using T = double;
-  __device__ static __forceinline__ void load(const void* p, const void* q, size_t i, double& re,
-                                              double& im) {
-    const nf2 h = __builtin_nontemporal_load(static_cast<const nf2*>(p) + i);
-    const nf2 l = __builtin_nontemporal_load(static_cast<const nf2*>(q) + i);
-    re = (double)h.x + (double)l.x;
-    im = (double)h.y + (double)l.y;
-  }
 };
 
 // ----------------------------------------------------------------- matvec
 //
-// One workgroup (4 waves) per stored R x R block (P, Q) (the kernel also
-// takes row slices of RS < R rows, grid.y = R / RS; one slice measured as
-// fast and halves the column partials).  Wave w walks the columns
-// [w R/4, (w+1) R/4) of the block; in each column a lane owns VW adjacent
-// rows per 64 VW-row group (VW = 2 for the complex64 triangles: 16-byte
-// loads), so every load instruction reads one contiguous 64 VW-entry
-// segment.  The lane adds A_rc x_c into its row accumulators and
-// conj(A_rc) x_r into the column sum, which a wavefront reduction completes.
-// Row sums of the four waves are combined through LDS.  Outputs are
-// per-block partial vectors in FP64 (rows: rowpart[blk][R]; columns:
-// colpart[blk][slice][R]); mv_reduce_kernel sums them in a fixed order, so
-// the result is deterministic and each block is read once.
-template <int AR, int VW>
-struct Loader;
-template <int AR>
-struct Loader<AR, 1> {
-  using T = typename Elem<AR>::T;
-  __device__ static __forceinline__ void load(const void* p, const void* q, size_t i, T* re, T* im) {
-    Elem<AR>::load(p, q, i, re[0], im[0]);
-  }
-};
-typedef float nf4 __attribute__((ext_vector_type(4)));
-template <>
-struct Loader<AR_HI, 2> {
-  __device__ static __forceinline__ void load(const void* p, const void*, size_t i, float* re, float* im) {
-    const nf4 v = __builtin_nontemporal_load(reinterpret_cast<const nf4*>(static_cast<const nf2*>(p) + i));
-    re[0] = v.x;
-    im[0] = v.y;
-    re[1] = v.z;
-    im[1] = v.w;
-  }
-};
-template <>
-struct Loader<AR_HI64, 2> {
-  __device__ static __forceinline__ void load(const void* p, const void*, size_t i, double* re, double* im) {
-    const nf4 v = __builtin_nontemporal_load(reinterpret_cast<const nf4*>(static_cast<const nf2*>(p) + i));
-    re[0] = (double)v.x;
-    im[0] = (double)v.y;
-    re[1] = (double)v.z;
-    im[1] = (double)v.w;
-  }
-};
-template <>
-struct Loader<AR_HILO, 2> {
-  __device__ static __forceinline__ void load(const void* p, const void* q, size_t i, double* re, double* im) {
-    const nf4 h = __builtin_nontemporal_load(reinterpret_cast<const nf4*>(static_cast<const nf2*>(p) + i));
-    const nf4 l = __builtin_nontemporal_load(reinterpret_cast<const nf4*>(static_cast<const nf2*>(q) + i));
-    re[0] = (double)h.x + (double)l.x;
-    im[0] = (double)h.y + (double)l.y;
-    re[1] = (double)h.z + (double)l.z;
-    im[1] = (double)h.w + (double)l.w;
-  }
-};
-
+// One workgroup (4 waves) per stored R x R block (P, Q), R >= 128 (block edge
+// 64: tile64_kernel).  In each column a lane owns VW adjacent rows per
+// 64 VW-row group (VW = 2 for the complex64 triangles: 16-byte loads), so
+// every load instruction reads one contiguous 64 VW-entry segment.  The lane
+// adds A_rc x_c into its row accumulators and conj(A_rc) x_r into the column
+// sum, which a wavefront reduction completes.  Row sums of the four waves are
+// combined through LDS.  Outputs are per-block partial vectors in FP64 (rows:
+// rowpart[blk][R]; columns: colpart[blk][slice][R]); mv_reduce_kernel sums
+// them in a fixed order, so the result is deterministic and each block is read
+// once.
 // entries per lane-load: two complex64 (16 bytes) where a slice has >= 128 rows
 template <int R, int AR>
 struct MvShape {
@@ -157,143 +76,6 @@ struct MvShape {
   static constexpr int G = RS / (64 * VW);
   static constexpr int RPL = G * VW;
 };
-
-template <int R, int AR, int BM>
-__global__ void __launch_bounds__(kThreads)
-    mv_block_kernel(const void* __restrict__ a0, const void* __restrict__ a1,
-                    const void* __restrict__ b0, const void* __restrict__ b1,
-                    const int2* __restrict__ blkmap, int64_t n, const double2* __restrict__ va,
-                    int conja, const double2* __restrict__ vb, int conjb, double sb,
-                    double2* __restrict__ rowpart, double2* __restrict__ colpart) {
-  using T = typename Elem<AR>::T;
-  using Sh = MvShape<R, AR>;
-  constexpr int RS = Sh::RS, NS = Sh::NS, VW = Sh::VW, G = Sh::G, RPL = Sh::RPL;
-  constexpr int CPW = R / 4;
-  __shared__ double2 sh[4][RS];
-
-  const int blk = blockIdx.x;
-  const int slice = blockIdx.y;
-  const int2 pq = blkmap[blk];
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63;
-  const int64_t row0 = (int64_t)pq.x * R + slice * RS, col0 = (int64_t)pq.y * R;
-  const size_t base = (size_t)blk * R * R + (size_t)slice * RS;
-  const T ca = conja ? T(-1) : T(1);
-  const T cb = conjb ? T(-1) : T(1);
-  const T tsb = (T)sb;
-
-  // Row-side inputs x_r (and the explicit B input); lane row (g, e) is
-  // slice row g 64 VW + lane VW + e.
-  T xar[RPL], xai[RPL], xbr[RPL], xbi[RPL];
-#pragma unroll
-  for (int g = 0; g < G; ++g)
-#pragma unroll
-    for (int e = 0; e < VW; ++e) {
-      const int q = g * VW + e;
-      const int64_t i = row0 + g * 64 * VW + lane * VW + e;
-      double2 v = make_double2(0.0, 0.0), w = make_double2(0.0, 0.0);
-      if (i < n) {
-        v = va[i];
-        if (BM == BM_EXPLICIT) w = vb[i];
-      }
-      xar[q] = (T)v.x;
-      xai[q] = ca * (T)v.y;
-      if (BM == BM_EXPLICIT) {
-        xbr[q] = tsb * (T)w.x;
-        xbi[q] = tsb * cb * (T)w.y;
-      } else {
-        xbr[q] = T(0);
-        xbi[q] = T(0);
-      }
-    }
-
-  T rr[RPL], ri[RPL];
-#pragma unroll
-  for (int q = 0; q < RPL; ++q) {
-    rr[q] = T(0);
-    ri[q] = T(0);
-  }
-
-#pragma unroll 2
-  for (int cc = 0; cc < CPW; ++cc) {
-    const int c = wave * CPW + cc;
-    const int64_t j = col0 + c;
-    double2 vj = make_double2(0.0, 0.0), wj = make_double2(0.0, 0.0);
-    if (j < n) {
-      vj = va[j];
-      if (BM == BM_EXPLICIT) wj = vb[j];
-    }
-    const T xcr = (T)vj.x, xci = ca * (T)vj.y;
-    T ycr = T(0), yci = T(0);  // B input at column c
-    if (BM == BM_CONJ) {
-      ycr = tsb * xcr;
-      yci = -tsb * xci;
-    } else if (BM == BM_EXPLICIT) {
-      ycr = tsb * (T)wj.x;
-      yci = tsb * cb * (T)wj.y;
-    }
-    T cr = T(0), ci = T(0), dr = T(0), di = T(0);
-    const size_t cbase = base + (size_t)c * R + lane * VW;
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-      T are[VW], aim[VW], bre[VW], bim[VW];
-      Loader<AR, VW>::load(a0, a1, cbase + g * 64 * VW, are, aim);
-      if (BM != BM_NONE) Loader<AR, VW>::load(b0, b1, cbase + g * 64 * VW, bre, bim);
-#pragma unroll
-      for (int e = 0; e < VW; ++e) {
-        const int q = g * VW + e;
-        const T ar = are[e], ai = aim[e];
-        // row r: A_rc x_c
-        rr[q] += ar * xcr - ai * xci;
-        ri[q] += ar * xci + ai * xcr;
-        // column c: conj(A_rc) x_r
-        cr += ar * xar[q] + ai * xai[q];
-        ci += ar * xai[q] - ai * xar[q];
-        if (BM != BM_NONE) {
-          const T br = bre[e], bi = bim[e];
-          rr[q] += br * ycr - bi * yci;
-          ri[q] += br * yci + bi * ycr;
-          if (BM == BM_CONJ) {
-            // column c: B_rc conj(x_r) (the sign sb is applied after the sum)
-            dr += br * xar[q] + bi * xai[q];
-            di += bi * xar[q] - br * xai[q];
-          } else {
-            dr += br * xbr[q] - bi * xbi[q];
-            di += br * xbi[q] + bi * xbr[q];
-          }
-        }
-      }
-    }
-    if (BM == BM_CONJ) {
-      cr += tsb * dr;
-      ci += tsb * di;
-    } else if (BM == BM_EXPLICIT) {
-      cr += dr;
-      ci += di;
-    }
-    cr = wave_sum(cr);
-    ci = wave_sum(ci);
-    if (lane == 0) colpart[((size_t)blk * NS + slice) * R + c] = make_double2((double)cr, (double)ci);
-  }
-
-#pragma unroll
-  for (int g = 0; g < G; ++g)
-#pragma unroll
-    for (int e = 0; e < VW; ++e) {
-      const int q = g * VW + e;
-      sh[wave][g * 64 * VW + lane * VW + e] = make_double2((double)rr[q], (double)ri[q]);
-    }
-  __syncthreads();
-  for (int r = threadIdx.x; r < RS; r += kThreads) {
-    double2 t = sh[0][r];
-#pragma unroll
-    for (int w = 1; w < 4; ++w) {
-      t.x += sh[w][r].x;
-      t.y += sh[w][r].y;
-    }
-    rowpart[(size_t)blk * R + slice * RS + r] = t;
-  }
-}
 
 // Wavefront sum with DPP row shifts and row broadcasts (no LDS traffic);
 // the total is returned to every lane (read from lane 63).
@@ -465,9 +247,8 @@ __device__ __forceinline__ void raw_get(const RawCol<AR>& r, int e, T& re, T& im
   }
 }
 
-// One-vector pass, streaming form: same blocks, slices and partial layout as
-// mv_block_kernel, but the four waves interleave columns (wave w takes
-// columns w, w + 4, ...), the loads of a wave's next column are issued
+// One-vector pass, streaming form: the four waves interleave columns (wave w
+// takes columns w, w + 4, ...), the loads of a wave's next column are issued
 // before its current one is consumed (two columns in flight per wave in
 // registers), the column sums use DPP reductions, and they are kept one per
 // lane and stored per 64 columns, so the column loop has no branches.
@@ -711,133 +492,322 @@ __global__ void __launch_bounds__(64 * W)
   }
 }
 
-// ------------------------------------------------- full-H products (FP64)
+// ------------------------------------------- small matrices: 64 x 64 blocks
 //
-// M v for NH vectors v_q = [x_q; y_q] in one read of A and B: output 2q is
-// A x_q + B y_q (top of M v_q), output 2q+1 is A conj(y_q) + B conj(x_q)
-// (the conjugate of the bottom).  Per stored entry pair (A_rc, B_rc) and
-// vector the row r gains A_rc a_c + B_rc b_c and the column c gains
-// conj(A_rc) a_r + B_rc b_r (A Hermitian, B symmetric), (a, b) = (x, y) or
-// (conj y, conj x).  A workgroup covers RS <= 256 rows of a block (grid.y
-// row slices) so that the per-lane row state of 2 NH outputs stays in
-// registers; wave w walks columns [w R/4, (w+1) R/4) as in the one-vector
-// kernel.  Row partials: rowpart[o][blk][R]; column partials:
-// colpart[o][blk][slice][R]; mh_reduce_kernel sums them in a fixed order.
-template <int R, int AR, int NH>
+// Every product of a pass on block edge 64 (N below about 5800): one workgroup
+// per stored block, lane = row, wave w the CPW columns [w CPW, (w + 1) CPW) of
+// the block.  MODE: T64_A rows A x, T64_K A x + sb B conj(x) through the real
+// 2 x 2 block of the entry pair (as in mk_block_kernel), T64_E A x + B y with
+// an explicit y, T64_H the full-H product of NV / 2 vectors in the sum /
+// difference basis: half-vector 2p is u = x + conj(y) and half-vector 2p + 1 is
+// -i w with w = x - conj(y), since K2 w = i K1 (-i w); both go through K1.
+//
+// What bounds it: below N = 1500 or so the latency of one block's loads and
+// column sums, above it the loads; with the column sums as one six-step
+// wavefront sum per value (18 instructions each) it was bound by those sums.
+// Here a wave sums 16 values at once: four exchange steps (lanes 32, 16, 8
+// and 4 apart) each halve the number of registers instead of summing the same
+// value in every lane, so 16 values take 57 instructions.  All loads of a wave's
+// columns are issued before the first is used (8 columns ahead where A and B
+// take 32 bytes per entry pair, 4 with eight half-vectors, to fit the registers:
+// 95.9 against 107.9 us for four vectors of H in complex128 at N = 4096).
+// Eight waves of 8 columns instead of four of 16 gained 3 % at N <= 1024 and
+// lost up to 45 % above.  Times of a pass with its sum, before and after (us):
+//   N = 1024 complex128: A x 16.0 -> 6.5, H x four vectors 68 -> 16
+//   N = 4096 complex128: K1 64 -> 45 (268 MB), A x four 202 -> 40
+//   N = 4096 hi: K1 53 -> 27 (134 MB), H x four vectors 330 -> 67
+enum { T64_A = 0, T64_K = 1, T64_E = 2, T64_H = 3 };
+
+template <int AR>
+struct Raw1 {
+  nf2 h, l;  // complex64 hi, and lo for HILO
+};
+template <>
+struct Raw1<AR_C128> {
+  nd2 h;
+};
+template <int AR>
+__device__ __forceinline__ void raw1_load(const void* p, const void* q, size_t i, Raw1<AR>& r) {
+  if constexpr (AR == AR_C128) {
+    r.h = static_cast<const nd2*>(p)[i];
+  } else {
+    r.h = static_cast<const nf2*>(p)[i];
+    if constexpr (AR == AR_HILO) r.l = static_cast<const nf2*>(q)[i];
+  }
+}
+template <int AR, typename T>
+__device__ __forceinline__ void raw1_get(const Raw1<AR>& r, T& re, T& im) {
+  if constexpr (AR == AR_HILO) {
+    re = (double)r.h.x + (double)r.l.x;
+    im = (double)r.h.y + (double)r.l.y;
+  } else {
+    re = (T)r.h.x;
+    im = (T)r.h.y;
+  }
+}
+
+// a + b after exchanging halves: lanes with bit 5 (4) of their number clear
+// get a of the lane pair, the others b of it.
+__device__ __forceinline__ double swap32_add(double a, double b) {
+  const auto lo = __builtin_amdgcn_permlane32_swap(__double2loint(a), __double2loint(b), false, false);
+  const auto hi = __builtin_amdgcn_permlane32_swap(__double2hiint(a), __double2hiint(b), false, false);
+  return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+__device__ __forceinline__ double swap16_add(double a, double b) {
+  const auto lo = __builtin_amdgcn_permlane16_swap(__double2loint(a), __double2loint(b), false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap(__double2hiint(a), __double2hiint(b), false, false);
+  return __hiloint2double(hi[0], lo[0]) + __hiloint2double(hi[1], lo[1]);
+}
+// The same with a DPP exchange inside rows of 16 lanes: banks (groups of four
+// lanes) in BA take a of their partner, the others b.
+template <int CTRL, int BA>
+__device__ __forceinline__ double dpp_swap_add(double a, double b) {
+  constexpr int BB = 0xf & ~BA;
+  const int xl = __builtin_amdgcn_update_dpp(__double2loint(a), __double2loint(b), CTRL, 0xf, BB, false);
+  const int xh = __builtin_amdgcn_update_dpp(__double2hiint(a), __double2hiint(b), CTRL, 0xf, BB, false);
+  const int yl = __builtin_amdgcn_update_dpp(__double2loint(b), __double2loint(a), CTRL, 0xf, BA, false);
+  const int yh = __builtin_amdgcn_update_dpp(__double2hiint(b), __double2hiint(a), CTRL, 0xf, BA, false);
+  return __hiloint2double(xh, xl) + __hiloint2double(yh, yl);
+}
+// Sums of 16 values over the wavefront: every lane of group (l >> 2) returns
+// the sum of value sum16_index(l).
+__device__ __forceinline__ double wave_sum16(double (&v)[16]) {
+#pragma unroll
+  for (int i = 0; i < 8; ++i) v[i] = swap32_add(v[2 * i], v[2 * i + 1]);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) v[i] = swap16_add(v[2 * i], v[2 * i + 1]);
+#pragma unroll
+  for (int i = 0; i < 2; ++i) v[i] = dpp_swap_add<0x128, 0x3>(v[2 * i], v[2 * i + 1]);  // row_ror:8
+  double s = dpp_swap_add<0x141, 0x5>(v[0], v[1]);                                      // row_half_mirror
+  s += dpp_f64<0xB1>(s);
+  s += dpp_f64<0x4E>(s);
+  return s;
+}
+__device__ __forceinline__ int sum16_index(int lane) {
+  return ((lane >> 5) & 1) | ((lane >> 3) & 2) | ((lane >> 1) & 4) | ((lane << 1) & 8);
+}
+
+// Half-vector q of the input at row i (zero past n).
+template <int MODE>
+__device__ __forceinline__ double2 t64_input(const double2* __restrict__ V, int64_t ldv, int64_t ldh, int64_t n,
+                                             int conja, const double2* __restrict__ vb, int conjb, double sb, int q,
+                                             int64_t i) {
+  if (i >= n) return make_double2(0.0, 0.0);
+  if constexpr (MODE == T64_H) {
+    const double2 x = V[(size_t)(q >> 1) * ldv + i], y = V[(size_t)(q >> 1) * ldv + ldh + i];
+    if (!(q & 1)) return make_double2(x.x + y.x, x.y - y.y);  // u
+    return make_double2(x.y + y.y, y.x - x.x);                // -i w
+  } else {
+    if (MODE == T64_E && q == 1) {
+      const double2 y = vb[i];
+      return make_double2(sb * y.x, conjb ? -sb * y.y : sb * y.y);
+    }
+    const double2 x = V[(size_t)q * ldv + i];
+    return make_double2(x.x, conja ? -x.y : x.y);
+  }
+}
+
+// V: NV half-vectors (T64_H: NV / 2 full-H columns, bottom at ldh), column q at
+// q ldv.  Partials as in the streaming kernels: rowpart[o][blk][64],
+// colpart[o][blk][64], o = 0 .. NV - 1.
+template <int AR, int MODE, int NV>
 __global__ void __launch_bounds__(kThreads)
-    mh_block_kernel(const void* __restrict__ a0, const void* __restrict__ a1,
-                    const void* __restrict__ b0, const void* __restrict__ b1,
-                    const int2* __restrict__ blkmap, int64_t nblk, int64_t n,
-                    const double2* __restrict__ V, int64_t ldv, int64_t ldh,
-                    double2* __restrict__ rowpart, double2* __restrict__ colpart) {
-  constexpr int RS = R < 256 ? R : 256;
-  constexpr int NS = R / RS;
-  constexpr int RPL = RS / 64;
-  constexpr int CPW = R / 4;
-  constexpr int NO = 2 * NH;
-  __shared__ double2 sh[4][RS];
+    tile64_kernel(const void* __restrict__ a0, const void* __restrict__ a1, const void* __restrict__ b0,
+                  const void* __restrict__ b1, const int2* __restrict__ blkmap, int64_t nblk, int64_t n,
+                  const double2* __restrict__ V, int64_t ldv, int64_t ldh, int conja,
+                  const double2* __restrict__ vb, int conjb, double sb, double2* __restrict__ rowpart,
+                  double2* __restrict__ colpart) {
+  using T = typename Elem<AR>::T;
+  constexpr int WAVES = 4, CPW = 64 / WAVES;
+  constexpr bool HASB = MODE != T64_A;
+  constexpr int NI = MODE == T64_E ? 2 : NV;  // input half-vectors
+  static_assert(MODE != T64_E || NV == 1, "explicit B input: one vector");
+  // values per column (two per output), padded to a power of two; columns per group of 16 values
+  constexpr int VP = NV == 1 ? 2 : NV == 2 ? 4 : NV <= 4 ? 8 : 16;
+  constexpr int CG = 16 / VP;
+  constexpr int DEPTH = (AR == AR_HI || AR == AR_HI64 || !HASB) ? CPW : NV == 8 ? 4 : 8;
+  // column entries of the wave, then (all waves done) the row sums
+  constexpr int LROW = WAVES * NV * 64, LCOL = 64 * NI;
+  __shared__ double2 lds[LROW > LCOL ? LROW : LCOL];
+  __shared__ double csum[WAVES][CPW * VP];  // column sums: [column group][value]
 
   const int blk = blockIdx.x;
-  const int slice = blockIdx.y;
   const int2 pq = blkmap[blk];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int lane = threadIdx.x & 63;
-  const int64_t row0 = (int64_t)pq.x * R + slice * RS, col0 = (int64_t)pq.y * R;
-  const size_t base = (size_t)blk * R * R + (size_t)slice * RS;
+  const int64_t row0 = (int64_t)pq.x * 64, col0 = (int64_t)pq.y * 64 + wave * CPW;
+  const size_t base = (size_t)blk * 4096 + (size_t)wave * CPW * 64 + lane;
 
-  double xr[NH][RPL], xi[NH][RPL], yr[NH][RPL], yi[NH][RPL];
+  Raw1<AR> ra[CPW], rb[HASB ? CPW : 1];
 #pragma unroll
-  for (int q = 0; q < NH; ++q)
+  for (int c = 0; c < DEPTH; ++c) {
+    raw1_load<AR>(a0, a1, base + c * 64, ra[c]);
+    if (HASB) raw1_load<AR>(b0, b1, base + c * 64, rb[c]);
+  }
+  double2* cx = lds + (size_t)wave * CPW * NI;  // [c][input]
 #pragma unroll
-    for (int p = 0; p < RPL; ++p) {
-      const int64_t i = row0 + lane + 64 * p;
-      double2 x = make_double2(0.0, 0.0), y = make_double2(0.0, 0.0);
-      if (i < n) {
-        x = V[(size_t)q * ldv + i];
-        y = V[(size_t)q * ldv + ldh + i];
-      }
-      xr[q][p] = x.x;
-      xi[q][p] = x.y;
-      yr[q][p] = y.x;
-      yi[q][p] = y.y;
-    }
-  double rr[NO][RPL], ri[NO][RPL];
+  for (int e0 = 0; e0 < CPW * NI; e0 += 64) {
+    const int e = e0 + lane;
+    if (e < CPW * NI) cx[e] = t64_input<MODE>(V, ldv, ldh, n, conja, vb, conjb, sb, e % NI, col0 + e / NI);
+  }
+  T xr[NI], xi[NI], rr[NV], ri[NV];
 #pragma unroll
-  for (int o = 0; o < NO; ++o)
+  for (int q = 0; q < NI; ++q) {
+    const double2 x = t64_input<MODE>(V, ldv, ldh, n, conja, vb, conjb, sb, q, row0 + lane);
+    xr[q] = (T)x.x;
+    xi[q] = (T)x.y;
+  }
 #pragma unroll
-    for (int p = 0; p < RPL; ++p) {
-      rr[o][p] = 0.0;
-      ri[o][p] = 0.0;
-    }
+  for (int q = 0; q < NV; ++q) rr[q] = ri[q] = T(0);
+  const T tsb = (T)sb;
+  // this lane's place among the 16 sums of a column group, and the component
+  // it stores (the odd half-vectors of T64_H hold K1 (-i w) = -i K2 w)
+  const int idx = sum16_index(lane);
+  const int sq = (idx % VP) >> 1;
+  const bool swapped = MODE == T64_H && (sq & 1);
+  const int scomp = (idx & 1) ^ (swapped ? 1 : 0);
+  const double ssign = swapped && (idx & 1) ? -1.0 : 1.0;
+  double* cdst = csum[wave] + (idx / VP) * VP + 2 * sq + scomp;
+  wave_lds_sync();
 
-#pragma unroll 2
-  for (int cc = 0; cc < CPW; ++cc) {
-    const int c = wave * CPW + cc;
-    const int64_t j = col0 + c;
-    double cxr[NH], cxi[NH], cyr[NH], cyi[NH];
+  double vals[16];
 #pragma unroll
-    for (int q = 0; q < NH; ++q) {
-      double2 x = make_double2(0.0, 0.0), y = make_double2(0.0, 0.0);
-      if (j < n) {
-        x = V[(size_t)q * ldv + j];
-        y = V[(size_t)q * ldv + ldh + j];
+  for (int c = 0; c < CPW; ++c) {
+    if (DEPTH < CPW && c + DEPTH < CPW) {
+      raw1_load<AR>(a0, a1, base + (c + DEPTH) * 64, ra[c + DEPTH]);
+      if (HASB) raw1_load<AR>(b0, b1, base + (c + DEPTH) * 64, rb[c + DEPTH]);
+    }
+    T ar, ai, br = T(0), bi = T(0);
+    raw1_get<AR, T>(ra[c], ar, ai);
+    if (HASB) raw1_get<AR, T>(rb[c], br, bi);
+    T xc[NI], yc[NI], sr[NV], si[NV];
+#pragma unroll
+    for (int q = 0; q < NI; ++q) {
+      const double2 x = cx[c * NI + q];
+      xc[q] = (T)x.x;
+      yc[q] = (T)x.y;
+    }
+#pragma unroll
+    for (int q = 0; q < NV; ++q) sr[q] = si[q] = T(0);
+    if constexpr (MODE == T64_K || MODE == T64_H) {
+      const T bs = MODE == T64_K ? tsb * br : br, bt = MODE == T64_K ? tsb * bi : bi;  // sb = 1 or -1
+      const T kp = ar + bs, kq = ar - bs, ks = ai + bt, kt = bt - ai;
+#pragma unroll
+      for (int q = 0; q < NV; ++q) {
+        mac(rr[q], kp, xc[q]);
+        mac(rr[q], kt, yc[q]);
+        mac(ri[q], ks, xc[q]);
+        mac(ri[q], kq, yc[q]);
+        mac(sr[q], kp, xr[q]);
+        mac(sr[q], ks, xi[q]);
+        mac(si[q], kt, xr[q]);
+        mac(si[q], kq, xi[q]);
       }
-      cxr[q] = x.x;
-      cxi[q] = x.y;
-      cyr[q] = y.x;
-      cyi[q] = y.y;
-    }
-    double sr[NO], si[NO];
+    } else {
 #pragma unroll
-    for (int o = 0; o < NO; ++o) {
-      sr[o] = 0.0;
-      si[o] = 0.0;
-    }
-    const size_t cbase = base + (size_t)c * R + lane;
-#pragma unroll
-    for (int p = 0; p < RPL; ++p) {
-      double ar, ai, br, bi;
-      Elem<AR>::load(a0, a1, cbase + 64 * p, ar, ai);
-      Elem<AR>::load(b0, b1, cbase + 64 * p, br, bi);
-#pragma unroll
-      for (int q = 0; q < NH; ++q) {
-        // top, row r: A x_c + B y_c
-        rr[2 * q][p] += ar * cxr[q] - ai * cxi[q] + br * cyr[q] - bi * cyi[q];
-        ri[2 * q][p] += ar * cxi[q] + ai * cxr[q] + br * cyi[q] + bi * cyr[q];
-        // bottom (conjugated), row r: A conj(y_c) + B conj(x_c)
-        rr[2 * q + 1][p] += ar * cyr[q] + ai * cyi[q] + br * cxr[q] + bi * cxi[q];
-        ri[2 * q + 1][p] += ai * cyr[q] - ar * cyi[q] + bi * cxr[q] - br * cxi[q];
-        // top, column c: conj(A) x_r + B y_r
-        sr[2 * q] += ar * xr[q][p] + ai * xi[q][p] + br * yr[q][p] - bi * yi[q][p];
-        si[2 * q] += ar * xi[q][p] - ai * xr[q][p] + br * yi[q][p] + bi * yr[q][p];
-        // bottom (conjugated), column c: conj(A) conj(y_r) + B conj(x_r)
-        sr[2 * q + 1] += ar * yr[q][p] - ai * yi[q][p] + br * xr[q][p] + bi * xi[q][p];
-        si[2 * q + 1] += -ar * yi[q][p] - ai * yr[q][p] + bi * xr[q][p] - br * xi[q][p];
+      for (int q = 0; q < NV; ++q) {
+        // row r: A_rc x_c; column c: conj(A_rc) x_r
+        mac(rr[q], ar, xc[q]);
+        mac(rr[q], -ai, yc[q]);
+        mac(ri[q], ar, yc[q]);
+        mac(ri[q], ai, xc[q]);
+        mac(sr[q], ar, xr[q]);
+        mac(sr[q], ai, xi[q]);
+        mac(si[q], ar, xi[q]);
+        mac(si[q], -ai, xr[q]);
+      }
+      if constexpr (MODE == T64_E) {  // + B_rc y_c, + B_rc y_r
+        mac(rr[0], br, xc[1]);
+        mac(rr[0], -bi, yc[1]);
+        mac(ri[0], br, yc[1]);
+        mac(ri[0], bi, xc[1]);
+        mac(sr[0], br, xr[1]);
+        mac(sr[0], -bi, xi[1]);
+        mac(si[0], br, xi[1]);
+        mac(si[0], bi, xr[1]);
       }
     }
 #pragma unroll
-    for (int o = 0; o < NO; ++o) {
-      const double tr = wave_sum(sr[o]), ti = wave_sum(si[o]);
-      if (lane == 0) colpart[(((size_t)o * nblk + blk) * NS + slice) * R + c] = make_double2(tr, ti);
+    for (int j = 0; j < VP; ++j) {
+      double v = 0.0;
+      if (j < 2 * NV) v = (j & 1) ? (double)si[j / 2] : (double)sr[j / 2];
+      vals[(c % CG) * VP + j] = v;
     }
+    if (c % CG == CG - 1) {
+      const double t = wave_sum16(vals);
+      cdst[(c - (CG - 1)) * VP] = ssign * t;  // the four lanes of a group store the same value
+    }
+    // one column at a time: interleaved, the columns' entries and sums would
+    // not fit the registers
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  wave_lds_sync();
+#pragma unroll
+  for (int e0 = 0; e0 < CPW * NV; e0 += 64) {
+    const int e = e0 + lane, q = e / CPW, c = e % CPW;
+    if (e < CPW * NV)
+      colpart[((size_t)q * nblk + blk) * 64 + wave * CPW + c] =
+          make_double2(csum[wave][c * VP + 2 * q], csum[wave][c * VP + 2 * q + 1]);
   }
 
+  __syncthreads();
 #pragma unroll
-  for (int o = 0; o < NO; ++o) {
-#pragma unroll
-    for (int p = 0; p < RPL; ++p) sh[wave][lane + 64 * p] = make_double2(rr[o][p], ri[o][p]);
-    __syncthreads();
-    for (int r = threadIdx.x; r < RS; r += kThreads) {
-      double2 t = sh[0][r];
-#pragma unroll
-      for (int w = 1; w < 4; ++w) {
-        t.x += sh[w][r].x;
-        t.y += sh[w][r].y;
-      }
-      rowpart[((size_t)o * nblk + blk) * R + slice * RS + r] = t;
-    }
-    __syncthreads();
+  for (int q = 0; q < NV; ++q) {
+    const double vx = (double)rr[q], vy = (double)ri[q];
+    lds[(wave * NV + q) * 64 + lane] =
+        (MODE == T64_H && (q & 1)) ? make_double2(-vy, vx) : make_double2(vx, vy);
   }
+  __syncthreads();
+  for (int e = threadIdx.x; e < NV * 64; e += 64 * WAVES) {
+    double2 t = lds[e];
+#pragma unroll
+    for (int w = 1; w < WAVES; ++w) {
+      t.x += lds[w * NV * 64 + e].x;
+      t.y += lds[w * NV * 64 + e].y;
+    }
+    rowpart[((size_t)(e >> 6) * nblk + blk) * 64 + (e & 63)] = t;
+  }
+}
+
+template <int AR, int MODE, int NV>
+void launch_tile64(const Layout& L, const MatPtrs& m, const double2* V, int64_t ldv, int64_t ldh, int conja,
+                   const double2* vb, int conjb, double sb, double2* part, hipStream_t s) {
+  double2* rowpart = part;
+  double2* colpart = part + (size_t)NV * L.nblk * 64;
+  hipLaunchKernelGGL((tile64_kernel<AR, MODE, NV>), dim3((unsigned)L.nblk), dim3(kThreads), 0, s, m.a, m.alo, m.b,
+                     m.blo, L.blkmap, L.nblk, L.n, V, ldv, ldh, conja, vb, conjb, sb, rowpart, colpart);
+}
+
+template <int AR>
+hipError_t tile64_mv(BMode bm, const Layout& L, const MatPtrs& m, const double2* va, int conja, const double2* vb,
+                     int conjb, double sb, double2* part, hipStream_t s) {
+  if (bm == BM_NONE)
+    launch_tile64<AR, T64_A, 1>(L, m, va, 0, 0, conja, nullptr, 0, 1.0, part, s);
+  else if (bm == BM_CONJ)
+    launch_tile64<AR, T64_K, 1>(L, m, va, 0, 0, conja, nullptr, 0, sb, part, s);
+  else
+    launch_tile64<AR, T64_E, 1>(L, m, va, 0, 0, conja, vb, conjb, sb, part, s);
+  return hipGetLastError();
+}
+
+template <int AR>
+hipError_t tile64_mh(int nh, const Layout& L, const MatPtrs& m, const double2* V, int64_t ldv, int64_t ldh,
+                     double2* part, hipStream_t s) {
+  switch (nh) {
+    case 1:
+      launch_tile64<AR, T64_H, 2>(L, m, V, ldv, ldh, 0, nullptr, 0, 1.0, part, s);
+      break;
+    case 2:
+      launch_tile64<AR, T64_H, 4>(L, m, V, ldv, ldh, 0, nullptr, 0, 1.0, part, s);
+      break;
+    case 3:
+      launch_tile64<AR, T64_H, 6>(L, m, V, ldv, ldh, 0, nullptr, 0, 1.0, part, s);
+      break;
+    default:
+      launch_tile64<AR, T64_H, 8>(L, m, V, ldv, ldh, 0, nullptr, 0, 1.0, part, s);
+  }
+  return hipGetLastError();
 }
 
 // rows per workgroup slice of the multi-vector pass: as many as the
@@ -849,8 +819,8 @@ __host__ __device__ constexpr int mk_rows(int nv) { return nv >= 4 ? 128 : (nv >
 // (BM_CONJ: K1 for sb = 1, K2 for sb = -1) for NV vectors in one read of the
 // triangles.  Row r gains A_rc x_c (+ sb B_rc conj(x_c)), column c gains
 // conj(A_rc) x_r (+ sb B_rc conj(x_r)); with B, both through the real 2 x 2
-// block of the entry pair (see the column loop).  Same slicing, lane layout and
-// partial layout as mv_block_kernel, with NV outputs:
+// block of the entry pair (see the column loop).  Same lane and partial
+// layout as mv_stream_kernel, with row slices and NV outputs:
 // rowpart[q][blk][R], colpart[q][blk][slice][R].
 template <int R, int AR, int NV>
 struct MkShape {
@@ -1287,18 +1257,16 @@ __global__ void __launch_bounds__(kThreads)
   }
 }
 
-// Sum of the partials of mh_block_kernel (pairs != 0: output 2q goes to the
-// top of column q of MV, output 2q+1 conjugated and times bsign to its
-// bottom; bsign = 1: M v, -1: H v) or of mk_block_kernel (pairs == 0:
-// output q to column q).  Grid (ceil(n / 64), outputs).  sd != 0 (the
-// streaming full-H kernel): outputs 2q, 2q+1 are K1 u_q and K2 w_q; the
-// workgroup of vector q (grid (ceil(n / 64), vectors)) sums both and writes
-// the top (K1 u + K2 w) / 2 and the conjugated bottom (K1 u - K2 w) / 2.
+// Sum of the partials of a multi-vector pass (sd == 0: output q to column q of
+// MV) or of a full-H product (sd != 0: outputs 2q, 2q+1 are K1 u_q and K2 w_q;
+// the workgroup of vector q sums both and writes the top (K1 u + K2 w) / 2 and
+// the conjugated bottom (K1 u - K2 w) / 2, the bottom times bsign: 1 for M v,
+// -1 for H v).  Grid (ceil(n / 64), vectors).
 template <int W>
 __global__ void __launch_bounds__(64 * W)
     mh_reduce_kernel(const double2* __restrict__ rowpart, const double2* __restrict__ colpart, int R, int NS,
                      int nb, int64_t nblk, int64_t n, double2* __restrict__ MV, int64_t ldv, int64_t ldh,
-                     double bsign, int pairs, const double* __restrict__ dc, double dsg,
+                     double bsign, const double* __restrict__ dc, double dsg,
                      const double2* __restrict__ X, int64_t ldx, int64_t ldhx, int sd) {
   __shared__ double2 sh[W][64];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -1333,56 +1301,36 @@ __global__ void __launch_bounds__(64 * W)
   part_range<W>(rowpart + o * rs, colpart + o * cs, R, NS, nb, P, r, wave, sx, sy);
   const double2 t = wave_order_sum<W>(sh, wave, lane, sx, sy);
   if (wave != 0 || i >= n) return;
-  sx = t.x;
-  sy = t.y;
-  // diagonal correction: output o multiplies A by x_o (mk) or, for the fused
-  // full-H product, by x_q (top) and conj(y_q) (the conjugate of the bottom)
+  double tx = t.x, ty = t.y;
   if (dc) {
     const double f = dsg * dc[i];
-    if (!pairs) {
-      const double2 x = X[(size_t)o * ldx + i];
-      sx = fma(f, x.x, sx);
-      sy = fma(f, x.y, sy);
-    } else if (o & 1) {
-      const double2 y = X[(size_t)(o >> 1) * ldx + ldhx + i];
-      sx = fma(f, y.x, sx);
-      sy = fma(-f, y.y, sy);
-    } else {
-      const double2 x = X[(size_t)(o >> 1) * ldx + i];
-      sx = fma(f, x.x, sx);
-      sy = fma(f, x.y, sy);
-    }
+    const double2 x = X[(size_t)o * ldx + i];
+    tx = fma(f, x.x, tx);
+    ty = fma(f, x.y, ty);
   }
-  if (!pairs) {
-    MV[(size_t)o * ldv + i] = make_double2(sx, sy);
-    return;
-  }
-  const int q = o >> 1;
-  if (o & 1)
-    MV[(size_t)q * ldv + ldh + i] = make_double2(bsign * sx, -bsign * sy);
-  else
-    MV[(size_t)q * ldv + i] = make_double2(sx, sy);
+  MV[(size_t)o * ldv + i] = make_double2(tx, ty);
 }
 
-// ny: outputs (or, sd, vectors) summed
 void launch_mh_reduce(const Layout& L, int ny, int ns, const double2* rowpart, const double2* colpart, double2* MV,
-                      int64_t ldv, int64_t ldh, double bsign, int pairs, const MatPtrs& m, const double2* X,
+                      int64_t ldv, int64_t ldh, double bsign, const MatPtrs& m, const double2* X,
                       int64_t ldx, int64_t ldhx, int sd, hipStream_t s) {
   const dim3 grid((unsigned)((L.n + 63) / 64), (unsigned)ny);
   if (reduce_wide(L))
     hipLaunchKernelGGL(mh_reduce_kernel<16>, grid, dim3(1024), 0, s, rowpart, colpart, L.R, ns, L.nb, L.nblk, L.n,
-                       MV, ldv, ldh, bsign, pairs, m.dc, m.dsign, X, ldx, ldhx, sd);
+                       MV, ldv, ldh, bsign, m.dc, m.dsign, X, ldx, ldhx, sd);
   else
     hipLaunchKernelGGL(mh_reduce_kernel<4>, grid, dim3(256), 0, s, rowpart, colpart, L.R, ns, L.nb, L.nblk, L.n, MV,
-                       ldv, ldh, bsign, pairs, m.dc, m.dsign, X, ldx, ldhx, sd);
+                       ldv, ldh, bsign, m.dc, m.dsign, X, ldx, ldhx, sd);
 }
 
 template <int R, int AR>
 hipError_t launch_mh(int nh, const Layout& L, const MatPtrs& m, const double2* V, int64_t ldv, int64_t ldh,
                      double2* part, hipStream_t s) {
-  double2* rowpart = part;
-  double2* colpart = part + (size_t)2 * nh * L.nblk * R;
-  if constexpr (R >= 128) {
+  if constexpr (R == 64) {
+    return tile64_mh<AR>(nh, L, m, V, ldv, ldh, part, s);
+  } else {
+    double2* rowpart = part;
+    double2* colpart = part + (size_t)2 * nh * L.nblk * R;
     // u, w of every vector over the padded length, after the partials (mh_part_elems)
     const int64_t pl = (int64_t)L.nb * R;
     double2* uw = colpart + (size_t)2 * nh * L.nblk * R;
@@ -1403,22 +1351,6 @@ hipError_t launch_mh(int nh, const Layout& L, const MatPtrs& m, const double2* V
                          L.blkmap, L.nblk, L.n, uw, pl, rowpart, colpart);
     return hipGetLastError();
   }
-  constexpr int NS = 1;  // R = 64: one slice per block
-  const dim3 grid((unsigned)L.nblk, (unsigned)NS);
-  // at most two vectors per launch here; vectors 2q, 2q + 1 write outputs
-  // 4q .. 4q + 3 of the same partial layout
-  for (int q0 = 0; q0 < nh; q0 += 2) {
-    const double2* Vq = V + (size_t)q0 * ldv;
-    double2* rp = rowpart + (size_t)2 * q0 * L.nblk * R;
-    double2* cp = colpart + (size_t)2 * q0 * L.nblk * NS * R;
-    if (nh - q0 == 1)
-      hipLaunchKernelGGL((mh_block_kernel<R, AR, 1>), grid, dim3(kThreads), 0, s, m.a, m.alo, m.b, m.blo,
-                         L.blkmap, L.nblk, L.n, Vq, ldv, ldh, rp, cp);
-    else
-      hipLaunchKernelGGL((mh_block_kernel<R, AR, 2>), grid, dim3(kThreads), 0, s, m.a, m.alo, m.b, m.blo,
-                         L.blkmap, L.nblk, L.n, Vq, ldv, ldh, rp, cp);
-  }
-  return hipGetLastError();
 }
 
 template <int R>
@@ -1432,17 +1364,16 @@ hipError_t dispatch_mh(Arith ar, int nh, const Layout& L, const MatPtrs& m, cons
 template <int R, int AR, int BM>
 hipError_t launch_mv(const Layout& L, const MatPtrs& m, const double2* va, int conja,
                      const double2* vb, int conjb, double sb, double2* part, hipStream_t s) {
-  double2* rowpart = part;
-  double2* colpart = part + (size_t)L.nblk * L.R;
-  if constexpr (R >= 128)
+  if constexpr (R == 64) {
+    return tile64_mv<AR>((BMode)BM, L, m, va, conja, vb, conjb, sb, part, s);
+  } else {
+    double2* rowpart = part;
+    double2* colpart = part + (size_t)L.nblk * L.R;
     hipLaunchKernelGGL((mv_stream_kernel<R, AR, BM>), dim3((unsigned)L.nblk, (unsigned)MvShape<R, AR>::NS),
                        dim3(kThreads), 0, s, m.a, m.alo, m.b, m.blo, L.blkmap, L.n, va, conja, vb, conjb, sb,
                        rowpart, colpart);
-  else
-    hipLaunchKernelGGL((mv_block_kernel<R, AR, BM>), dim3((unsigned)L.nblk, (unsigned)MvShape<R, AR>::NS),
-                       dim3(kThreads), 0, s, m.a, m.alo, m.b, m.blo, L.blkmap, L.n, va, conja, vb, conjb, sb,
-                       rowpart, colpart);
-  return hipGetLastError();
+    return hipGetLastError();
+  }
 }
 
 template <int R, int AR>
@@ -2495,23 +2426,24 @@ hipError_t mh_apply(const Layout& L, Arith ar, const MatPtrs& m, int nh, const d
     e = hipEventRecord(ev1, s);
     if (e != hipSuccess) return e;
   }
-  const int ns = 1;  // one set of column partials per block (both kernels)
   const double2* rowpart = part;
   const double2* colpart = part + (size_t)2 * nh * L.nblk * L.R;
-  const int sd = L.R >= 128;  // the streaming kernel's sum / difference outputs
-  launch_mh_reduce(L, sd ? nh : 2 * nh, ns, rowpart, colpart, MV, ldv, ldh, bsign, 1, m, V, ldv, ldh, sd, s);
+  launch_mh_reduce(L, nh, 1, rowpart, colpart, MV, ldv, ldh, bsign, m, V, ldv, ldh, 1, s);
   return hipGetLastError();
 }
 
 template <int R, int AR, int BM, int NV>
 hipError_t launch_mk(const Layout& L, const MatPtrs& m, const double2* V, int64_t ldv, double sb, double2* part,
                      hipStream_t s) {
-  static_assert(R >= 128, "the multi-vector kernel streams 16-byte segments of at least 128-row slices");
-  using Sh = MkShape<R, AR, NV>;
-  double2* rowpart = part;
-  double2* colpart = part + (size_t)NV * L.nblk * R;
-  hipLaunchKernelGGL((mk_block_kernel<R, AR, BM, NV>), dim3((unsigned)L.nblk, (unsigned)Sh::NS), dim3(kThreads),
-                     0, s, m.a, m.alo, m.b, m.blo, L.blkmap, L.nblk, L.n, V, ldv, sb, rowpart, colpart);
+  if constexpr (R == 64) {
+    launch_tile64<AR, BM == BM_CONJ ? T64_K : T64_A, NV>(L, m, V, ldv, 0, 0, nullptr, 0, sb, part, s);
+  } else {
+    using Sh = MkShape<R, AR, NV>;
+    double2* rowpart = part;
+    double2* colpart = part + (size_t)NV * L.nblk * R;
+    hipLaunchKernelGGL((mk_block_kernel<R, AR, BM, NV>), dim3((unsigned)L.nblk, (unsigned)Sh::NS), dim3(kThreads),
+                       0, s, m.a, m.alo, m.b, m.blo, L.blkmap, L.nblk, L.n, V, ldv, sb, rowpart, colpart);
+  }
   return hipGetLastError();
 }
 
@@ -2563,13 +2495,8 @@ hipError_t mk_apply(const Layout& L, Arith ar, BMode bm, const MatPtrs& m, int n
   }
   switch (L.R) {
     case 64:
-      // small matrices: one-vector passes
-      for (int q = 0; q < nv; ++q) {
-        e = matvec(L, ar, bm, m, V + (size_t)q * ldv, 0, nullptr, 0, sb, part, out + (size_t)q * ldo, s,
-                   q == 0 ? ev0 : nullptr, q == nv - 1 ? ev1 : nullptr);
-        if (e != hipSuccess) return e;
-      }
-      return hipSuccess;
+      e = dispatch_mk<64>(ar, bm, nv, L, m, V, ldv, sb, part, s);
+      break;
     case 128:
       e = dispatch_mk<128>(ar, bm, nv, L, m, V, ldv, sb, part, s);
       break;
@@ -2590,7 +2517,7 @@ hipError_t mk_apply(const Layout& L, Arith ar, BMode bm, const MatPtrs& m, int n
   const int ns = L.R < mk_rows(nv) ? 1 : L.R / mk_rows(nv);
   const double2* rowpart = part;
   const double2* colpart = part + (size_t)nv * L.nblk * L.R;
-  launch_mh_reduce(L, nv, ns, rowpart, colpart, out, ldo, 0, 1.0, 0, m, V, ldv, 0, 0, s);
+  launch_mh_reduce(L, nv, ns, rowpart, colpart, out, ldo, 0, 1.0, m, V, ldv, 0, 0, s);
   return hipGetLastError();
 }
 

@@ -548,6 +548,11 @@ bse_status passes_n(Solver& S, Arith ar, int op, int nv, const double2* v, doubl
 // PH: K1 metric through P = K1 U), CGS twice per column.  With rec >= 0 the
 // coefficients are those of the product of block [rec, rec + nb): column
 // rec + q of Tc gains rows c .. c + q (the upper triangular factor).
+// Where the basis (PH: with its partners) already spans the whole space the
+// columns are rounding noise, whose <w, K1 w> may have either sign and says
+// nothing about M: the flag is left alone there (flag_at).
+int* flag_at(const Solver& S, int64_t c, int64_t dim) { return c >= dim ? nullptr : S.flag; }
+
 bse_status orth_block(Solver& S, int c, int nb, int rec) {
   bse_handle h = S.h;
   for (int q = 0; q < nb; ++q) {
@@ -563,7 +568,7 @@ bse_status orth_block(Solver& S, int c, int nb, int rec) {
                                  S.s));
     }
     double* bt = rec >= 0 ? (double*)(S.Tc + (size_t)(rec + q) * S.ldT + c + q) : nullptr;
-    HIP_TRY(h, bse::normalize(w, z, S.n, nullptr, nullptr, 0, nullptr, bt, 0, S.flag, S.red, S.s));
+    HIP_TRY(h, bse::normalize(w, z, S.n, nullptr, nullptr, 0, nullptr, bt, 0, flag_at(S, c + q, S.n), S.red, S.s));
   }
   return BSE_OK;
 }
@@ -935,7 +940,8 @@ bse_status step_g(Solver& S, Arith ar, int c) {
   HIP_TRY(h, bse::cdot(KU, c + 1, KPG, c + 1, ld, v, n, S.cpart, S.H1, S.s));
   HIP_TRY(h, bse::cgemv_sub(U, c + 1, PG, c + 1, KU, KPG, ld, S.H1, 2, v, kv, n, S.s));
   HIP_TRY(h, bse::acc_cols(Cc, S.ldT, S.H1, S.ncolmax, c + 1, 1, 1, S.s));
-  HIP_TRY(h, bse::normalize(v, kv, n, nullptr, nullptr, 0, nullptr, (double*)(Cc + c + 1), 0, S.flag, S.red, S.s));
+  HIP_TRY(h, bse::normalize(v, kv, n, nullptr, nullptr, 0, nullptr, (double*)(Cc + c + 1), 0,
+                            flag_at(S, c + 1, n), S.red, S.s));
   HIP_TRY(h, ot.end());
   if (ar == bse::AR_HI || ar == bse::AR_HI64)
     S.steps32 += 1;
@@ -1120,7 +1126,7 @@ bse_status orth_block_m(Solver& S, int c, int nb, int rec) {
         HIP_TRY(h, bse::acc_cols(S.Tc + (size_t)(rec + q) * S.ldT + c, S.ldT, S.H3, S.ncolmax, q, 1, 0, S.s));
     }
     double* bt = rec >= 0 ? (double*)(S.Tc + (size_t)(rec + q) * S.ldT + c + q) : nullptr;
-    HIP_TRY(h, bse::normalize(w, z, n2, nullptr, nullptr, 0, nullptr, bt, 0, S.flag, S.red, S.s));
+    HIP_TRY(h, bse::normalize(w, z, n2, nullptr, nullptr, 0, nullptr, bt, 0, flag_at(S, c + q, 2 * S.n), S.red, S.s));
   }
   return BSE_OK;
 }
