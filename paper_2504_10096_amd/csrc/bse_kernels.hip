@@ -569,22 +569,36 @@ __device__ __forceinline__ double dpp_swap_add(double a, double b) {
   const int yh = __builtin_amdgcn_update_dpp(__double2hiint(b), __double2hiint(a), CTRL, 0xf, BA, false);
   return __hiloint2double(xh, xl) + __hiloint2double(yh, yl);
 }
-// Sums of 16 values over the wavefront: every lane of group (l >> 2) returns
-// the sum of value sum16_index(l).
-__device__ __forceinline__ double wave_sum16(double (&v)[16]) {
+// Sums of N = 4, 8 or 16 values over the wavefront: every lane returns the sum
+// of value wave_sum_index<N>(lane).
+template <int N>
+__device__ __forceinline__ double wave_sum_n(double (&v)[N]) {
+  static_assert(N == 4 || N == 8 || N == 16, "4, 8 or 16 values");
 #pragma unroll
-  for (int i = 0; i < 8; ++i) v[i] = swap32_add(v[2 * i], v[2 * i + 1]);
+  for (int i = 0; i < N / 2; ++i) v[i] = swap32_add(v[2 * i], v[2 * i + 1]);
 #pragma unroll
-  for (int i = 0; i < 4; ++i) v[i] = swap16_add(v[2 * i], v[2 * i + 1]);
+  for (int i = 0; i < N / 4; ++i) v[i] = swap16_add(v[2 * i], v[2 * i + 1]);
+  if constexpr (N >= 8) {
 #pragma unroll
-  for (int i = 0; i < 2; ++i) v[i] = dpp_swap_add<0x128, 0x3>(v[2 * i], v[2 * i + 1]);  // row_ror:8
-  double s = dpp_swap_add<0x141, 0x5>(v[0], v[1]);                                      // row_half_mirror
-  s += dpp_f64<0xB1>(s);
-  s += dpp_f64<0x4E>(s);
+    for (int i = 0; i < N / 8; ++i) v[i] = dpp_swap_add<0x128, 0x3>(v[2 * i], v[2 * i + 1]);  // row_ror:8
+  } else {
+    v[0] += dpp_f64<0x128>(v[0]);
+  }
+  double s;
+  if constexpr (N == 16)
+    s = dpp_swap_add<0x141, 0x5>(v[0], v[1]);  // row_half_mirror
+  else
+    s = v[0] + dpp_f64<0x141>(v[0]);
+  s += dpp_f64<0xB1>(s);  // quad_perm: lane xor 1
+  s += dpp_f64<0x4E>(s);  // lane xor 2
   return s;
 }
-__device__ __forceinline__ int sum16_index(int lane) {
-  return ((lane >> 5) & 1) | ((lane >> 3) & 2) | ((lane >> 1) & 4) | ((lane << 1) & 8);
+template <int N>
+__device__ __forceinline__ int wave_sum_index(int lane) {
+  int i = ((lane >> 5) & 1) | ((lane >> 3) & 2);
+  if (N >= 8) i |= (lane >> 1) & 4;
+  if (N == 16) i |= (lane << 1) & 8;
+  return i;
 }
 
 // Half-vector q of the input at row i (zero past n).
@@ -662,7 +676,7 @@ __global__ void __launch_bounds__(kThreads)
   const T tsb = (T)sb;
   // this lane's place among the 16 sums of a column group, and the component
   // it stores (the odd half-vectors of T64_H hold K1 (-i w) = -i K2 w)
-  const int idx = sum16_index(lane);
+  const int idx = wave_sum_index<16>(lane);
   const int sq = (idx % VP) >> 1;
   const bool swapped = MODE == T64_H && (sq & 1);
   const int scomp = (idx & 1) ^ (swapped ? 1 : 0);
@@ -734,7 +748,7 @@ __global__ void __launch_bounds__(kThreads)
       vals[(c % CG) * VP + j] = v;
     }
     if (c % CG == CG - 1) {
-      const double t = wave_sum16(vals);
+      const double t = wave_sum_n<16>(vals);
       cdst[(c - (CG - 1)) * VP] = ssign * t;  // the four lanes of a group store the same value
     }
     // one column at a time: interleaved, the columns' entries and sums would
@@ -1467,16 +1481,81 @@ __global__ void __launch_bounds__(kThreads)
 }
 
 // -------------------------------------------------- orthogonalization (CGS)
+// h[q ncol + c] = sum_i conj(V[i, c]) w_q[i] for the NW vectors w_q = W + q ldw
+// (NW = 1: columns of V0, then of V1), in one launch: a workgroup of 16 waves
+// takes two columns, wave w rows 64 (w + 16 t) + lane; the waves' sums meet in
+// LDS and are added in wave order.  For vectors up to kDotRows rows, where the
+// chunk partials of cdot_part_kernel and their sum in a second launch are
+// latency only: n = 4096, 64 columns 8.0 us for both launches, 3.3 us here;
+// n = 10048 8.1 against 5.2 us; at n = 20736 a wave's 20 row steps take longer
+// (8 columns: 5.6 against 8.4 us).  Four columns per workgroup leave half the
+// workgroups and took 4.2 us at n = 4096.
+constexpr int64_t kDotRows = 12288;
+template <int NW>
+__global__ void __launch_bounds__(1024)
+    cdot_short_kernel(const double2* __restrict__ V0, int n0, const double2* __restrict__ V1, int n1, int64_t ld,
+                      const double2* __restrict__ W, int64_t ldw, int64_t n, double2* __restrict__ h) {
+  constexpr int CB = 2, NVAL = 2 * CB * NW;
+  constexpr int GV = NVAL % 16 == 0 ? 16 : NVAL % 8 == 0 ? 8 : 4;  // values per wavefront sum
+  static_assert(NVAL % GV == 0, "whole groups of values");
+  __shared__ double red[16][NVAL];
+  const int ncol = n0 + n1;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int c0 = blockIdx.x * CB;
+  const double2* col[CB];
+#pragma unroll
+  for (int u = 0; u < CB; ++u) {
+    const int c = c0 + u < ncol ? c0 + u : c0;  // past the end: a valid column, result unused
+    col[u] = c < n0 ? V0 + (size_t)c * ld : V1 + (size_t)(c - n0) * ld;
+  }
+  double vals[NVAL];  // value 2 (q CB + u) + component
+#pragma unroll
+  for (int j = 0; j < NVAL; ++j) vals[j] = 0.0;
+#pragma unroll 4
+  for (int64_t i = wave * 64 + lane; i < n; i += 1024) {
+    double2 v[CB], w[NW];
+#pragma unroll
+    for (int u = 0; u < CB; ++u) v[u] = col[u][i];
+#pragma unroll
+    for (int q = 0; q < NW; ++q) w[q] = W[(size_t)q * ldw + i];
+#pragma unroll
+    for (int q = 0; q < NW; ++q)
+#pragma unroll
+      for (int u = 0; u < CB; ++u) {
+        const int j = 2 * (q * CB + u);
+        mac(vals[j], v[u].x, w[q].x);
+        mac(vals[j], v[u].y, w[q].y);
+        mac(vals[j + 1], v[u].x, w[q].y);
+        mac(vals[j + 1], -v[u].y, w[q].x);
+      }
+  }
+#pragma unroll
+  for (int g = 0; g < NVAL / GV; ++g) {
+    double t[GV];
+#pragma unroll
+    for (int j = 0; j < GV; ++j) t[j] = vals[g * GV + j];
+    red[wave][g * GV + wave_sum_index<GV>(lane)] = wave_sum_n<GV>(t);
+  }
+  __syncthreads();
+  for (int j = threadIdx.x; j < NVAL; j += 1024) {
+    double t = red[0][j];
+#pragma unroll
+    for (int w = 1; w < 16; ++w) t += red[w][j];
+    const int q = j / (2 * CB), u = (j / 2) % CB;
+    if (c0 + u < ncol) reinterpret_cast<double*>(h)[2 * ((size_t)q * ncol + c0 + u) + (j & 1)] = t;
+  }
+}
+
 // part[chunk * ncol + c] = sum over the 256-row chunk of conj(V[i, c]) w[i].
-// Grid (chunks, ceil(ncol / 64)); wave w of the group handles 16 columns,
-// four at a time: the 16 loads of four columns are issued together, then the
+// Grid (chunks, ceil(ncol / (4 cpw))); wave w of the group handles cpw columns
+// (dot_cpw), four at a time: the 16 loads of four columns are issued together, then the
 // eight sums over the wavefront go through LDS (lds_group_sum: eight values
 // per lane in, one sum per eight-lane group out); lane l holds rows
 // l + 64 s (s < 4) of w in registers.
 __global__ void __launch_bounds__(kThreads)
     cdot_part_kernel(const double2* __restrict__ V0, int n0, const double2* __restrict__ V1,
                      int n1, int64_t ld, const double2* __restrict__ w, int64_t n,
-                     double2* __restrict__ part) {
+                     double2* __restrict__ part, int cpw) {
   __shared__ double stg[4][8 * stage_ld(8)];  // per wave: the column-sum stage
   const int ncol = n0 + n1;
   const int64_t r0 = (int64_t)blockIdx.x * kChunk;
@@ -1491,8 +1570,8 @@ __global__ void __launch_bounds__(kThreads)
     wr[s] = v.x;
     wi[s] = v.y;
   }
-  const int cbeg = blockIdx.y * 64 + wave * 16;
-  const int cend = min(cbeg + 16, ncol);
+  const int cbeg = (blockIdx.y * 4 + wave) * cpw;
+  const int cend = min(cbeg + cpw, ncol);
   for (int t0 = cbeg; t0 < cend; t0 += 4) {
     double2 v[4][4];
 #pragma unroll
@@ -1548,16 +1627,60 @@ __global__ void __launch_bounds__(kThreads)
 // w[i] -= sum_c V[i, c] h[c];  z[i] -= sum_c P[i, c] h[c] (WithZ).
 // real_h 1: h[c] -> Re h[c]; 2: Re h[c] on the first n0 columns and
 // i Im h[c] on the others (a real coefficient on each basis vector and on
-// each i-multiple of the second basis).  One row per thread; the column
-// loops of the two bases are separate and unrolled so that several loads are
-// in flight per thread (the loop is latency-bound otherwise).
+// each i-multiple of the second basis).
+//
+// A workgroup takes 256 / CG rows, thread group g of CG the g-th share of the
+// columns, whose sums meet in LDS in group order.  One row per thread with all
+// its columns, as this kernel was first written, is a serial chain on a few CUs
+// for short vectors (n = 4096: 16 workgroups, 19 us for 200 columns of V and P
+// against 4.6 us in 16 groups); at HBM-bound lengths the groups cost nothing
+// (gemv_groups).  The column loops of the two bases are separate and take
+// batches of 8 columns so that several loads are in flight per thread.
 template <bool WithZ>
+__device__ __forceinline__ void gemv_range(const double2* __restrict__ V, const double2* __restrict__ P, int64_t ld,
+                                           const double2* hs, int c, int end, int64_t i, double& ar, double& ai,
+                                           double& br, double& bi) {
+  // batches of 8 columns: all loads of a batch are issued before the first use
+  for (; c + 8 <= end; c += 8) {
+    double2 v[8], q[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = V[(size_t)(c + u) * ld + i];
+    if (WithZ) {
+#pragma unroll
+      for (int u = 0; u < 8; ++u) q[u] = P[(size_t)(c + u) * ld + i];
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const double2 hc = hs[c + u];
+      ar += v[u].x * hc.x - v[u].y * hc.y;
+      ai += v[u].x * hc.y + v[u].y * hc.x;
+      if (WithZ) {
+        br += q[u].x * hc.x - q[u].y * hc.y;
+        bi += q[u].x * hc.y + q[u].y * hc.x;
+      }
+    }
+  }
+  for (; c < end; ++c) {
+    const double2 hc = hs[c];
+    const double2 v = V[(size_t)c * ld + i];
+    ar += v.x * hc.x - v.y * hc.y;
+    ai += v.x * hc.y + v.y * hc.x;
+    if (WithZ) {
+      const double2 q = P[(size_t)c * ld + i];
+      br += q.x * hc.x - q.y * hc.y;
+      bi += q.x * hc.y + q.y * hc.x;
+    }
+  }
+}
+
+template <bool WithZ, int CG>
 __global__ void __launch_bounds__(kThreads)
     cgemv_sub_kernel(const double2* __restrict__ V0, int n0, const double2* __restrict__ V1, int n1,
                      const double2* __restrict__ P0, const double2* __restrict__ P1, int64_t ld,
                      const double2* __restrict__ h, int real_h, double2* __restrict__ w,
                      double2* __restrict__ z, int64_t n) {
-  extern __shared__ double2 hs[];
+  extern __shared__ double2 hs[];  // the coefficients, then the groups' sums
+  constexpr int RW = kThreads / CG;
   const int ncol = n0 + n1;
   for (int c = threadIdx.x; c < ncol; c += kThreads) {
     double2 v = h[c];
@@ -1568,44 +1691,26 @@ __global__ void __launch_bounds__(kThreads)
     hs[c] = v;
   }
   __syncthreads();
-  const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (i >= n) return;
+  const int r = threadIdx.x % RW, g = threadIdx.x / RW;
+  const int64_t i = (int64_t)blockIdx.x * RW + r;
   double ar = 0.0, ai = 0.0, br = 0.0, bi = 0.0;
-  for (int part = 0; part < 2; ++part) {
-    const double2* __restrict__ V = part ? V1 : V0;
-    const double2* __restrict__ P = part ? P1 : P0;
-    const int cnt = part ? n1 : n0, off = part ? n0 : 0;
-    int c = 0;
-    // batches of 8 columns: all loads of a batch are issued before the first use
-    for (; c + 8 <= cnt; c += 8) {
-      double2 v[8], q[8];
+  if (i < n) {
+    const int c0 = (int)((int64_t)ncol * g / CG), c1 = (int)((int64_t)ncol * (g + 1) / CG);
+    if (c0 < n0) gemv_range<WithZ>(V0, P0, ld, hs, c0, min(c1, n0), i, ar, ai, br, bi);
+    if (c1 > n0) gemv_range<WithZ>(V1, P1, ld, hs + n0, max(c0 - n0, 0), c1 - n0, i, ar, ai, br, bi);
+  }
+  __syncthreads();
+  hs[threadIdx.x] = make_double2(ar, ai);
+  if (WithZ) hs[kThreads + threadIdx.x] = make_double2(br, bi);
+  __syncthreads();
+  if (g != 0 || i >= n) return;
 #pragma unroll
-      for (int u = 0; u < 8; ++u) v[u] = V[(size_t)(c + u) * ld + i];
-      if (WithZ) {
-#pragma unroll
-        for (int u = 0; u < 8; ++u) q[u] = P[(size_t)(c + u) * ld + i];
-      }
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const double2 hc = hs[off + c + u];
-        ar += v[u].x * hc.x - v[u].y * hc.y;
-        ai += v[u].x * hc.y + v[u].y * hc.x;
-        if (WithZ) {
-          br += q[u].x * hc.x - q[u].y * hc.y;
-          bi += q[u].x * hc.y + q[u].y * hc.x;
-        }
-      }
-    }
-    for (; c < cnt; ++c) {
-      const double2 hc = hs[off + c];
-      const double2 v = V[(size_t)c * ld + i];
-      ar += v.x * hc.x - v.y * hc.y;
-      ai += v.x * hc.y + v.y * hc.x;
-      if (WithZ) {
-        const double2 q = P[(size_t)c * ld + i];
-        br += q.x * hc.x - q.y * hc.y;
-        bi += q.x * hc.y + q.y * hc.x;
-      }
+  for (int t = 1; t < CG; ++t) {
+    ar += hs[t * RW + r].x;
+    ai += hs[t * RW + r].y;
+    if (WithZ) {
+      br += hs[kThreads + t * RW + r].x;
+      bi += hs[kThreads + t * RW + r].y;
     }
   }
   double2 wv = w[i];
@@ -1628,7 +1733,7 @@ __global__ void __launch_bounds__(kThreads)
 template <int NW>
 __global__ void __launch_bounds__(kThreads)
     cdotm_part_kernel(const double2* __restrict__ V, int ncol, int64_t ld, const double2* __restrict__ W,
-                      int64_t ldw, int64_t n, double2* __restrict__ part) {
+                      int64_t ldw, int64_t n, double2* __restrict__ part, int cpw) {
   __shared__ double stg[4][8 * stage_ld(8)];  // per wave: the column-sum stage
   const int64_t r0 = (int64_t)blockIdx.x * kChunk;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
@@ -1644,8 +1749,8 @@ __global__ void __launch_bounds__(kThreads)
       wr[q][s] = v.x;
       wi[q][s] = v.y;
     }
-  const int cbeg = blockIdx.y * 64 + wave * 16;
-  const int cend = min(cbeg + 16, ncol);
+  const int cbeg = (blockIdx.y * 4 + wave) * cpw;
+  const int cend = min(cbeg + cpw, ncol);
   for (int t0 = cbeg; t0 < cend; t0 += 4) {
     double2 v[4][4];
 #pragma unroll
@@ -1686,43 +1791,59 @@ __global__ void __launch_bounds__(kThreads)
   }
 }
 
-// w_q[i] -= sum_c V[i, c] h[q ldh + c] for q < NW: one row per thread, each
-// basis entry loaded once for all NW vectors.
-template <int NW>
+// w_q[i] -= sum_c V[i, c] h[q ldh + c] for q < NW, each basis entry loaded once
+// for all NW vectors; rows and column groups as in cgemv_sub_kernel.
+template <int NW, int CG>
 __global__ void __launch_bounds__(kThreads)
     cgemvm_sub_kernel(const double2* __restrict__ V, int ncol, int64_t ld, const double2* __restrict__ h,
                       int ldh, double2* __restrict__ W, int64_t ldw, int64_t n) {
-  extern __shared__ double2 hs[];  // NW * ncol coefficients
+  extern __shared__ double2 hs[];  // NW * ncol coefficients, then the groups' sums
+  constexpr int RW = kThreads / CG;
   for (int t = threadIdx.x; t < NW * ncol; t += kThreads) hs[t] = h[(size_t)(t / ncol) * ldh + t % ncol];
   __syncthreads();
-  const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
-  if (i >= n) return;
+  const int r = threadIdx.x % RW, g = threadIdx.x / RW;
+  const int64_t i = (int64_t)blockIdx.x * RW + r;
   double ar[NW], ai[NW];
 #pragma unroll
   for (int q = 0; q < NW; ++q) ar[q] = ai[q] = 0.0;
-  int c = 0;
-  for (; c + 8 <= ncol; c += 8) {
-    double2 v[8];
+  if (i < n) {
+    int c = (int)((int64_t)ncol * g / CG);
+    const int end = (int)((int64_t)ncol * (g + 1) / CG);
+    for (; c + 8 <= end; c += 8) {
+      double2 v[8];
 #pragma unroll
-    for (int u = 0; u < 8; ++u) v[u] = V[(size_t)(c + u) * ld + i];
+      for (int u = 0; u < 8; ++u) v[u] = V[(size_t)(c + u) * ld + i];
 #pragma unroll
-    for (int u = 0; u < 8; ++u)
+      for (int u = 0; u < 8; ++u)
+#pragma unroll
+        for (int q = 0; q < NW; ++q) {
+          const double2 hc = hs[q * ncol + c + u];
+          ar[q] += v[u].x * hc.x - v[u].y * hc.y;
+          ai[q] += v[u].x * hc.y + v[u].y * hc.x;
+        }
+    }
+    for (; c < end; ++c) {
+      const double2 v = V[(size_t)c * ld + i];
 #pragma unroll
       for (int q = 0; q < NW; ++q) {
-        const double2 hc = hs[q * ncol + c + u];
-        ar[q] += v[u].x * hc.x - v[u].y * hc.y;
-        ai[q] += v[u].x * hc.y + v[u].y * hc.x;
+        const double2 hc = hs[q * ncol + c];
+        ar[q] += v.x * hc.x - v.y * hc.y;
+        ai[q] += v.x * hc.y + v.y * hc.x;
       }
-  }
-  for (; c < ncol; ++c) {
-    const double2 v = V[(size_t)c * ld + i];
-#pragma unroll
-    for (int q = 0; q < NW; ++q) {
-      const double2 hc = hs[q * ncol + c];
-      ar[q] += v.x * hc.x - v.y * hc.y;
-      ai[q] += v.x * hc.y + v.y * hc.x;
     }
   }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < NW; ++q) hs[q * kThreads + threadIdx.x] = make_double2(ar[q], ai[q]);
+  __syncthreads();
+  if (g != 0 || i >= n) return;
+#pragma unroll
+  for (int q = 0; q < NW; ++q)
+#pragma unroll
+    for (int t = 1; t < CG; ++t) {
+      ar[q] += hs[q * kThreads + t * RW + r].x;
+      ai[q] += hs[q * kThreads + t * RW + r].y;
+    }
 #pragma unroll
   for (int q = 0; q < NW; ++q) {
     double2 wv = W[(size_t)q * ldw + i];
@@ -1747,17 +1868,10 @@ __global__ void __launch_bounds__(kThreads)
   if (threadIdx.x == 0) part[blockIdx.x] = s;
 }
 
-// Every workgroup sums the chunk partials in the same order (identical
-// beta everywhere), then scales its rows; workgroup 0 records alpha, beta.
-__global__ void __launch_bounds__(kThreads)
-    normalize_kernel(double2* __restrict__ w, double2* __restrict__ z, int64_t n,
-                     const double* __restrict__ part, int64_t nch, const double2* __restrict__ h1,
-                     const double2* __restrict__ h2, int jh, double* __restrict__ alpha,
-                     double* __restrict__ beta, int j, int* __restrict__ flag) {
-  __shared__ double sh[4];
-  double s = 0.0;
-  for (int64_t k = threadIdx.x; k < nch; k += kThreads) s += part[k];
-  const double b2 = block_sum(s, sh);
+// 1 / beta of beta^2 = b2; the first thread of the grid records alpha, beta.
+__device__ __forceinline__ double norm_scale(double b2, const double2* __restrict__ h1, const double2* __restrict__ h2,
+                                             int jh, double* __restrict__ alpha, double* __restrict__ beta, int j,
+                                             int* __restrict__ flag) {
   // b2 < 0: the K1 metric is indefinite (M not positive definite);
   // b2 == 0: exact breakdown (invariant subspace), the vector stays zero.
   const bool nonfinite = !isfinite(b2);
@@ -1770,9 +1884,22 @@ __global__ void __launch_bounds__(kThreads)
     // the first failure is the one reported (later ones are its consequences)
     if (flag && (nonfinite || indefinite) && flag[0] == 0) flag[0] = nonfinite ? 2 : 1;
   }
+  return 1.0 / bt;
+}
+
+// Every workgroup sums the chunk partials in the same order (identical
+// beta everywhere).
+__global__ void __launch_bounds__(kThreads)
+    normalize_kernel(double2* __restrict__ w, double2* __restrict__ z, int64_t n,
+                     const double* __restrict__ part, int64_t nch, const double2* __restrict__ h1,
+                     const double2* __restrict__ h2, int jh, double* __restrict__ alpha,
+                     double* __restrict__ beta, int j, int* __restrict__ flag) {
+  __shared__ double sh[4];
+  double s = 0.0;
+  for (int64_t k = threadIdx.x; k < nch; k += kThreads) s += part[k];
+  const double inv = norm_scale(block_sum(s, sh), h1, h2, jh, alpha, beta, j, flag);
   const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   if (i >= n) return;
-  const double inv = 1.0 / bt;
   double2 a = w[i];
   a.x *= inv;
   a.y *= inv;
@@ -1782,6 +1909,44 @@ __global__ void __launch_bounds__(kThreads)
     b.x *= inv;
     b.y *= inv;
     z[i] = b;
+  }
+}
+
+// The dot product and the scaling of a short vector in one launch: one
+// workgroup of 1024 threads holds up to 4 rows of w and z per thread in
+// registers between the two (n = 1024 5.2 -> 3.3 us, 4096 5.2 -> 4.2 us, level
+// at 8192).
+constexpr int64_t kNormRows = 4096;
+__global__ void __launch_bounds__(1024)
+    normalize_short_kernel(double2* __restrict__ w, double2* __restrict__ z, int64_t n,
+                           const double2* __restrict__ h1, const double2* __restrict__ h2, int jh,
+                           double* __restrict__ alpha, double* __restrict__ beta, int j, int* __restrict__ flag) {
+  __shared__ double sh[16];
+  constexpr int NR = kNormRows / 1024;
+  const bool two = z && z != w;
+  double2 a[NR], b[NR];
+#pragma unroll
+  for (int r = 0; r < NR; ++r) {
+    const int64_t i = threadIdx.x + 1024 * r;
+    a[r] = i < n ? w[i] : make_double2(0.0, 0.0);
+    b[r] = !two ? a[r] : i < n ? z[i] : make_double2(0.0, 0.0);
+  }
+  double s = 0.0;
+#pragma unroll
+  for (int r = 0; r < NR; ++r) s += a[r].x * b[r].x + a[r].y * b[r].y;
+  s = wave_sum(s);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = s;
+  __syncthreads();
+  double b2 = 0.0;
+#pragma unroll
+  for (int q = 0; q < 16; ++q) b2 += sh[q];
+  const double inv = norm_scale(b2, h1, h2, jh, alpha, beta, j, flag);
+#pragma unroll
+  for (int r = 0; r < NR; ++r) {
+    const int64_t i = threadIdx.x + 1024 * r;
+    if (i >= n) break;
+    w[i] = make_double2(a[r].x * inv, a[r].y * inv);
+    if (two) z[i] = make_double2(b[r].x * inv, b[r].y * inv);
   }
 }
 
@@ -2530,67 +2695,100 @@ hipError_t ingest(const Layout& L, bool is_a, bool hilo, const void* src, bool s
   return hipGetLastError();
 }
 
+// Columns per wave of the chunked dot products: 16 where the chunks and column
+// groups fill the chip, else 4 (more workgroups, each one batch of loads long).
+int dot_cpw(int64_t nch, int ncol) { return nch * ((ncol + 63) / 64) < 1024 ? 4 : 16; }
+
 hipError_t cdot(const double2* V0, int n0, const double2* V1, int n1, int64_t ld, const double2* w,
                 int64_t n, double2* part, double2* h, hipStream_t s) {
   const int ncol = n0 + n1;
   if (ncol == 0) return hipSuccess;
+  if (n <= kDotRows) {
+    hipLaunchKernelGGL(cdot_short_kernel<1>, dim3((unsigned)((ncol + 1) / 2)), dim3(1024), 0, s, V0, n0, V1, n1, ld, w, (int64_t)0, n, h);
+    return hipGetLastError();
+  }
   const int64_t nch = nchunks(n);
-  hipLaunchKernelGGL(cdot_part_kernel, dim3((unsigned)nch, (unsigned)((ncol + 63) / 64)),
-                     dim3(kThreads), 0, s, V0, n0, V1, n1, ld, w, n, part);
+  const int cpw = dot_cpw(nch, ncol);
+  hipLaunchKernelGGL(cdot_part_kernel, dim3((unsigned)nch, (unsigned)((ncol + 4 * cpw - 1) / (4 * cpw))),
+                     dim3(kThreads), 0, s, V0, n0, V1, n1, ld, w, n, part, cpw);
   hipLaunchKernelGGL(colsum_kernel, dim3((unsigned)((ncol + 3) / 4)), dim3(kThreads), 0, s, part, nch, ncol, h);
+  return hipGetLastError();
+}
+
+template <int NW>
+hipError_t launch_cdotm(const double2* V, int ncol, int64_t ld, const double2* W, int64_t ldw, int64_t n,
+                        double2* part, double2* h, hipStream_t s) {
+  if (n <= kDotRows) {
+    hipLaunchKernelGGL(cdot_short_kernel<NW>, dim3((unsigned)((ncol + 1) / 2)), dim3(1024), 0, s, V, ncol, nullptr, 0, ld, W, ldw, n, h);
+    return hipGetLastError();
+  }
+  const int64_t nch = nchunks(n);
+  const int cpw = dot_cpw(nch, ncol);
+  hipLaunchKernelGGL(cdotm_part_kernel<NW>, dim3((unsigned)nch, (unsigned)((ncol + 4 * cpw - 1) / (4 * cpw))),
+                     dim3(kThreads), 0, s, V, ncol, ld, W, ldw, n, part, cpw);
+  hipLaunchKernelGGL(colsum_kernel, dim3((unsigned)((NW * ncol + 3) / 4)), dim3(kThreads), 0, s, part, nch, NW * ncol,
+                     h);
   return hipGetLastError();
 }
 
 hipError_t cdotm(const double2* V, int ncol, int64_t ld, const double2* W, int64_t ldw, int nw, int64_t n,
                  double2* part, double2* h, hipStream_t s) {
   if (ncol == 0) return hipSuccess;
-  const int64_t nch = nchunks(n);
-  const dim3 grid((unsigned)nch, (unsigned)((ncol + 63) / 64));
   switch (nw) {
     case 1:
-      hipLaunchKernelGGL(cdotm_part_kernel<1>, grid, dim3(kThreads), 0, s, V, ncol, ld, W, ldw, n, part);
-      break;
+      return launch_cdotm<1>(V, ncol, ld, W, ldw, n, part, h, s);
     case 2:
-      hipLaunchKernelGGL(cdotm_part_kernel<2>, grid, dim3(kThreads), 0, s, V, ncol, ld, W, ldw, n, part);
-      break;
+      return launch_cdotm<2>(V, ncol, ld, W, ldw, n, part, h, s);
     case 3:
-      hipLaunchKernelGGL(cdotm_part_kernel<3>, grid, dim3(kThreads), 0, s, V, ncol, ld, W, ldw, n, part);
-      break;
+      return launch_cdotm<3>(V, ncol, ld, W, ldw, n, part, h, s);
     case 4:
-      hipLaunchKernelGGL(cdotm_part_kernel<4>, grid, dim3(kThreads), 0, s, V, ncol, ld, W, ldw, n, part);
-      break;
+      return launch_cdotm<4>(V, ncol, ld, W, ldw, n, part, h, s);
     default:
       return hipErrorInvalidValue;
   }
-  hipLaunchKernelGGL(colsum_kernel, dim3((unsigned)((nw * ncol + 3) / 4)), dim3(kThreads), 0, s, part, nch,
-                     nw * ncol, h);
-  return hipGetLastError();
+}
+
+// Column groups of the basis updates (cgemv_sub_kernel) by the rows n, from
+// updates of two vectors by 200 columns (us, 16 / 4 / 1 groups): n = 4096
+// 3.9 / 6.2 / 16.2, 10048 6.6 / 8.0 / 32, 20736 14.0 / 13.1 / 34.6, 65536
+// 32.6 / 33.6 / 39.9, 200000 123 / 117 / 116.
+int gemv_groups(int64_t n) { return n <= 16384 ? 16 : 4; }
+
+// The LDS of an update: its coefficients, or the groups' sums where those are larger.
+size_t gemv_lds(int ncoef, int nsums) { return std::max((size_t)ncoef, (size_t)nsums * kThreads) * sizeof(double2); }
+
+template <int NW>
+void launch_cgemvm(const double2* V, int ncol, int64_t ld, const double2* h, int ldh, double2* W, int64_t ldw,
+                   int64_t n, hipStream_t s) {
+  const int cg = gemv_groups(n), rows = kThreads / cg;
+  const dim3 grid((unsigned)((n + rows - 1) / rows));
+  const size_t lds = gemv_lds(NW * ncol, NW);
+  if (cg == 16)
+    hipLaunchKernelGGL((cgemvm_sub_kernel<NW, 16>), grid, dim3(kThreads), lds, s, V, ncol, ld, h, ldh, W, ldw, n);
+  else
+    hipLaunchKernelGGL((cgemvm_sub_kernel<NW, 4>), grid, dim3(kThreads), lds, s, V, ncol, ld, h, ldh, W, ldw, n);
 }
 
 hipError_t cgemvm_sub(const double2* V, int ncol, int64_t ld, const double2* h, int ldh, double2* W, int64_t ldw,
                       int nw, int64_t n, hipStream_t s) {
   if (ncol == 0) return hipSuccess;
-  const dim3 grid((unsigned)((n + kThreads - 1) / kThreads));
-  const size_t lds = (size_t)nw * ncol * sizeof(double2);
-  if (lds > 65536) {  // coefficients beyond the LDS of one group: one vector at a time
-    for (int q = 0; q < nw; ++q) {
-      hipLaunchKernelGGL(cgemvm_sub_kernel<1>, grid, dim3(kThreads), (size_t)ncol * sizeof(double2), s, V, ncol,
-                         ld, h + (size_t)q * ldh, ldh, W + (size_t)q * ldw, ldw, n);
-    }
+  if ((size_t)nw * ncol * sizeof(double2) > 65536) {  // coefficients beyond the LDS of one group: one vector at a time
+    for (int q = 0; q < nw; ++q)
+      launch_cgemvm<1>(V, ncol, ld, h + (size_t)q * ldh, ldh, W + (size_t)q * ldw, ldw, n, s);
     return hipGetLastError();
   }
   switch (nw) {
     case 1:
-      hipLaunchKernelGGL(cgemvm_sub_kernel<1>, grid, dim3(kThreads), lds, s, V, ncol, ld, h, ldh, W, ldw, n);
+      launch_cgemvm<1>(V, ncol, ld, h, ldh, W, ldw, n, s);
       break;
     case 2:
-      hipLaunchKernelGGL(cgemvm_sub_kernel<2>, grid, dim3(kThreads), lds, s, V, ncol, ld, h, ldh, W, ldw, n);
+      launch_cgemvm<2>(V, ncol, ld, h, ldh, W, ldw, n, s);
       break;
     case 3:
-      hipLaunchKernelGGL(cgemvm_sub_kernel<3>, grid, dim3(kThreads), lds, s, V, ncol, ld, h, ldh, W, ldw, n);
+      launch_cgemvm<3>(V, ncol, ld, h, ldh, W, ldw, n, s);
       break;
     case 4:
-      hipLaunchKernelGGL(cgemvm_sub_kernel<4>, grid, dim3(kThreads), lds, s, V, ncol, ld, h, ldh, W, ldw, n);
+      launch_cgemvm<4>(V, ncol, ld, h, ldh, W, ldw, n, s);
       break;
     default:
       return hipErrorInvalidValue;
@@ -2598,24 +2796,37 @@ hipError_t cgemvm_sub(const double2* V, int ncol, int64_t ld, const double2* h, 
   return hipGetLastError();
 }
 
+template <bool WithZ>
+void launch_cgemv(const double2* V0, int n0, const double2* V1, int n1, const double2* P0, const double2* P1,
+                  int64_t ld, const double2* h, int real_h, double2* w, double2* z, int64_t n, hipStream_t s) {
+  const int cg = gemv_groups(n), rows = kThreads / cg;
+  const dim3 grid((unsigned)((n + rows - 1) / rows));
+  const size_t lds = gemv_lds(n0 + n1, WithZ ? 2 : 1);
+  if (cg == 16)
+    hipLaunchKernelGGL((cgemv_sub_kernel<WithZ, 16>), grid, dim3(kThreads), lds, s, V0, n0, V1, n1, P0, P1, ld, h,
+                       real_h, w, z, n);
+  else
+    hipLaunchKernelGGL((cgemv_sub_kernel<WithZ, 4>), grid, dim3(kThreads), lds, s, V0, n0, V1, n1, P0, P1, ld, h,
+                       real_h, w, z, n);
+}
+
 hipError_t cgemv_sub(const double2* V0, int n0, const double2* V1, int n1, const double2* P0,
                      const double2* P1, int64_t ld, const double2* h, int real_h, double2* w,
                      double2* z, int64_t n, hipStream_t s) {
-  const int ncol = n0 + n1;
-  if (ncol == 0) return hipSuccess;
-  const dim3 grid((unsigned)((n + kThreads - 1) / kThreads));
-  const size_t lds = (size_t)ncol * sizeof(double2);
+  if (n0 + n1 == 0) return hipSuccess;
   if (z)
-    hipLaunchKernelGGL(cgemv_sub_kernel<true>, grid, dim3(kThreads), lds, s, V0, n0, V1, n1, P0, P1, ld, h, real_h,
-                       w, z, n);
+    launch_cgemv<true>(V0, n0, V1, n1, P0, P1, ld, h, real_h, w, z, n, s);
   else
-    hipLaunchKernelGGL(cgemv_sub_kernel<false>, grid, dim3(kThreads), lds, s, V0, n0, V1, n1, P0, P1, ld, h,
-                       real_h, w, z, n);
+    launch_cgemv<false>(V0, n0, V1, n1, P0, P1, ld, h, real_h, w, z, n, s);
   return hipGetLastError();
 }
 
 hipError_t normalize(double2* w, double2* z, int64_t n, const double2* h1, const double2* h2, int jh,
                      double* alpha, double* beta, int j, int* flag, double* part, hipStream_t s) {
+  if (n <= kNormRows) {
+    hipLaunchKernelGGL(normalize_short_kernel, dim3(1), dim3(1024), 0, s, w, z, n, h1, h2, jh, alpha, beta, j, flag);
+    return hipGetLastError();
+  }
   const int64_t nch = nchunks(n);
   hipLaunchKernelGGL(rdot_part_kernel, dim3((unsigned)nch), dim3(kThreads), 0, s, w, z ? z : w, n,
                      part);
