@@ -113,12 +113,17 @@ bse_status fail(bse_handle h, bse_status s, const std::string& msg) {
 // Complex Hermitian eigenproblem of order m (column-major a, overwritten;
 // ascending w, orthonormal vectors z), the projected problems of the
 // restarts and of the refinement.  On the device with rocSOLVER's divide and
-// conquer when it can be set up: at order 560 it takes 16 ms against 53 ms
-// for the host QR of bse_smalleig.cpp; atomics are off in its rocBLAS calls,
-// so repeated solves stay bitwise identical.  The buffers grow with the
+// conquer above order kHostEig when it can be set up: at order 560 it takes
+// 16 ms against 53 ms for the host QR of bse_smalleig.cpp, while at small
+// orders its many launches dominate (ms, device / host with 16 / 4 / 1 threads,
+// copies included: order 48 1.1 / 0.31 / 0.35 / 0.29, 64 1.5 / 0.49 / 0.63 /
+// 0.64, 96 2.1 / 0.96 / 1.4 / 2.0, 128 3.2 / 1.8 / 2.6 / 4.5, 192 5.0 / 4.5 /
+// 7.9 / 14); atomics are off in its rocBLAS calls, so repeated solves stay
+// bitwise identical.  The buffers grow with the
 // largest order seen and stay with the handle.  Where rocBLAS cannot create
 // a handle (no device), or the call reports an error or no convergence, the
 // host QR solves the same problem.  Returns false only if that fails too.
+constexpr int kHostEig = 128;
 bool herm_eig_proj(bse_handle h, int m, double2* a, double* w, double2* z) {
   auto device = [&]() -> bool {
     if (h->eig_state == 0) {
@@ -173,7 +178,7 @@ bool herm_eig_proj(bse_handle h, int m, double2* a, double* w, double2* z) {
     return info == 0;
   };
   if (m < 1) return true;
-  if (device()) return true;
+  if (m > kHostEig && device()) return true;
   return bse::herm_eig(m, a, w, z);
 }
 
