@@ -2063,21 +2063,22 @@ __global__ void __launch_bounds__(kThreads)
 __global__ void __launch_bounds__(kThreads)
     colnorm_part_kernel(const double2* __restrict__ V, int ncol, int64_t ld, int64_t n,
                         double* __restrict__ part) {
+  // grid (chunks, ceil(ncol / 4)): one column per wave
   const int64_t r0 = (int64_t)blockIdx.x * kChunk;
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  for (int c = wave; c < ncol; c += 4) {
-    double s = 0.0;
+  const int c = blockIdx.y * 4 + wave;
+  if (c >= ncol) return;
+  double s = 0.0;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const int64_t i = r0 + lane + 64 * q;
-      if (i < n) {
-        const double2 v = V[(size_t)c * ld + i];
-        s += v.x * v.x + v.y * v.y;
-      }
+  for (int q = 0; q < 4; ++q) {
+    const int64_t i = r0 + lane + 64 * q;
+    if (i < n) {
+      const double2 v = V[(size_t)c * ld + i];
+      s += v.x * v.x + v.y * v.y;
     }
-    s = wave_sum(s);
-    if (lane == 0) part[(size_t)blockIdx.x * ncol + c] = s;
   }
+  s = wave_sum(s);
+  if (lane == 0) part[(size_t)blockIdx.x * ncol + c] = s;
 }
 
 __global__ void __launch_bounds__(kThreads)
@@ -2341,24 +2342,44 @@ __global__ void __launch_bounds__(64) pair_sum_kernel(const double* __restrict__
 //   G_A(i, j) = sum_c w_c (X_ic conj(X_jc) + conj(Y_ic) Y_jc),
 //   G_B(i, j) = sum_c w_c (X_ic conj(Y_jc) + conj(Y_ic) X_jc),
 // written packed (offset i + j (j + 1) / 2) with off-diagonal entries doubled
-// and the diagonal of G_A real.  The k columns pass through LDS in chunks of
-// 8 (the row side pre-multiplied by the weights); thread t owns rows
-// I 64 + (t & 15) + 16 r and columns J 64 + (t >> 4) + 16 q, r, q < 4, so a
-// store of one (r, q) covers 16 consecutive rows of 4 columns per wavefront.
-// MODE 0 writes G_A (ga) and G_B (gb); MODE 1 / 2 instead accumulate, over the
-// tile's entries, Re(conj(g_ij) C_ij) for the packed gradient entry g of G_A /
-// G_B (doubled off the diagonal) and a packed component C of that block, and
-// store the tile's sum in part[tile] (the other block's sums are not formed).
-constexpr int kGT = 64, kGK = 8;
+// and the diagonal of G_A real.  MODE 0 writes G_A (ga) and G_B (gb); MODE 1 /
+// 2 instead accumulate, over the tile's entries, Re(conj(g_ij) C_ij) for the
+// packed gradient entry g of G_A / G_B (doubled off the diagonal) and a packed
+// component C of that block, and store the tile's sum in part[tile] (the other
+// block's sums are not formed).
+//
+// A rank-k contraction on FP64 matrix cores (16x16x4).  With the four real
+// components r = (Re x, Im x, Re y, Im y) of a pair as the k dimension of one
+// instruction, r' = (Im x, -Re x, Re y, -Im y) on the row side and permutations
+// of r on the column side,
+//   Re G_A = r_i . r_j                       Im G_A = r'_i . (xr, xi, yi, yr)_j
+//   Re G_B = r_i . (yr, yi, xr, xi)_j        Im G_B = r'_i . (yr, yi, xi, xr)_j,
+// so a pair costs four instructions per 16 x 16 tile and no products beyond
+// the 16 real ones of the definition.  TDA (no Y): two pairs per instruction,
+// r = (Re x, Im x) of both, Re G_A = r_i . r_j, Im G_A = r'_i . r_j.  The
+// column index j is the instruction's row, so a lane group holds 16
+// consecutive rows i of a column and stores 256-byte segments.  Pairs pass
+// through LDS in chunks of 8 (16 without Y), the next chunk's loads in flight
+// under the current one's products; component rows are 80 doubles apart so
+// that the 16 lanes of each component read distinct banks.
+//
+// Bound by the matrix cores: N = 5000, k = 64, PH (26 GFLOP, 355 us at the
+// 72 TFLOP/s of a large FP64 product) 667 us with FMAs on 4 x 4 outputs per
+// thread, 510 us here (TDA 396 -> 143 us);
+// N = 16384, k = 16: 2033 -> 1901 us, of which the 4.3 GB written take about 870.
+constexpr int kGT = 64;
 
-template <int MODE>
-__global__ void __launch_bounds__(kThreads)
+template <int MODE, bool PH>
+__global__ void __launch_bounds__(kThreads, 2)
     grad_tile_kernel(const double2* __restrict__ X, const double2* __restrict__ Y, int64_t ld,
                      const double* __restrict__ wgt, int k, int64_t n, double2* __restrict__ ga,
                      double2* __restrict__ gb, const double2* __restrict__ C, double* __restrict__ part) {
-  __shared__ double2 sxi[kGK][kGT], sxj[kGK][kGT], syi[kGK][kGT], syj[kGK][kGT];
+  constexpr int NK = 8;              // instruction k-steps per chunk
+  constexpr int KP = PH ? NK : 2 * NK;  // pairs per chunk
+  constexpr int LDC = 80;
+  constexpr bool wantA = MODE != 2, wantB = MODE != 1 && PH;
+  __shared__ double si[NK][4][LDC], sj[NK][4][LDC];
   __shared__ double sred[4];
-  constexpr bool wantA = MODE != 2, wantB = MODE != 1;
   // tile (I, J) from the linear index over the upper triangle of tiles, column by column
   const int64_t b = blockIdx.x;
   int64_t J = (int64_t)((sqrt(8.0 * (double)b + 1.0) - 1.0) * 0.5);
@@ -2366,96 +2387,124 @@ __global__ void __launch_bounds__(kThreads)
   while ((J + 1) * (J + 2) / 2 <= b) ++J;
   const int64_t I = b - J * (J + 1) / 2;
   const int64_t i0 = I * kGT, j0 = J * kGT;
-  const int t = threadIdx.x, tr = t & 15, tc = t >> 4;
-  const bool ph = Y != nullptr;
-  double ar[4][4], ai[4][4], br[4][4], bi[4][4];
+  const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
+  const int li = lane & 15, lk = lane >> 4;
+  const int wi = (wave & 1) * 32, wj = (wave >> 1) * 32;  // this wave's 32 x 32 quarter
+
+  // staging: thread t holds row t & 63, k-steps (t >> 6) + 4 e (e < 2), of each side
+  const int row = t & 63, kq = t >> 6;
+  const bool in_i = i0 + row < n, in_j = j0 + row < n;
+  double2 pi[2][2], pj[2][2];  // [e][x, y] (TDA: [e][first, second pair])
+  auto fetch = [&](int c0) {
 #pragma unroll
-  for (int r = 0; r < 4; ++r)
+    for (int e = 0; e < 2; ++e)
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      ar[r][q] = 0.0;
-      ai[r][q] = 0.0;
-      br[r][q] = 0.0;
-      bi[r][q] = 0.0;
-    }
-  for (int c0 = 0; c0 < k; c0 += kGK) {
-    // stage the chunk: 8 x 64 entries of each of X_I, X_J (and Y_I, Y_J); two per thread each
-    for (int e = t; e < kGK * kGT; e += kThreads) {
-      const int kk = e / kGT, rr = e % kGT;
-      const int c = c0 + kk;
-      const int64_t ii = i0 + rr, jj = j0 + rr;
-      const bool cin = c < k;
-      const double w = cin ? wgt[c] : 0.0;
-      double2 xi = make_double2(0.0, 0.0), xj = xi, yi = xi, yj = xi;
-      if (cin && ii < n) {
-        xi = X[(size_t)c * ld + ii];
-        if (ph) yi = Y[(size_t)c * ld + ii];
-      }
-      if (cin && jj < n) {
-        xj = X[(size_t)c * ld + jj];
-        if (ph) yj = Y[(size_t)c * ld + jj];
-      }
-      sxi[kk][rr] = make_double2(w * xi.x, w * xi.y);
-      syi[kk][rr] = make_double2(w * yi.x, w * yi.y);
-      sxj[kk][rr] = xj;
-      syj[kk][rr] = yj;
-    }
-    __syncthreads();
-    for (int kk = 0; kk < kGK; ++kk) {
-      double2 xi[4], xj[4], yi[4], yj[4];
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        xi[r] = sxi[kk][tr + 16 * r];
-        yi[r] = syi[kk][tr + 16 * r];
-        xj[r] = sxj[kk][tc + 16 * r];
-        yj[r] = syj[kk][tc + 16 * r];
-      }
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          if (wantA) {
-            // X_i conj(X_j) + conj(Y_i) Y_j
-            ar[r][q] += xi[r].x * xj[q].x + xi[r].y * xj[q].y + yi[r].x * yj[q].x + yi[r].y * yj[q].y;
-            ai[r][q] += xi[r].y * xj[q].x - xi[r].x * xj[q].y + yi[r].x * yj[q].y - yi[r].y * yj[q].x;
+      for (int h = 0; h < 2; ++h) {
+        const int c = PH ? c0 + kq + 4 * e : c0 + 2 * (kq + 4 * e) + h;
+        const double2* src = PH && h ? Y : X;
+        double2 vi = make_double2(0.0, 0.0), vj = vi;
+        if (c < k) {
+          if (in_i) {
+            const double w = wgt[c];
+            vi = src[(size_t)c * ld + i0 + row];
+            vi = make_double2(w * vi.x, w * vi.y);
           }
-          if (wantB && ph) {
-            // X_i conj(Y_j) + conj(Y_i) X_j
-            br[r][q] += xi[r].x * yj[q].x + xi[r].y * yj[q].y + yi[r].x * xj[q].x + yi[r].y * xj[q].y;
-            bi[r][q] += xi[r].y * yj[q].x - xi[r].x * yj[q].y + yi[r].x * xj[q].y - yi[r].y * xj[q].x;
+          if (in_j) vj = src[(size_t)c * ld + j0 + row];
+        }
+        pi[e][h] = vi;
+        pj[e][h] = vj;
+      }
+  };
+  dbl4 acc[4][2][2];  // Re G_A, Im G_A, Re G_B, Im G_B
+#pragma unroll
+  for (int o = 0; o < 4; ++o)
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int c = 0; c < 2; ++c) acc[o][a][c] = dbl4{0.0, 0.0, 0.0, 0.0};
+  // component of the lane for r' (sign on odd components) and the column permutations
+  const int pr = PH ? (lk < 2 ? lk ^ 1 : lk) : lk ^ 1;
+  const double sgn = (lk & 1) ? -1.0 : 1.0;
+  const int p1 = PH ? (lk < 2 ? lk : lk ^ 1) : lk;  // (xr, xi, yi, yr)
+  const int p2 = lk ^ 2;                            // (yr, yi, xr, xi)
+  const int p3 = lk < 2 ? lk + 2 : 3 - lk;          // (yr, yi, xi, xr)
+
+  fetch(0);
+  for (int c0 = 0; c0 < k; c0 += KP) {
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        si[kq + 4 * e][2 * h][row] = pi[e][h].x;
+        si[kq + 4 * e][2 * h + 1][row] = pi[e][h].y;
+        sj[kq + 4 * e][2 * h][row] = pj[e][h].x;
+        sj[kq + 4 * e][2 * h + 1][row] = pj[e][h].y;
+      }
+    __syncthreads();
+    if (c0 + KP < k) fetch(c0 + KP);
+#pragma unroll 2
+    for (int s = 0; s < NK; ++s) {
+      double ri[2], rp[2];
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        ri[c] = si[s][lk][wi + 16 * c + li];
+        rp[c] = sgn * si[s][pr][wi + 16 * c + li];
+      }
+#pragma unroll
+      for (int a = 0; a < 2; ++a) {
+        const int jj = wj + 16 * a + li;
+        if (wantA) {
+          const double q0 = sj[s][lk][jj], q1 = sj[s][p1][jj];
+#pragma unroll
+          for (int c = 0; c < 2; ++c) {
+            acc[0][a][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(q0, ri[c], acc[0][a][c], 0, 0, 0);
+            acc[1][a][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(q1, rp[c], acc[1][a][c], 0, 0, 0);
           }
         }
+        if (wantB) {
+          const double q2 = sj[s][p2][jj], q3 = sj[s][p3][jj];
+#pragma unroll
+          for (int c = 0; c < 2; ++c) {
+            acc[2][a][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(q2, ri[c], acc[2][a][c], 0, 0, 0);
+            acc[3][a][c] = __builtin_amdgcn_mfma_f64_16x16x4f64(q3, rp[c], acc[3][a][c], 0, 0, 0);
+          }
+        }
+      }
     }
     __syncthreads();
   }
-  double acc = 0.0;
+  // entry (row i, column j): lane i + 16 (j % 4) of the tile, register j / 4
+  double sum = 0.0;
 #pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    const int64_t j = j0 + tc + 16 * q;
-    if (j >= n) continue;
-    const int64_t off = j * (j + 1) / 2;
+  for (int a = 0; a < 2; ++a)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const int64_t i = i0 + tr + 16 * r;
-      if (i > j) continue;
-      const double f = i == j ? 1.0 : 2.0;
-      if (MODE == 0) {
-        if (ga) ga[off + i] = i == j ? make_double2(ar[r][q], 0.0) : make_double2(f * ar[r][q], f * ai[r][q]);
-        if (gb) gb[off + i] = make_double2(f * br[r][q], f * bi[r][q]);
-      } else {
-        const double2 cv = C[off + i];
-        const double gr = MODE == 1 ? ar[r][q] : br[r][q];
-        const double gi = MODE == 1 ? (i == j ? 0.0 : ai[r][q]) : bi[r][q];
-        acc += f * (gr * cv.x + gi * cv.y);
+      const int64_t j = j0 + wj + 16 * a + 4 * r + lk;
+      if (j >= n) continue;
+      const int64_t off = j * (j + 1) / 2;
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const int64_t i = i0 + wi + 16 * c + li;
+        if (i > j) continue;
+        const double f = i == j ? 1.0 : 2.0;
+        if (MODE == 0) {
+          if (ga)
+            ga[off + i] = i == j ? make_double2(acc[0][a][c][r], 0.0)
+                                 : make_double2(f * acc[0][a][c][r], f * acc[1][a][c][r]);
+          if (gb) gb[off + i] = make_double2(f * acc[2][a][c][r], f * acc[3][a][c][r]);
+        } else {
+          const double2 cv = C[off + i];
+          const double gr = MODE == 1 ? acc[0][a][c][r] : acc[2][a][c][r];
+          const double gi = MODE == 1 ? (i == j ? 0.0 : acc[1][a][c][r]) : acc[3][a][c][r];
+          sum += f * (gr * cv.x + gi * cv.y);
+        }
       }
     }
-  }
   if (MODE != 0) {
-    acc = block_sum(acc, sred);
-    if (threadIdx.x == 0) part[blockIdx.x] = acc;
+    sum = block_sum(sum, sred);
+    if (t == 0) part[blockIdx.x] = sum;
   }
 }
-
 
 // part[block] = sum_i d_i sum_c wgt_c (|X_ci|^2 + |Y_ci|^2) over the block's rows.
 __global__ void __launch_bounds__(kThreads)
@@ -2851,8 +2900,8 @@ hipError_t colnorms(const double2* V, int ncol, int64_t ld, int64_t n, double* p
                     hipStream_t s) {
   if (ncol == 0) return hipSuccess;
   const int64_t nch = nchunks(n);
-  hipLaunchKernelGGL(colnorm_part_kernel, dim3((unsigned)nch), dim3(kThreads), 0, s, V, ncol, ld, n,
-                     part);
+  hipLaunchKernelGGL(colnorm_part_kernel, dim3((unsigned)nch, (unsigned)((ncol + 3) / 4)), dim3(kThreads), 0, s, V,
+                     ncol, ld, n, part);
   hipLaunchKernelGGL(colsum_real_kernel, dim3((unsigned)((ncol + 3) / 4)), dim3(kThreads), 0, s, part, nch, ncol,
                      nrm);
   return hipGetLastError();
@@ -2983,16 +3032,24 @@ hipError_t resid_norms(const double2* out, const double2* v, int cj, double sgn_
   return hipGetLastError();
 }
 
-hipError_t quad_packed(const double2* X, const double2* Y, int64_t ld, const double* wgt, int k, int64_t n,
-                       const double2* C, int target_b, double* part, hipStream_t s) {
-  const dim3 grid((unsigned)quad_packed_parts(n));
-  if (target_b)
-    hipLaunchKernelGGL(grad_tile_kernel<2>, grid, dim3(kThreads), 0, s, X, Y, ld, wgt, k, n, nullptr, nullptr, C,
+template <int MODE>
+hipError_t launch_grad(const double2* X, const double2* Y, int64_t ld, const double* wgt, int k, int64_t n,
+                       double2* ga, double2* gb, const double2* C, double* part, hipStream_t s) {
+  const int64_t nt = (n + kGT - 1) / kGT;
+  const dim3 grid((unsigned)(nt * (nt + 1) / 2));
+  if (Y)
+    hipLaunchKernelGGL((grad_tile_kernel<MODE, true>), grid, dim3(kThreads), 0, s, X, Y, ld, wgt, k, n, ga, gb, C,
                        part);
   else
-    hipLaunchKernelGGL(grad_tile_kernel<1>, grid, dim3(kThreads), 0, s, X, Y, ld, wgt, k, n, nullptr, nullptr, C,
+    hipLaunchKernelGGL((grad_tile_kernel<MODE, false>), grid, dim3(kThreads), 0, s, X, Y, ld, wgt, k, n, ga, gb, C,
                        part);
   return hipGetLastError();
+}
+
+hipError_t quad_packed(const double2* X, const double2* Y, int64_t ld, const double* wgt, int k, int64_t n,
+                       const double2* C, int target_b, double* part, hipStream_t s) {
+  return target_b ? launch_grad<2>(X, Y, ld, wgt, k, n, nullptr, nullptr, C, part, s)
+                  : launch_grad<1>(X, Y, ld, wgt, k, n, nullptr, nullptr, C, part, s);
 }
 
 hipError_t quad_diag(const double2* X, const double2* Y, int64_t ld, const double* wgt, int k,
@@ -3004,10 +3061,7 @@ hipError_t quad_diag(const double2* X, const double2* Y, int64_t ld, const doubl
 
 hipError_t grad_packed(const double2* X, const double2* Y, int64_t ld, const double* wgt, int k,
                        int64_t n, double2* ga, double2* gb, hipStream_t s) {
-  const int64_t nt = (n + kGT - 1) / kGT;
-  hipLaunchKernelGGL(grad_tile_kernel<0>, dim3((unsigned)(nt * (nt + 1) / 2)), dim3(kThreads), 0, s, X, Y, ld, wgt,
-                     k, n, ga, gb, nullptr, nullptr);
-  return hipGetLastError();
+  return launch_grad<0>(X, Y, ld, wgt, k, n, ga, gb, nullptr, nullptr, s);
 }
 
 int64_t quad_packed_parts(int64_t n) {

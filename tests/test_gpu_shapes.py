@@ -69,3 +69,46 @@ def test_orthogonalization_lengths(n, variant, block):
     nrm = torch.sqrt((x.abs() ** 2).sum(0) + (y.abs() ** 2).sum(0))
     assert float((res / (om * nrm)).max()) <= 1.01 * tol
     assert float(((x.abs() ** 2).sum(0) - (y.abs() ** 2).sum(0) - 1.0).abs().max()) < 1e-12
+
+
+def _packed_gradients(x, y, g):
+    """dL/dA, dL/dB of L = sum g omega from the definition (LAPACK-'U', off-diagonal doubled)."""
+    n = x.shape[1]
+    j, i = np.tril_indices(n)  # packed order: column j, rows i <= j
+    f = np.where(i == j, 1.0, 2.0)
+    w = g if y is None else g / (np.sum(np.abs(x) ** 2, 1) - np.sum(np.abs(y) ** 2, 1))
+    ga = (x.T * w) @ x.conj()
+    if y is None:
+        return f * ga[i, j], None
+    ga = ga + (y.conj().T * w) @ y
+    gb = (x.T * w) @ y.conj() + (y.conj().T * w) @ x
+    return f * ga[i, j], f * gb[i, j]
+
+
+# one tile, its edge and remainder, several tiles; pairs below, at and past the chunks of 8 (16 for TDA)
+@pytest.mark.parametrize("n,k", [(7, 1), (63, 3), (64, 7), (65, 8), (130, 9), (200, 16), (129, 17), (257, 33)])
+@pytest.mark.parametrize("kind", ["tda", "ph"])
+def test_gradient_tiles(kind, n, k):
+    """The packed gradients and the packed-component scalars of the handle's own pairs against the
+    definition in FP64: sums of 4 k products per entry, so 1e-14 of the largest entry allows for
+    about 10 roundings of it (k <= 33)."""
+    print(f"gradient tiles {kind} n={n} k={k}", flush=True)
+    rng = np.random.default_rng(2000 + n)
+    A, B = random_herm(rng, n, lam_min=1.0), random_sym(rng, n, 0.5)
+    ap, bp = pack_upper(A), pack_upper(B) if kind == "ph" else None
+    s = make_solver(kind, ap, bp)
+    _, x, y, _ = s.solve(k, 1e-8)
+    g = rng.standard_normal(k)
+    da, db = s.backward(dev(g))
+    ra, rb = _packed_gradients(host(x), None if y is None else host(y), g)
+    assert np.max(np.abs(host(da) - ra)) <= 1e-14 * np.max(np.abs(ra))
+    if kind == "ph":
+        assert np.max(np.abs(host(db) - rb)) <= 1e-14 * np.max(np.abs(ra))
+    c = rng.standard_normal(len(ap)) + 1j * rng.standard_normal(len(ap))
+    comps = [("A", "packed", dev(c), 1.0)] + ([("B", "packed", dev(c), -0.5)] if kind == "ph" else [])
+    got = s.strength(dev(g), comps)
+    # Re sum conj(g_ij) C_ij; a diagonal entry of G_A is real
+    for v, ref, sc in zip(got, [ra, rb], [1.0, -0.5]):
+        terms = np.real(np.conj(ref) * c)
+        assert abs(v - sc * np.sum(terms)) <= 1e-14 * np.sum(np.abs(ref) * np.abs(c))
+    s.close()
