@@ -569,6 +569,15 @@ __device__ __forceinline__ double dpp_swap_add(double a, double b) {
   const int yh = __builtin_amdgcn_update_dpp(__double2hiint(b), __double2hiint(a), CTRL, 0xf, BA, false);
   return __hiloint2double(xh, xl) + __hiloint2double(yh, yl);
 }
+// The same between banks 0 and 1 and banks 2 and 3: even banks get a of the
+// pair, odd banks b.
+__device__ __forceinline__ double bank_pair_add(double a, double b) {
+  const int xl = __builtin_amdgcn_update_dpp(__double2loint(a), __double2loint(b), 0x124, 0xf, 0xa, false);
+  const int xh = __builtin_amdgcn_update_dpp(__double2hiint(a), __double2hiint(b), 0x124, 0xf, 0xa, false);
+  const int yl = __builtin_amdgcn_update_dpp(__double2loint(b), __double2loint(a), 0x12c, 0xf, 0x5, false);
+  const int yh = __builtin_amdgcn_update_dpp(__double2hiint(b), __double2hiint(a), 0x12c, 0xf, 0x5, false);
+  return __hiloint2double(xh, xl) + __hiloint2double(yh, yl);
+}
 // Sums of N = 4, 8 or 16 values over the wavefront: every lane returns the sum
 // of value wave_sum_index<N>(lane).
 template <int N>
@@ -1025,10 +1034,10 @@ __global__ void __launch_bounds__(kThreads)
 }
 
 // The sum / difference inputs of mh_stream_kernel: UW[2q][i] = x_q[i] + conj(y_q[i]),
-// UW[2q + 1][i] = x_q[i] - conj(y_q[i]) for i < pl (zero past n), column q of V
-// being [x_q (ldh); y_q].  Grid (ceil(pl / 256), nh).
+// UW[2q + 1][i] = x_q[i] - conj(y_q[i]) (rot: times -i) for i < pl (zero past n),
+// column q of V being [x_q (ldh); y_q].  Grid (ceil(pl / 256), nh).
 __global__ void __launch_bounds__(kThreads)
-    hsd_stage_kernel(const double2* __restrict__ V, int64_t ldv, int64_t ldh, int64_t n, int64_t pl,
+    hsd_stage_kernel(const double2* __restrict__ V, int64_t ldv, int64_t ldh, int64_t n, int64_t pl, int rot,
                      double2* __restrict__ UW) {
   const int64_t i = (int64_t)blockIdx.x * kThreads + threadIdx.x;
   const int q = blockIdx.y;
@@ -1040,7 +1049,7 @@ __global__ void __launch_bounds__(kThreads)
     w = make_double2(x.x - y.x, x.y + y.y);
   }
   UW[(size_t)(2 * q) * pl + i] = u;
-  UW[(size_t)(2 * q + 1) * pl + i] = w;
+  UW[(size_t)(2 * q + 1) * pl + i] = rot ? make_double2(w.y, -w.x) : w;
 }
 
 // rows per workgroup slice of the streaming full-H kernel: 256 rows spread
@@ -1271,6 +1280,309 @@ __global__ void __launch_bounds__(kThreads)
   }
 }
 
+// Multi-vector passes on FP64 matrix cores (R >= 128): NV <= 4 NG half-vectors
+// (MODE as in tile64_kernel: T64_A, T64_K, or T64_H with u and -i w = -i (x -
+// conj(y)) of NV / 2 full-H vectors, both through K1).
+//
+// What bounds it: with FMAs the four-vector full-H read on hi was bound by
+// their issue at two waves per SIMD (2.75 ms at N = 32768, where its 8.6 GB take
+// 1.4 ms at the rate of a plain read).  v_mfma_f64_4x4x4 sustains 73 TFLOP/s
+// against 58 for a pure FMA loop in a quarter of the instructions; its four
+// independent 4 x 4 blocks take four vectors on the right, so eight
+// half-vectors are two instructions with nothing padded (the 16 x 16 form would
+// run half empty).  1.85 ms here, of which the products alone take 0.95 (matrix
+// instructions and FP64 vector instructions share one unit: together they ran
+// at 72 TFLOP/s, so conversions and sums are worth removing).
+//
+// Row products: lane l holds entry (row pair l & 15, column l >> 4) of a 16 VW x 4
+// subtile, which is the A operand A[i = l & 3][k = l >> 4] of block
+// (l >> 2) & 3 with the column as k; the four real coefficients kp, kt, ks, kq
+// of the entry pair are four such operands.  Column products contract over
+// rows: the same coefficients with lane bits 0-1 and 4-5 exchanged, through
+// LDS within the wave (columns 320 bytes apart: the 16 lanes of a read phase on
+// distinct banks); exchanging the entries instead and forming the coefficients
+// twice took 2.00 ms.  64 entry pairs cost 8 NG matrix instructions and eight
+// conversions and sums.
+//
+// A workgroup takes one R x R block; each wave owns an equal share of its rows for
+// all columns, so the row sums stay in its registers to the end; the column
+// sums of a step (four columns) are added over the lanes' row blocks and meet
+// the other waves' in LDS every 32 columns (fixed order: deterministic).  The
+// loads of the next four columns are issued before the current ones are used.
+constexpr int kMfmaChunk = 32;  // columns between two combinations of the waves' column sums
+
+__device__ __forceinline__ double mfma4(double a, double b, double c) {
+  return __builtin_amdgcn_mfma_f64_4x4x4f64(a, b, c, 0, 0, 0);
+}
+
+// Which products take the matrix cores, from reads with their sums (us, FMA
+// kernel / matrix cores; hi unless marked):
+//   H of 4 vectors, R = 128: 308 / 225, 256: 764 / 494, 512: 2748 / 1846; hi + lo
+//   R = 256: 966 / 869, complex128 1142 / 840, but R = 128 363 / 377 and 362 /
+//   365; of 3: R = 128 219 / 218, 256 568 / 475, 512 2181 / 1798; of 2: R = 128
+//   179 / 188, 256 459 / 442, hi + lo 789 / 828 (bound by the read).
+//   A x four: R = 128 133 / 114, 256 332 / 245, 512 1233 / 921, hi + lo R = 256
+//   456 / 437, R = 128 177 / 192, complex128 446 / 424 and 185 / 177; K1 x
+//   four: R = 128 178 / 184, 256 466 / 432, 512 1748 / 1632, hi + lo 858 / 810
+//   and 322 / 339, complex128 938 / 786 and 341 / 321; three vectors within 5 %
+//   either way (K1: R = 128 167 / 175, 256 441 / 421, 512 1570 / 1587, no gain in
+//   a Haydock run at N = 12001).
+constexpr bool mh_on_mfma(int R, int AR, int nh) { return AR != AR_HI && nh >= 3 && (R >= 256 || AR == AR_HI64); }
+constexpr bool mk_on_mfma(int R, int AR, int BM, int nv) {
+  if (AR == AR_HI || R < 128 || nv < 4) return false;
+  if (R == 128) return AR == AR_C128 || (AR == AR_HI64 && BM == BM_NONE);
+  return true;
+}
+
+// waves of a workgroup: the row state of 64 rows and eight half-vectors fits
+// two waves per SIMD, that of 128 rows (block edge 512 on four waves) spilled
+constexpr int mfma_waves(int R) { return R == 512 ? 8 : 4; }
+
+template <int R, int AR, int MODE, int NG>
+__global__ void __launch_bounds__(64 * mfma_waves(R), 2)
+    mfma_pass_kernel(const void* __restrict__ a0, const void* __restrict__ a1, const void* __restrict__ b0,
+                     const void* __restrict__ b1, const int2* __restrict__ blkmap, int64_t nblk, int64_t n,
+                     const double2* __restrict__ V, int64_t ldv, int nv, double sb,
+                     double2* __restrict__ rowpart, double2* __restrict__ colpart) {
+  constexpr int VW = AR == AR_C128 ? 1 : 2;  // rows per lane load
+  constexpr int WAVES = mfma_waves(R);
+  constexpr int RT = R / WAVES;              // rows of a wave
+  constexpr int SUB = RT / (16 * VW);        // 16 VW x 4 subtiles of a step
+  constexpr bool HASB = MODE != T64_A;
+  constexpr int NM = HASB ? 2 : 1;  // double2 of coefficients per entry pair
+  constexpr int STEPS = R / 4, SPC = kMfmaChunk / 4;
+  constexpr int TLD = 20;  // double2 per transposed column (16 and padding)
+  __shared__ double2 trn[WAVES][2][NM][4 * TLD];                   // [wave][buffer][matrix]
+  __shared__ double2 csum[2][WAVES][4 * NG][kMfmaChunk + 4];       // [buffer][wave][output][column]
+
+  const int blk = blockIdx.x;
+  const int2 pq = blkmap[blk];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  const int l0 = lane & 3, lb = (lane >> 2) & 3, l2 = lane >> 4;
+  const int64_t row0 = (int64_t)pq.x * R + wave * RT, col0 = (int64_t)pq.y * R;
+  // half-vector q at index i; past the ends the last one (the stored entries
+  // there are zero, the outputs not written)
+  auto input = [&](int q, int64_t i) -> double2 {
+    return V[(size_t)(q < nv ? q : nv - 1) * ldv + (i < n ? i : n - 1)];
+  };
+
+  // row-side operands B[k = l2][j = l0] of block lb: row pair lb + 4 l2
+  double xr[SUB][VW][NG], xi[SUB][VW][NG], dr[SUB][VW][NG], di[SUB][VW][NG];
+#pragma unroll
+  for (int s = 0; s < SUB; ++s)
+#pragma unroll
+    for (int e = 0; e < VW; ++e)
+#pragma unroll
+      for (int g = 0; g < NG; ++g) {
+        const double2 x = input(4 * g + l0, row0 + s * 16 * VW + (lb + 4 * l2) * VW + e);
+        xr[s][e][g] = x.x;
+        xi[s][e][g] = x.y;
+        dr[s][e][g] = 0.0;
+        di[s][e][g] = 0.0;
+      }
+
+  const size_t lbase = (size_t)blk * R * R + (size_t)l2 * R + wave * RT + (lane & 15) * VW;
+  // the loads run AHEAD steps ahead of their use, in slots that the unrolled
+  // loop renames (hi: the next step's first exchange needs its entries a step
+  // early, 2111 -> 2004 us at N = 32768; the wider entries have no registers
+  // for it and lose 4 %)
+  constexpr int AHEAD = AR == AR_HI64 ? 2 : 1;
+  RawCol<AR> ra[4][SUB], rb[4][HASB ? SUB : 1];
+  double2 xc[4][NG];
+  auto fetch = [&](int st, auto slot) {
+    constexpr int S = decltype(slot)::value;
+#pragma unroll
+    for (int s = 0; s < SUB; ++s) {
+      raw_load<AR>(a0, a1, lbase + (size_t)st * 4 * R + s * 16 * VW, ra[S][s]);
+      if constexpr (HASB) raw_load<AR>(b0, b1, lbase + (size_t)st * 4 * R + s * 16 * VW, rb[S][s]);
+    }
+#pragma unroll
+    for (int g = 0; g < NG; ++g) xc[S][g] = input(4 * g + l0, col0 + st * 4 + l2);
+  };
+  double2* const tw = &trn[wave][0][0][0];
+  const int wr = (lane >> 4) * TLD + (lane & 15);  // this lane's place as written
+  const int rd = l0 * TLD + lb + 4 * l2;           // and as read: column l0, row pair lb + 4 l2
+
+  // the real 2 x 2 block of an entry pair
+  struct Coef {
+    double kp, kt, ks, kq;
+  };
+  auto coef = [&](double ar, double ai, double br, double bi) {
+    Coef c;
+    if constexpr (MODE == T64_A) {
+      c.kp = c.kq = ar;
+      c.ks = ai;
+      c.kt = -ai;
+    } else {
+      if constexpr (MODE == T64_K) {  // sb = 1 or -1
+        br *= sb;
+        bi *= sb;
+      }
+      c.kp = ar + br;
+      c.kq = ar - br;
+      c.ks = ai + bi;
+      c.kt = bi - ai;
+    }
+    return c;
+  };
+
+  // unit u of a step: rows e = u % VW of subtile u / VW, 64 entry pairs; its
+  // coefficients (rc) go through LDS into the transposed lanes (tc)
+  constexpr int UN = SUB * VW;
+  Coef rc[2], tc[2];
+  auto exchange = [&](auto slot, auto unit, auto bufc) {
+    constexpr int S = decltype(slot)::value, u = decltype(unit)::value, X = decltype(bufc)::value;
+    double ar, ai, br = 0.0, bi = 0.0;
+    raw_get<AR, double>(ra[S][u / VW], u % VW, ar, ai);
+    if constexpr (HASB) raw_get<AR, double>(rb[S][u / VW], u % VW, br, bi);
+    const Coef c = coef(ar, ai, br, bi);
+    rc[X] = c;
+    double2* w = tw + X * NM * 4 * TLD;
+    w[wr] = make_double2(c.kp, c.ks);
+    if constexpr (HASB) w[4 * TLD + wr] = make_double2(c.kt, c.kq);
+    wave_lds_sync();
+    const double2 t = w[rd];
+    tc[X].kp = t.x;
+    tc[X].ks = t.y;
+    if constexpr (HASB) {
+      const double2 t2 = w[4 * TLD + rd];
+      tc[X].kt = t2.x;
+      tc[X].kq = t2.y;
+    } else {
+      tc[X].kt = -t.y;
+      tc[X].kq = t.x;
+    }
+    wave_lds_sync();
+  };
+  // column sums of a step over the row blocks lb (lane bits 2-3, the banks of a
+  // DPP row): the 2 NG values of a lane are exchanged so that each bank ends up
+  // with the sum of one of them (NG = 1: each of two, twice)
+  double cr[NG], ci[NG];
+  double* const cdst = reinterpret_cast<double*>(&csum[0][wave][NG == 2 ? (lb & 2) * 2 + l0 : l0][l2]) +
+                       (NG == 2 ? lb & 1 : lb >> 1);
+  auto col_out = [&](int st, const double (&pr)[NG], const double (&pi)[NG]) {
+    double v;
+    if constexpr (NG == 2) {
+      const double p = dpp_swap_add<0x128, 0x3>(pr[0], pr[1]);  // row_ror:8; banks 0, 1: group 0
+      const double q = dpp_swap_add<0x128, 0x3>(pi[0], pi[1]);
+      v = bank_pair_add(p, q);  // banks 0, 2: real part, 1, 3: imaginary part
+    } else {
+      const double p = dpp_swap_add<0x128, 0x3>(pr[0], pi[0]);  // banks 0, 1: real part, 2, 3: imaginary part
+      v = bank_pair_add(p, p);
+    }
+    constexpr int BUFD = WAVES * 4 * NG * (kMfmaChunk + 4) * 2;  // doubles of one buffer of csum
+    cdst[((st / SPC) & 1) * BUFD + (st % SPC) * 8] = v;
+  };
+  // the waves' column sums of a chunk
+  auto chunk_out = [&](int ch) {
+    __syncthreads();  // the other buffer of csum is free once every wave is here again
+    for (int v = threadIdx.x; v < 4 * NG * kMfmaChunk; v += 64 * WAVES) {
+      const int q = v / kMfmaChunk, c = v % kMfmaChunk;
+      double2 t = csum[ch & 1][0][q][c];
+#pragma unroll
+      for (int w = 1; w < WAVES; ++w) {
+        t.x += csum[ch & 1][w][q][c].x;
+        t.y += csum[ch & 1][w][q][c].y;
+      }
+      if (MODE == T64_H && (q & 1)) t = make_double2(-t.y, t.x);  // K2 w = i K1 (-i w)
+      if (q < nv) colpart[((size_t)q * nblk + blk) * R + ch * kMfmaChunk + c] = t;
+    }
+  };
+
+  // One step: the exchanges run one unit ahead of the products (the next
+  // step's first unit included), the previous step's column sums are finished
+  // under this step's products.
+  auto step = [&](int st, auto slot) {
+    constexpr int S = decltype(slot)::value;
+    fetch(st + AHEAD < STEPS ? st + AHEAD : STEPS - 1, std::integral_constant<int, (S + AHEAD) % 4>());
+    __builtin_amdgcn_sched_barrier(0);  // the loads stay ahead of their use
+    double pr[NG], pi[NG];
+#pragma unroll
+    for (int g = 0; g < NG; ++g) {
+      pr[g] = cr[g];
+      pi[g] = ci[g];
+      cr[g] = ci[g] = 0.0;
+    }
+    auto unit = [&](auto uc) {
+      constexpr int u = decltype(uc)::value;
+      constexpr int X = (S * UN + u) & 1;
+      if constexpr (u + 1 < UN)
+        exchange(slot, std::integral_constant<int, u + 1>(), std::integral_constant<int, 1 - X>());
+      else
+        exchange(std::integral_constant<int, (S + 1) % 4>(), std::integral_constant<int, 0>(),
+                 std::integral_constant<int, 1 - X>());
+      constexpr int s = u / VW, e = u % VW;
+      const Coef &c = rc[X], &t = tc[X];
+#pragma unroll
+      for (int g = 0; g < NG; ++g) {
+        dr[s][e][g] = mfma4(c.kp, xc[S][g].x, dr[s][e][g]);
+        di[s][e][g] = mfma4(c.ks, xc[S][g].x, di[s][e][g]);
+        cr[g] = mfma4(t.kp, xr[s][e][g], cr[g]);
+        ci[g] = mfma4(t.kt, xr[s][e][g], ci[g]);
+      }
+#pragma unroll
+      for (int g = 0; g < NG; ++g) {
+        dr[s][e][g] = mfma4(c.kt, xc[S][g].y, dr[s][e][g]);
+        di[s][e][g] = mfma4(c.kq, xc[S][g].y, di[s][e][g]);
+        cr[g] = mfma4(t.ks, xi[s][e][g], cr[g]);
+        ci[g] = mfma4(t.kq, xi[s][e][g], ci[g]);
+      }
+      if (u == 0 && st > 0) col_out(st - 1, pr, pi);
+    };
+    unit(std::integral_constant<int, 0>());
+    unit(std::integral_constant<int, 1>());
+    if constexpr (UN > 2) {
+      unit(std::integral_constant<int, 2>());
+      unit(std::integral_constant<int, 3>());
+    }
+    static_assert(UN == 2 || UN == 4, "units of a step");
+    if (st > 0 && st % SPC == 0) chunk_out(st / SPC - 1);
+  };
+  fetch(0, std::integral_constant<int, 0>());
+  if constexpr (AHEAD >= 2) fetch(1, std::integral_constant<int, 1>());
+  if constexpr (AHEAD >= 3) fetch(2, std::integral_constant<int, 2>());
+  exchange(std::integral_constant<int, 0>(), std::integral_constant<int, 0>(), std::integral_constant<int, 0>());
+  for (int st = 0; st < STEPS; st += 4) {
+    step(st, std::integral_constant<int, 0>());
+    step(st + 1, std::integral_constant<int, 1>());
+    step(st + 2, std::integral_constant<int, 2>());
+    step(st + 3, std::integral_constant<int, 3>());
+  }
+  col_out(STEPS - 1, cr, ci);
+  chunk_out(STEPS / SPC - 1);
+  // D[i = l2][j = l0] of block lb: row pair l2 + 4 lb, half-vector l0
+#pragma unroll
+  for (int g = 0; g < NG; ++g) {
+    const int q = 4 * g + l0;
+    if (q >= nv) continue;
+    double2* rp = rowpart + ((size_t)q * nblk + blk) * R + wave * RT + (l2 + 4 * lb) * VW;
+#pragma unroll
+    for (int s = 0; s < SUB; ++s)
+#pragma unroll
+      for (int e = 0; e < VW; ++e) {
+        const double vx = dr[s][e][g], vy = di[s][e][g];
+        rp[s * 16 * VW + e] = (MODE == T64_H && (q & 1)) ? make_double2(-vy, vx) : make_double2(vx, vy);
+      }
+  }
+}
+
+// nx: entries of a column of V (its leading dimension ldv)
+template <int R, int AR, int MODE>
+hipError_t launch_mfma(int nv, const Layout& L, const MatPtrs& m, const double2* V, int64_t ldv, int64_t nx,
+                       double sb, double2* part, hipStream_t s) {
+  double2* rowpart = part;
+  double2* colpart = part + (size_t)nv * L.nblk * R;
+  const dim3 grid((unsigned)L.nblk), wg(64 * mfma_waves(R));
+  if (nv <= 4)
+    hipLaunchKernelGGL((mfma_pass_kernel<R, AR, MODE, 1>), grid, wg, 0, s, m.a, m.alo, m.b, m.blo, L.blkmap, L.nblk,
+                       nx, V, ldv, nv, sb, rowpart, colpart);
+  else if constexpr (MODE == T64_H)
+    hipLaunchKernelGGL((mfma_pass_kernel<R, AR, MODE, 2>), grid, wg, 0, s, m.a, m.alo, m.b, m.blo, L.blkmap, L.nblk,
+                       nx, V, ldv, nv, sb, rowpart, colpart);
+  return hipGetLastError();
+}
+
 // Sum of the partials of a multi-vector pass (sd == 0: output q to column q of
 // MV) or of a full-H product (sd != 0: outputs 2q, 2q+1 are K1 u_q and K2 w_q;
 // the workgroup of vector q sums both and writes the top (K1 u + K2 w) / 2 and
@@ -1348,8 +1660,10 @@ hipError_t launch_mh(int nh, const Layout& L, const MatPtrs& m, const double2* V
     // u, w of every vector over the padded length, after the partials (mh_part_elems)
     const int64_t pl = (int64_t)L.nb * R;
     double2* uw = colpart + (size_t)2 * nh * L.nblk * R;
+    const bool mfma = mh_on_mfma(R, AR, nh);
     hipLaunchKernelGGL(hsd_stage_kernel, dim3((unsigned)((pl + kThreads - 1) / kThreads), (unsigned)nh),
-                       dim3(kThreads), 0, s, V, ldv, ldh, L.n, pl, uw);
+                       dim3(kThreads), 0, s, V, ldv, ldh, L.n, pl, (int)mfma, uw);
+    if (mfma) return launch_mfma<R, AR, T64_H>(2 * nh, L, m, uw, pl, pl, 1.0, part, s);
     const dim3 grid((unsigned)L.nblk);
     if (nh == 1)
       hipLaunchKernelGGL((mh_stream_kernel<R, AR, 1>), grid, dim3(kThreads), 0, s, m.a, m.alo, m.b, m.blo,
@@ -1357,12 +1671,14 @@ hipError_t launch_mh(int nh, const Layout& L, const MatPtrs& m, const double2* V
     else if (nh == 2)
       hipLaunchKernelGGL((mh_stream_kernel<R, AR, 2>), grid, dim3(kThreads), 0, s, m.a, m.alo, m.b, m.blo,
                          L.blkmap, L.nblk, L.n, uw, pl, rowpart, colpart);
-    else if (nh == 3)
-      hipLaunchKernelGGL((mh_stream_kernel<R, AR, 3>), grid, dim3(kThreads), 0, s, m.a, m.alo, m.b, m.blo,
-                         L.blkmap, L.nblk, L.n, uw, pl, rowpart, colpart);
-    else
-      hipLaunchKernelGGL((mh_stream_kernel<R, AR, 4>), grid, dim3(kThreads), 0, s, m.a, m.alo, m.b, m.blo,
-                         L.blkmap, L.nblk, L.n, uw, pl, rowpart, colpart);
+    if constexpr (!mh_on_mfma(R, AR, 3)) {
+      if (nh == 3)
+        hipLaunchKernelGGL((mh_stream_kernel<R, AR, 3>), grid, dim3(kThreads), 0, s, m.a, m.alo, m.b, m.blo,
+                           L.blkmap, L.nblk, L.n, uw, pl, rowpart, colpart);
+      else if (nh == 4)
+        hipLaunchKernelGGL((mh_stream_kernel<R, AR, 4>), grid, dim3(kThreads), 0, s, m.a, m.alo, m.b, m.blo,
+                           L.blkmap, L.nblk, L.n, uw, pl, rowpart, colpart);
+    }
     return hipGetLastError();
   }
 }
@@ -2651,6 +2967,8 @@ hipError_t launch_mk(const Layout& L, const MatPtrs& m, const double2* V, int64_
                      hipStream_t s) {
   if constexpr (R == 64) {
     launch_tile64<AR, BM == BM_CONJ ? T64_K : T64_A, NV>(L, m, V, ldv, 0, 0, nullptr, 0, sb, part, s);
+  } else if constexpr (mk_on_mfma(R, AR, BM, NV)) {
+    return launch_mfma<R, AR, BM == BM_CONJ ? T64_K : T64_A>(NV, L, m, V, ldv, L.n, sb, part, s);
   } else {
     using Sh = MkShape<R, AR, NV>;
     double2* rowpart = part;
@@ -2728,7 +3046,8 @@ hipError_t mk_apply(const Layout& L, Arith ar, BMode bm, const MatPtrs& m, int n
     e = hipEventRecord(ev1, s);
     if (e != hipSuccess) return e;
   }
-  const int ns = L.R < mk_rows(nv) ? 1 : L.R / mk_rows(nv);
+  // (the matrix-core pass writes one set of column partials)
+  const int ns = mk_on_mfma(L.R, ar, bm, nv) || L.R < mk_rows(nv) ? 1 : L.R / mk_rows(nv);
   const double2* rowpart = part;
   const double2* colpart = part + (size_t)nv * L.nblk * L.R;
   launch_mh_reduce(L, nv, ns, rowpart, colpart, out, ldo, 0, 1.0, m, V, ldv, 0, 0, s);

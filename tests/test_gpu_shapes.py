@@ -112,3 +112,28 @@ def test_gradient_tiles(kind, n, k):
         terms = np.real(np.conj(ref) * c)
         assert abs(v - sc * np.sum(terms)) <= 1e-14 * np.sum(np.abs(ref) * np.abs(c))
     s.close()
+
+
+# the multi-vector products of every larger block edge: one block, ragged block rows, several vectors
+# per read and a remainder (7 = 4 + 3)
+@pytest.mark.parametrize("block", [128, 256, 512])
+@pytest.mark.parametrize("n", [100, 512, 1100])
+@pytest.mark.parametrize("storage", ["c128", "hilo"])
+def test_large_block_products(block, n, storage, monkeypatch):
+    print(f"large block products n={n} block={block} storage={storage}", flush=True)
+    rng = np.random.default_rng(3000 + n)
+    A, B = random_herm(rng, n), random_sym(rng, n, 0.5)
+    ap, bp = pack_upper(A), pack_upper(B)
+    ap32, bp32 = hi_operator(ap, bp)
+    s = make_solver("ph", ap, bp, storage, block, monkeypatch)
+    for prec in ["fp64"] + (["hi64"] if storage == "hilo" else []):
+        pa, pb = (ap32, bp32) if prec == "hi64" else (ap, bp)
+        for op in ["A", "K1", "K2", "H"]:
+            length = 2 * n if op == "H" else n
+            for nvec in [1, 2, 3, 4, 7]:
+                x = rng.standard_normal((nvec, length)) + 1j * rng.standard_normal((nvec, length))
+                got = host(s.apply(op, dev(x), precision=prec))
+                ref = oracle.apply_dense(op, pa, x, pb)
+                err = np.max(np.abs(got - ref)) / np.max(np.abs(ref))
+                assert err < 1e-13, (op, prec, nvec, err)
+    s.close()
