@@ -11,6 +11,7 @@
 #include <stdint.h>
 
 #include "bse_internal.h"
+#include "bse_wave.h"
 
 namespace bse {
 namespace {
@@ -289,172 +290,292 @@ __global__ void __launch_bounds__(256)
     if (c < nb) A[(size_t)(j0 + c) * ld + i] = x[c];
 }
 
-// Block-wide sum (blockDim.x = 1024) into every thread.
-__device__ inline double block_sum1024(double v, double* red) {
+// Sum over a wavefront into every lane, fixed order.
+__device__ inline double wave_sum64(double v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
-  if (l == 0) red[w] = v;
-  __syncthreads();
+  return v;
+}
+
+// Skew-symmetric Householder reduction: two launches per column j (local panel
+// column t), bound by their latency, not by the reads (the trailing matrix is
+// 33 MB at order 2048).  A launch for each of the reflector, the product, the
+// corrections, p and the panel update, one row per thread with 256 columns in
+// sequence in the product, took 29 us per column at order 2048; 11.3 us now.
+//
+// 16 waves per workgroup, so that a wave's share of the columns (16 of 256), of the
+// panel's pairs and of its remaining columns is one batch of loads (four waves:
+// 13.3 us per column for both).
+constexpr int kSW = 16;
+
+// The reflector of column a = W[j+1:, j]: (I - tau v v^T) a = beta e_1, v_0 = 1,
+// v_i = a_i sc; every wave forms (beta, tau, sc) itself from the npn partial
+// sums of a_i^2, i > j + 1, that the launch before left in pn.
+__device__ inline void reflector(const double* __restrict__ pn, int npn, double alpha, int lane, double& beta,
+                                 double& tau, double& sc) {
   double s = 0.0;
-  if (threadIdx.x < 64) {
-    s = threadIdx.x < 16 ? red[threadIdx.x] : 0.0;
-#pragma unroll
-    for (int o = 8; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-    if (threadIdx.x == 0) red[16] = s;
-  }
-  __syncthreads();
-  s = red[16];
-  __syncthreads();
-  return s;
-}
-
-// Skew-symmetric Householder reduction, column j (local panel column t).
-// The panel's earlier reflections have already been applied to this column
-// (skew_eager_kernel), so a = W[j+1:, j] as stored; the reflector
-// (I - tau v v^T) a = beta e_1 with v_0 = 1 overwrites W[j+1:, j] and goes to
-// Vp[:, t]; e[j] = beta, tau[j] = tau.  One workgroup.
-__global__ void __launch_bounds__(1024)
-    skew_col_kernel(double* __restrict__ W, int64_t ld, int64_t m, int64_t j, int t, double* __restrict__ Vp,
-                    int64_t ldp, double* __restrict__ tau, double* __restrict__ e) {
-  __shared__ double red[24];
-  __shared__ double scale;
-  const int tid = threadIdx.x;
-  double* col = W + (size_t)j * ld;
-  double ss = 0.0;
-  for (int64_t i = j + 2 + tid; i < m; i += 1024) ss = fma(col[i], col[i], ss);
-  const double sig2 = block_sum1024(ss, red);
-  if (tid == 0) {
-    const double alpha = col[j + 1];
-    double beta, tu, sc;
-    if (sig2 == 0.0) {
-      beta = alpha;
-      tu = 0.0;
-      sc = 0.0;
-    } else {
-      beta = -copysign(sqrt(fma(alpha, alpha, sig2)), alpha);
-      tu = (beta - alpha) / beta;
-      sc = 1.0 / (alpha - beta);
-    }
-    e[j] = beta;
-    tau[j] = tu;
-    scale = sc;
-  }
-  __syncthreads();
-  const double sc = scale;
-  for (int64_t i = j + 1 + tid; i < m; i += 1024) {
-    const double v = i == j + 1 ? 1.0 : col[i] * sc;
-    col[i] = v;
-    Vp[(size_t)t * ldp + i] = v;
+  for (int q = lane; q < npn; q += 64) s += pn[q];
+  const double sig2 = wave_sum64(s);
+  if (sig2 == 0.0) {
+    beta = alpha;
+    tau = 0.0;
+    sc = 0.0;
+  } else {
+    beta = -copysign(sqrt(fma(alpha, alpha, sig2)), alpha);
+    tau = (beta - alpha) / beta;
+    sc = 1.0 / (alpha - beta);
   }
 }
 
-// The new reflection pair (v, z) = (Vp[:, t], Zp[:, t]) of column j applied to
-// the panel's remaining columns c in (j, r0): W[i, c] += v_i z_c - z_i v_c for
-// rows i > j.  Grid: row blocks x columns.
+// pn[b] = sum of W[i, j]^2 over the block's rows i >= j + 2 (a panel's first column).
 __global__ void __launch_bounds__(256)
-    skew_eager_kernel(double* __restrict__ W, int64_t ld, int64_t m, int64_t j, int t,
-                      const double* __restrict__ Vp, const double* __restrict__ Zp, int64_t ldp) {
-  const int64_t c = j + 1 + blockIdx.y;
-  const int64_t i = j + 1 + (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= m) return;
-  const double* v = Vp + (size_t)t * ldp;
-  const double* z = Zp + (size_t)t * ldp;
-  double* w = W + (size_t)c * ld + i;
-  *w = fma(v[i], z[c], fma(-z[i], v[c], *w));
+    skew_norm_kernel(const double* __restrict__ W, int64_t ld, int64_t m, int64_t j, double* __restrict__ pn) {
+  __shared__ double red[4];
+  const int64_t i = j + 2 + (int64_t)blockIdx.x * 256 + threadIdx.x;
+  const double a = i < m ? W[(size_t)j * ld + i] : 0.0;
+  const double s = wave_sum64(a * a);
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) pn[blockIdx.x] = red[0] + red[1] + red[2] + red[3];
 }
 
-// Partial products of the trailing matrix with the reflector v of column j:
-// part[y * m + i] = sum over columns c in chunk y (of 256, from j + 1) of
-// W[i, c] v_c, rows i > j.
-__global__ void __launch_bounds__(256)
-    skew_gemv_kernel(const double* __restrict__ W, int64_t ld, int64_t m, int64_t j, double* __restrict__ part) {
+// First launch of column j.  Workgroups b < nrow nchunk: partial products of
+// the stored trailing matrix with v, 64 rows by 256 columns (each wave an equal
+// share): part[y m + i] = sum over columns c of chunk y (from j + 1) of W[i, c]
+// v_c.  The others, 2 t of them: dots[s] = Vp[:, s] . v and dots[t + s] =
+// Zp[:, s] . v over the rows from r0 on (s = t - 1: from j + 1 on), the part of
+// the panel's updates not yet stored in W (see skew_update_kernel).  Workgroup
+// 0 records e[j] = beta, tau[j] and *scp = sc.
+__global__ void __launch_bounds__(64 * kSW)
+    skew_mv_kernel(const double* __restrict__ W, int64_t ld, int64_t m, int64_t j, int64_t r0, int t, int nrow,
+                   int nchunk, const double* __restrict__ pn, int npn, const double* __restrict__ Vp,
+                   const double* __restrict__ Zp, int64_t ldp, double* __restrict__ part, double* __restrict__ dots,
+                   double* __restrict__ tau, double* __restrict__ e, double* __restrict__ scp) {
+  constexpr int CW = 256 / kSW;  // columns of a wave
   __shared__ double vs[256];
-  const int tid = threadIdx.x;
-  const int64_t c0 = j + 1 + (int64_t)blockIdx.y * 256;
-  const double* v = W + (size_t)j * ld;
-  vs[tid] = c0 + tid < m ? v[c0 + tid] : 0.0;
-  __syncthreads();
-  const int64_t i = j + 1 + (int64_t)blockIdx.x * 256 + tid;
-  if (i >= m) return;
-  const int cnt = (int)(m - c0 < 256 ? m - c0 : 256);
+  __shared__ double red[kSW][64];
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const double* a = W + (size_t)j * ld;
+  double beta, tj, sc;
+  reflector(pn, npn, a[j + 1], lane, beta, tj, sc);
+  const int b = blockIdx.x;
+  if (b == 0 && tid == 0) {
+    e[j] = beta;
+    tau[j] = tj;
+    *scp = sc;
+  }
+  if (b >= nrow * nchunk) {
+    const int d = b - nrow * nchunk, s_ = d < t ? d : d - t;
+    const double* q = (d < t ? Vp : Zp) + (size_t)s_ * ldp;
+    double acc = 0.0;
+    for (int64_t i = (s_ == t - 1 ? j + 1 : r0) + tid; i < m; i += 64 * kSW)
+      acc = fma(q[i], i == j + 1 ? 1.0 : a[i] * sc, acc);
+    acc = wave_sum64(acc);
+    if (lane == 0) red[0][wave] = acc;
+    __syncthreads();
+    if (tid == 0) {
+      double t = red[0][0];
+      for (int w = 1; w < kSW; ++w) t += red[0][w];
+      dots[d] = t;
+    }
+    return;
+  }
+  const int y = b / nrow;
+  const int64_t i = j + 1 + (int64_t)(b % nrow) * 64 + lane;
+  const int64_t cy = j + 1 + (int64_t)y * 256, c0 = cy + wave * CW;
+  if (tid < 256) vs[tid] = cy + tid < m ? (cy + tid == j + 1 ? 1.0 : a[cy + tid] * sc) : 0.0;
+  double w[CW];
   const double* wr = W + (size_t)c0 * ld + i;
+#pragma unroll
+  for (int u = 0; u < CW; ++u) w[u] = i < m && c0 + u < m ? wr[(size_t)u * ld] : 0.0;
+  __syncthreads();
   double s0 = 0.0, s1 = 0.0;
-  int q = 0;
-  for (; q + 1 < cnt; q += 2) {
-    s0 = fma(wr[(size_t)q * ld], vs[q], s0);
-    s1 = fma(wr[(size_t)(q + 1) * ld], vs[q + 1], s1);
+#pragma unroll
+  for (int u = 0; u < CW; u += 2) {
+    s0 = fma(w[u], vs[wave * CW + u], s0);
+    s1 = fma(w[u + 1], vs[wave * CW + u + 1], s1);
   }
-  if (q < cnt) s0 = fma(wr[(size_t)q * ld], vs[q], s0);
-  part[(size_t)blockIdx.y * m + i] = s0 + s1;
+  red[wave][lane] = s0 + s1;
+  __syncthreads();
+  if (wave == 0 && i < m) {
+    double t = red[0][lane];
+#pragma unroll
+    for (int u = 1; u < kSW; ++u) t += red[u][lane];
+    part[(size_t)y * m + i] = t;
+  }
 }
 
-// dots[s] = Vp[r0:, s] . v (s < t) and dots[t + s] = Zp[r0:, s] . v, one
-// workgroup per dot product: the panel's reflections restricted to the
-// trailing columns (>= r0), the part of the update not yet stored in W.
-__global__ void __launch_bounds__(1024)
-    skew_dots_kernel(const double* __restrict__ W, int64_t ld, int64_t m, int64_t j, int64_t r0, int t,
-                     const double* __restrict__ Vp, const double* __restrict__ Zp, int64_t ldp,
-                     double* __restrict__ dots) {
-  __shared__ double red[24];
-  const int s_ = blockIdx.x;
-  const double* q = s_ < t ? Vp + (size_t)s_ * ldp : Zp + (size_t)(s_ - t) * ldp;
-  const double* v = W + (size_t)j * ld;
-  double acc = 0.0;
-  for (int64_t i = r0 + threadIdx.x; i < m; i += 1024) acc = fma(q[i], v[i], acc);
-  acc = block_sum1024(acc, red);
-  if (threadIdx.x == 0) dots[s_] = acc;
-}
-
-// p = (stored trailing W) v + Vp (Zp[r0:]^T v) - Zp (Vp[r0:]^T v) on rows
-// i > j: the skew matrix as updated by the panel so far, times v (the stored
-// panel columns already carry the panel's reflections); Zp[:, t] = tau_j p.
-__global__ void __launch_bounds__(256)
-    skew_p_kernel(const double* __restrict__ part, int nchunk, int64_t m, int64_t j, int t,
-                  const double* __restrict__ Vp, double* __restrict__ Zp, int64_t ldp,
-                  const double* __restrict__ dots, const double* __restrict__ tau) {
-  __shared__ double dv[64], dz[64];
-  const int tid = threadIdx.x;
-  if (tid < t) {
-    dv[tid] = dots[tid];
-    dz[tid] = dots[t + tid];
+// Second launch of column j, 64 rows i > j per workgroup: the reflector goes to
+// W[j+1:, j] and Vp[:, t]; z = tau p with p = (the skew matrix as updated by the
+// panel so far) v = part + Vp (Zp^T v) - Zp (Vp^T v) goes to Zp[:, t].  The
+// reflection pair (v, z) of a column changes the panel's remaining columns c by
+// W[i, c] += v_i z_c - z_i v_c; z_c of other workgroups' rows is not known
+// here, so the pair is applied one launch later (the pair of column j - 1 to
+// the columns c > j), except to the next column j + 1, whose z every workgroup
+// forms for itself.  With the next column complete its norm partials pn are
+// left for the next reflector.
+__global__ void __launch_bounds__(64 * kSW)
+    skew_update_kernel(double* __restrict__ W, int64_t ld, int64_t m, int64_t j, int64_t r0, int t, int nchunk,
+                       const double* __restrict__ part, const double* __restrict__ dots,
+                       const double* __restrict__ tau, const double* __restrict__ scp, double* __restrict__ Vp,
+                       double* __restrict__ Zp, int64_t ldp, double* __restrict__ pn) {
+  __shared__ double red[kSW][64];
+  __shared__ double znext;
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const int64_t i = j + 1 + (int64_t)blockIdx.x * 64 + lane;
+  const bool in = i < m;
+  const double tj = tau[j], sc = *scp;
+  double p = 0.0;
+  if (in) {
+    for (int y = wave; y < nchunk; y += kSW) p += part[(size_t)y * m + i];
+#pragma unroll 4
+    for (int s_ = wave; s_ < t; s_ += kSW)
+      p = fma(Vp[(size_t)s_ * ldp + i], dots[t + s_], fma(-Zp[(size_t)s_ * ldp + i], dots[s_], p));
+  }
+  red[wave][lane] = p;
+  const bool more = j + 1 < r0;  // panel columns remain
+  if (wave == kSW - 1 && more) {
+    double q = 0.0;
+    for (int y = lane; y < nchunk; y += 64) q += part[(size_t)y * m + j + 1];
+    if (lane < t) q = fma(Vp[(size_t)lane * ldp + j + 1], dots[t + lane], fma(-Zp[(size_t)lane * ldp + j + 1], dots[lane], q));
+    q = wave_sum64(q);
+    if (lane == 0) znext = tj * q;
   }
   __syncthreads();
-  const int64_t i = j + 1 + (int64_t)blockIdx.x * 256 + tid;
-  if (i >= m) return;
-  double p = 0.0;
-  for (int y = 0; y < nchunk; ++y) p += part[(size_t)y * m + i];
-  for (int s_ = 0; s_ < t; ++s_)
-    p = fma(Vp[(size_t)s_ * ldp + i], dz[s_], fma(-Zp[(size_t)s_ * ldp + i], dv[s_], p));
-  Zp[(size_t)t * ldp + i] = tau[j] * p;
+  double z = red[0][lane];
+#pragma unroll
+  for (int w = 1; w < kSW; ++w) z += red[w][lane];
+  z *= tj;
+  // (every wave reads its rows of column j before wave 0 writes them below)
+  const double v = !in ? 0.0 : i == j + 1 ? 1.0 : W[(size_t)j * ld + i] * sc;
+  const double vo = in && t > 0 ? Vp[(size_t)(t - 1) * ldp + i] : 0.0;
+  const double zo = in && t > 0 ? Zp[(size_t)(t - 1) * ldp + i] : 0.0;
+  double nrm = 0.0;
+  if (in) {
+#pragma unroll 4
+    for (int64_t c = j + 1 + wave; c < r0; c += kSW) {
+      double w = W[(size_t)c * ld + i];
+      if (t > 0) w = fma(vo, Zp[(size_t)(t - 1) * ldp + c], fma(-zo, Vp[(size_t)(t - 1) * ldp + c], w));
+      if (c == j + 1) {
+        w = fma(v, znext, w - z);  // v_c = 1
+        if (i >= j + 3) nrm = w * w;
+      }
+      W[(size_t)c * ld + i] = w;
+    }
+  }
+  __syncthreads();
+  if (wave == 0) {
+    if (in) {
+      W[(size_t)j * ld + i] = v;
+      Vp[(size_t)t * ldp + i] = v;
+      Zp[(size_t)t * ldp + i] = z;
+    }
+    if (more) {
+      nrm = wave_sum64(nrm);
+      if (lane == 0) pn[blockIdx.x] = nrm;
+    }
+  }
 }
 
 // Back-transformation of the eigenvectors, one workgroup per real column x
 // of R (m rows): x <- H_0 H_1 ... H_{m-2} x with H_j = I - tau_j v_j v_j^T
-// (v_j in W[j+1:, j]), then x <- L^{-T} x (L lower, in l).
+// (v_j in W[j+1:, j]), then x <- L^{-T} x (L lower, in l).  Both are chains of m
+// reductions over the workgroup and bound by their latency, so they go eight at
+// a time: one reduction gives the eight products v_q . x and the 28 products v_q .
+// v_r of a block of reflectors, from which every thread forms the eight steps
+// y_q = tau_q (v_q . x - sum over the reflectors r applied before of y_r v_q . v_r);
+// the solve takes the eight dot products of a block of rows with the solved part
+// together and finishes the 8 x 8 triangle in one thread.  One reflector and
+// one row at a time took 6.0 ms at order 2048, 2.0 ms here.
 __global__ void __launch_bounds__(1024)
     skew_back_kernel(const double* __restrict__ W, int64_t ld, const double* __restrict__ tau,
                      const double* __restrict__ l, int64_t ldl, int64_t m, double* __restrict__ R, int64_t ldr) {
-  __shared__ double red[24];
+  constexpr int NB = 8, NG = NB * (NB - 1) / 2, NV = 48;  // 8 + 28 values, padded to three groups of 16
+  __shared__ double red[16][NV];
+  __shared__ double tot[NV];
+  __shared__ double tri[NB][NB];
   double* x = R + (size_t)blockIdx.x * ldr;
-  const int tid = threadIdx.x;
-  for (int64_t j = m - 2; j >= 0; --j) {
-    const double tj = tau[j];
-    if (tj == 0.0) continue;  // uniform across the workgroup
-    const double* v = W + (size_t)j * ld;
-    double s = 0.0;
-    for (int64_t i = j + 1 + tid; i < m; i += 1024) s = fma(v[i], x[i], s);
-    s = block_sum1024(s, red) * tj;
-    for (int64_t i = j + 1 + tid; i < m; i += 1024) x[i] = fma(-s, v[i], x[i]);
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  // pair (q, r), r > q -> 8 + gi(q, r)
+  auto gi = [](int q, int r) { return NB + q * (2 * NB - q - 1) / 2 + (r - q - 1); };
+  for (int64_t jb = (m - 2) / NB * NB; jb >= 0; jb -= NB) {  // reflectors jb .. jb + 7 (those below m - 1)
+    double val[NV];
+#pragma unroll
+    for (int q = 0; q < NV; ++q) val[q] = 0.0;
+    for (int64_t i = jb + 1 + tid; i < m; i += 1024) {
+      double v[NB];
+#pragma unroll
+      for (int q = 0; q < NB; ++q) v[q] = jb + q < i ? W[(size_t)(jb + q) * ld + i] : 0.0;  // i < m: jb + q < m - 1
+      const double xi = x[i];
+#pragma unroll
+      for (int q = 0; q < NB; ++q) {
+        val[q] = fma(v[q], xi, val[q]);
+#pragma unroll
+        for (int r = q + 1; r < NB; ++r) val[gi(q, r)] = fma(v[q], v[r], val[gi(q, r)]);
+      }
+    }
+#pragma unroll
+    for (int g = 0; g < NV / 16; ++g) {
+      double t[16];
+#pragma unroll
+      for (int q = 0; q < 16; ++q) t[q] = val[16 * g + q];
+      red[wave][16 * g + wave_sum_index<16>(lane)] = wave_sum_n<16>(t);
+    }
+    __syncthreads();
+    if (tid < NB + NG) {
+      double t = 0.0;
+#pragma unroll
+      for (int w = 0; w < 16; ++w) t += red[w][tid];
+      tot[tid] = t;
+    }
+    __syncthreads();
+    double y[NB];
+#pragma unroll
+    for (int q = NB - 1; q >= 0; --q) {  // H_{jb+7} is applied first
+      double d = tot[q];
+#pragma unroll
+      for (int r = q + 1; r < NB; ++r) d = fma(-y[r], tot[gi(q, r)], d);
+      y[q] = (jb + q < m - 1 ? tau[jb + q] : 0.0) * d;
+    }
+    for (int64_t i = jb + 1 + tid; i < m; i += 1024) {
+      double xi = x[i];
+#pragma unroll
+      for (int q = NB - 1; q >= 0; --q) xi = fma(-y[q], jb + q < i ? W[(size_t)(jb + q) * ld + i] : 0.0, xi);
+      x[i] = xi;
+    }
     __syncthreads();
   }
-  // L^T x = b, backward: x_j = (b_j - sum_{i > j} L_ij x_i) / L_jj
-  for (int64_t j = m - 1; j >= 0; --j) {
-    const double* lc = l + (size_t)j * ldl;
-    double s = 0.0;
-    for (int64_t i = j + 1 + tid; i < m; i += 1024) s = fma(lc[i], x[i], s);
-    s = block_sum1024(s, red);
-    if (tid == 0) x[j] = (x[j] - s) / lc[j];
+  // L^T x = b, backward, rows jb .. jb + 7 (those below m): x_j = (b_j - sum_{i > j} L_ij x_i) / L_jj
+  for (int64_t jb = (m - 1) / NB * NB; jb >= 0; jb -= NB) {
+    double val[NB];
+#pragma unroll
+    for (int q = 0; q < NB; ++q) val[q] = 0.0;
+    for (int64_t i = jb + NB + tid; i < m; i += 1024) {
+      const double xi = x[i];
+#pragma unroll
+      for (int q = 0; q < NB; ++q) val[q] = fma(l[(size_t)(jb + q) * ldl + i], xi, val[q]);
+    }
+    red[wave][wave_sum_index<NB>(lane)] = wave_sum_n<NB>(val);
+    if (tid < NB * NB) {  // the block's triangle, identity past the last row
+      const int q = tid / NB, r = tid % NB;
+      tri[q][r] = jb + r < m && r >= q ? l[(size_t)(jb + q) * ldl + jb + r] : (q == r ? 1.0 : 0.0);
+    }
+    __syncthreads();
+    if (tid == 0) {
+      double xs[NB];
+#pragma unroll
+      for (int q = NB - 1; q >= 0; --q) {
+        double s = 0.0;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) s += red[w][q];
+#pragma unroll
+        for (int r = q + 1; r < NB; ++r) s = fma(tri[q][r], xs[r], s);
+        xs[q] = jb + q < m ? (x[jb + q] - s) / tri[q][q] : 0.0;
+      }
+#pragma unroll
+      for (int q = 0; q < NB; ++q)
+        if (jb + q < m) x[jb + q] = xs[q];
+    }
     __syncthreads();
   }
 }
@@ -530,30 +651,28 @@ hipError_t dense_cholesky(double* A, int64_t ld, int64_t m, int* flag, hipStream
 hipError_t skew_tridiag(double* W, int64_t ld, int64_t m, double* Vp, double* Zp, int64_t ldp, double* part,
                         double* dots, double* tau, double* e, hipStream_t s) {
   constexpr int nb = 64;
+  // behind the partial products: sc of the current reflector, the norm partials of the next one
+  double* scp = part + (size_t)((m - 1 + 255) / 256) * m;
+  double* pn = scp + 1;
   for (int64_t j0 = 0; j0 + 1 < m; j0 += nb) {
     const int tend = (int)(m - 1 - j0 < nb ? m - 1 - j0 : nb);
-    hipError_t err = hipMemsetAsync(Vp, 0, sizeof(double) * (size_t)ldp * nb, s);
-    if (err == hipSuccess) err = hipMemsetAsync(Zp, 0, sizeof(double) * (size_t)ldp * nb, s);
-    if (err != hipSuccess) return err;
     const int64_t r0 = j0 + tend;
+    int npn = (int)((m - j0 - 2 + 255) / 256);
+    if (npn > 0) hipLaunchKernelGGL(skew_norm_kernel, dim3((unsigned)npn), dim3(256), 0, s, W, ld, m, j0, pn);
     for (int t = 0; t < tend; ++t) {
       const int64_t j = j0 + t, L = m - j - 1;
-      hipLaunchKernelGGL(skew_col_kernel, dim3(1), dim3(1024), 0, s, W, ld, m, j, t, Vp, ldp, tau, e);
-      const unsigned rb = (unsigned)((L + 255) / 256);
-      hipLaunchKernelGGL(skew_gemv_kernel, dim3(rb, rb), dim3(256), 0, s, W, ld, m, j, part);
-      if (t > 0)
-        hipLaunchKernelGGL(skew_dots_kernel, dim3((unsigned)(2 * t)), dim3(1024), 0, s, W, ld, m, j, r0, t, Vp, Zp,
-                           ldp, dots);
-      hipLaunchKernelGGL(skew_p_kernel, dim3(rb), dim3(256), 0, s, part, (int)rb, m, j, t, Vp, Zp, ldp, dots, tau);
-      if (j + 1 < r0)
-        hipLaunchKernelGGL(skew_eager_kernel, dim3(rb, (unsigned)(r0 - j - 1)), dim3(256), 0, s, W, ld, m, j, t, Vp,
-                           Zp, ldp);
+      const int nrow = (int)((L + 63) / 64), nchunk = (int)((L + 255) / 256);
+      hipLaunchKernelGGL(skew_mv_kernel, dim3((unsigned)(nrow * nchunk + 2 * t)), dim3(64 * kSW), 0, s, W, ld, m, j, r0, t,
+                         nrow, nchunk, pn, npn, Vp, Zp, ldp, part, dots, tau, e, scp);
+      hipLaunchKernelGGL(skew_update_kernel, dim3((unsigned)nrow), dim3(64 * kSW), 0, s, W, ld, m, j, r0, t, nchunk, part,
+                         dots, tau, scp, Vp, Zp, ldp, pn);
+      npn = nrow;
     }
     const int64_t rest = m - r0;
     if (rest > 0) {
       // trailing W += Vp Zp^T - Zp Vp^T (rows and columns >= r0)
       double* c = W + (size_t)r0 * ld + r0;
-      err = dense_gemm(0, 1, rest, rest, tend, 1.0, Vp + r0, ldp, Zp + r0, ldp, 1.0, c, ld, 0, s);
+      hipError_t err = dense_gemm(0, 1, rest, rest, tend, 1.0, Vp + r0, ldp, Zp + r0, ldp, 1.0, c, ld, 0, s);
       if (err == hipSuccess) err = dense_gemm(0, 1, rest, rest, tend, -1.0, Zp + r0, ldp, Vp + r0, ldp, 1.0, c, ld, 0, s);
       if (err != hipSuccess) return err;
     }

@@ -265,7 +265,7 @@ hipError_t scale_cols(double2* x, double2* y, int64_t ld, int64_t n, int k, cons
 //     m x m W (full storage, destroyed): T[j+1, j] = e[j] (j < m - 1); the
 //     reflector H_j = I - tau[j] v v^T of column j, v_0 = 1, is left in
 //     W[j+1:, j].  Workspace: Vp, Zp (ldp >= m, 64 columns each), part
-//     (ceil((m - 1) / 256) * m), dots (128).
+//     ((ceil((m - 1) / 256) + 1) * m), dots (128).
 //   skew_back: for ncol real columns of R (m x ncol, leading dimension ldr),
 //     x <- L^{-T} Q x with Q = H_0 H_1 ... H_{m-2} from skew_tridiag and the
 //     lower factor L (leading dimension ldl).

@@ -2671,11 +2671,11 @@ bse_status bse_direct(bse_handle h, int32_t k, double* omega, void* x, void* y, 
     const double te = now_ms();
     // reduction workspace: G is free now
     const int64_t nch = (n2 - 1 + 255) / 256;
-    HIP_TRY(h, dev_alloc(h, bE, sizeof(double) * (size_t)(2 * n2 * 64 + nch * n2 + 128 + 2 * n2)));
+    HIP_TRY(h, dev_alloc(h, bE, sizeof(double) * (size_t)(2 * n2 * 64 + (nch + 1) * n2 + 128 + 2 * n2)));
     double* Vp = (double*)bE.p;
     double* Zp = Vp + (size_t)n2 * 64;
     double* part = Zp + (size_t)n2 * 64;
-    double* dots = part + (size_t)nch * n2;
+    double* dots = part + (size_t)(nch + 1) * n2;
     double* tau = dots + 128;
     double* ed = tau + n2;
     HIP_TRY(h, bse::skew_tridiag(Wm, n2, n2, Vp, Zp, n2, part, dots, tau, ed, s));

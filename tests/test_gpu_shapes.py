@@ -137,3 +137,17 @@ def test_large_block_products(block, n, storage, monkeypatch):
                 err = np.max(np.abs(got - ref)) / np.max(np.abs(ref))
                 assert err < 1e-13, (op, prec, nvec, err)
     s.close()
+
+
+# orders 2 n around the blocks of eight of the back-transformation, the panels of 64 columns and the
+# chunks of 256 columns of the reduction; tolerance 1e-12 as in test_gpu_direct
+@pytest.mark.parametrize("n", [1, 2, 4, 5, 31, 32, 33, 64, 65, 97, 128, 129, 161])
+def test_direct_orders(n):
+    import test_gpu_direct as tgd
+    print(f"direct orders n={n}", flush=True)
+    rng = np.random.default_rng(4000 + n)
+    A, B = random_herm(rng, n, lam_min=1.0), random_sym(rng, n, 0.5)
+    ap, bp = pack_upper(A), pack_upper(B)
+    s = make_solver("ph", ap, bp)
+    tgd.check_ph(s, ap, bp, max(1, n // 3))
+    s.close()
