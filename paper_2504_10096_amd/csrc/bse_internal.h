@@ -211,6 +211,16 @@ bool zchol(int s, double2* a);
 void zlsolve(int s, const double2* l, double2* x, int c);
 void zlhsolve(int s, const double2* l, double2* x, int c);
 
+// Device reduction of a complex Hermitian matrix (m x m, full storage,
+// column-major, leading dimension m, destroyed; 2 <= m <= kHermTridiagMax) to
+// real tridiagonal form, A = Q T Q^H (bse_heig.hip): d, e the diagonals of T,
+// Q = H_0 ... H_{m-2} with H_j = I - tau_j v_j v_j^H, v_j in rows j + 1 .. of
+// column j of V (one first).  work: 2 m complex entries.  Weak: a build of the
+// driver without device code has none and solves on the host.
+constexpr int kHermTridiagMax = 2048;
+__attribute__((weak)) hipError_t herm_tridiag(int m, double2* A, double2* V, double* d, double* e, double2* tau,
+                                              double2* work, hipStream_t s);
+
 // Residual pieces of one vector: part2[2*chunk] = ||out - sgn*om*(cj ? conj(v) : v)||^2 over the
 // chunk, part2[2*chunk+1] = ||v||^2; res[0..1] = sums over chunks.
 hipError_t resid_norms(const double2* out, const double2* v, int cj, double sgn_om, int64_t n,

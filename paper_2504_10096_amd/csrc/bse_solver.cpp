@@ -61,7 +61,8 @@ struct bse_handle_s {
   rocblas_handle eigh = nullptr;
   int eig_state = 0;
   int eig_cap = 0;  // largest order the buffers below hold
-  void *eig_a = nullptr, *eig_w = nullptr, *eig_e = nullptr, *eig_info = nullptr, *eig_work = nullptr;
+  void *eig_a = nullptr, *eig_w = nullptr, *eig_e = nullptr, *eig_info = nullptr, *eig_work = nullptr,
+       *eig_v = nullptr, *eig_z = nullptr, *eig_t = nullptr;
 };
 
 namespace {
@@ -112,18 +113,38 @@ bse_status fail(bse_handle h, bse_status s, const std::string& msg) {
 
 // Complex Hermitian eigenproblem of order m (column-major a, overwritten;
 // ascending w, orthonormal vectors z), the projected problems of the
-// restarts and of the refinement.  On the device with rocSOLVER's divide and
-// conquer above order kHostEig when it can be set up: at order 560 it takes
-// 16 ms against 53 ms for the host QR of bse_smalleig.cpp, while at small
-// orders its many launches dominate (ms, device / host with 16 / 4 / 1 threads,
-// copies included: order 48 1.1 / 0.31 / 0.35 / 0.29, 64 1.5 / 0.49 / 0.63 /
-// 0.64, 96 2.1 / 0.96 / 1.4 / 2.0, 128 3.2 / 1.8 / 2.6 / 4.5, 192 5.0 / 4.5 /
-// 7.9 / 14); atomics are off in its rocBLAS calls, so repeated solves stay
-// bitwise identical.  The buffers grow with the
+// restarts and of the refinement.  On the device above order kHostEig when it
+// can be set up: the reduction to tridiagonal form by herm_tridiag, its
+// eigenpairs by rocSOLVER's divide and conquer.  At small orders the launches
+// dominate (ms, device with the library's reduction / host QR of
+// bse_smalleig.cpp with 16 / 4 / 1 threads, copies included: order 48 1.1 / 0.31 /
+// 0.35 / 0.29, 64 1.5 / 0.49 / 0.63 / 0.64, 96 2.1 / 0.96 / 1.4 / 2.0, 128 3.2 /
+// 1.8 / 2.6 / 4.5, 192 5.0 / 4.5 / 7.9 / 14).  With herm_tridiag order 144 takes
+// 2.4 ms (3.45 with the library's reduction), 224 4.0 (6.2), 608 12.5 (16.0); the
+// host takes 6.3 ms at order 224, 53 at 560.  Atomics are off in the rocBLAS calls, so repeated solves stay bitwise identical.  The buffers grow with the
 // largest order seen and stay with the handle.  Where rocBLAS cannot create
 // a handle (no device), or the call reports an error or no convergence, the
 // host QR solves the same problem.  Returns false only if that fails too.
 constexpr int kHostEig = 128;
+
+// The library's part of a projected eigenproblem of order m: the eigenpairs of
+// the tridiagonal matrix in eig_w, eig_e and the back-transformation through the
+// reflectors in eig_v, eig_t into eig_z; above the orders of herm_tridiag the
+// whole problem, eig_a to eig_z (the same buffer there).
+bool solve_tridiag(bse_handle h, int m) {
+  auto* z = static_cast<rocblas_double_complex*>(h->eig_z);
+  auto* w = static_cast<double*>(h->eig_w);
+  auto* e = static_cast<double*>(h->eig_e);
+  auto* info = static_cast<rocblas_int*>(h->eig_info);
+  if (m > bse::kHermTridiagMax)
+    return rocsolver_zheevd(h->eigh, rocblas_evect_original, rocblas_fill_upper, m, z, m, w, e, info) ==
+           rocblas_status_success;
+  return rocsolver_zstedc(h->eigh, rocblas_evect_tridiagonal, m, w, e, z, m, info) == rocblas_status_success &&
+         rocsolver_zunmtr(h->eigh, rocblas_side_left, rocblas_fill_lower, rocblas_operation_none, m, m,
+                          static_cast<rocblas_double_complex*>(h->eig_v), m,
+                          static_cast<rocblas_double_complex*>(h->eig_t), z, m) == rocblas_status_success;
+}
+
 bool herm_eig_proj(bse_handle h, int m, double2* a, double* w, double2* z) {
   auto device = [&]() -> bool {
     if (h->eig_state == 0) {
@@ -139,7 +160,8 @@ bool herm_eig_proj(bse_handle h, int m, double2* a, double* w, double2* z) {
     }
     if (h->eig_state != 1) return false;
     if (m > h->eig_cap) {
-      for (void** p : {&h->eig_a, &h->eig_w, &h->eig_e, &h->eig_info, &h->eig_work}) {
+      for (void** p : {&h->eig_a, &h->eig_w, &h->eig_e, &h->eig_info, &h->eig_work, &h->eig_v, &h->eig_z,
+                       &h->eig_t}) {
         dfree(h, *p);
         *p = nullptr;
       }
@@ -147,38 +169,42 @@ bool herm_eig_proj(bse_handle h, int m, double2* a, double* w, double2* z) {
       if (dmalloc(h, &h->eig_a, sizeof(double2) * (size_t)m * m) != hipSuccess ||
           dmalloc(h, &h->eig_w, sizeof(double) * m) != hipSuccess ||
           dmalloc(h, &h->eig_e, sizeof(double) * m) != hipSuccess ||
-          dmalloc(h, &h->eig_info, sizeof(rocblas_int)) != hipSuccess)
+          dmalloc(h, &h->eig_info, sizeof(rocblas_int)) != hipSuccess ||
+          dmalloc(h, &h->eig_v, sizeof(double2) * (size_t)m * m) != hipSuccess ||
+          dmalloc(h, &h->eig_z, sizeof(double2) * (size_t)m * m) != hipSuccess ||
+          dmalloc(h, &h->eig_t, sizeof(double2) * 3 * (size_t)m) != hipSuccess)
         return false;
       // rocSOLVER's workspace for this order, from the handle's memory
       size_t ws = 0;
       if (rocblas_start_device_memory_size_query(h->eigh) != rocblas_status_success) return false;
-      (void)rocsolver_zheevd(h->eigh, rocblas_evect_original, rocblas_fill_upper, m,
-                             static_cast<rocblas_double_complex*>(h->eig_a), m, static_cast<double*>(h->eig_w),
-                             static_cast<double*>(h->eig_e), static_cast<rocblas_int*>(h->eig_info));
+      (void)solve_tridiag(h, m);
       if (rocblas_stop_device_memory_size_query(h->eigh, &ws) != rocblas_status_success) return false;
       if (dmalloc(h, &h->eig_work, ws ? ws : 1) != hipSuccess) return false;
       if (rocblas_set_workspace(h->eigh, h->eig_work, ws) != rocblas_status_success) return false;
       h->eig_cap = m;
     }
-    if (hipMemcpyAsync(h->eig_a, a, sizeof(double2) * (size_t)m * m, hipMemcpyHostToDevice, h->stream) !=
-        hipSuccess)
+    const bool own = m <= bse::kHermTridiagMax;
+    double2* in = static_cast<double2*>(own ? h->eig_a : h->eig_z);
+    if (hipMemcpyAsync(in, a, sizeof(double2) * (size_t)m * m, hipMemcpyHostToDevice, h->stream) != hipSuccess)
       return false;
-    if (rocsolver_zheevd(h->eigh, rocblas_evect_original, rocblas_fill_upper, m,
-                         static_cast<rocblas_double_complex*>(h->eig_a), m, static_cast<double*>(h->eig_w),
-                         static_cast<double*>(h->eig_e),
-                         static_cast<rocblas_int*>(h->eig_info)) != rocblas_status_success)
-      return false;
+    if (own) {
+      double2* t = static_cast<double2*>(h->eig_t);
+      if (bse::herm_tridiag(m, in, static_cast<double2*>(h->eig_v), static_cast<double*>(h->eig_w),
+                            static_cast<double*>(h->eig_e), t, t + m, h->stream) != hipSuccess)
+        return false;
+    }
+    if (!solve_tridiag(h, m)) return false;
     rocblas_int info = -1;
     if (hipMemcpyAsync(&info, h->eig_info, sizeof(info), hipMemcpyDeviceToHost, h->stream) != hipSuccess ||
         hipMemcpyAsync(w, h->eig_w, sizeof(double) * m, hipMemcpyDeviceToHost, h->stream) != hipSuccess ||
-        hipMemcpyAsync(z, h->eig_a, sizeof(double2) * (size_t)m * m, hipMemcpyDeviceToHost, h->stream) !=
+        hipMemcpyAsync(z, h->eig_z, sizeof(double2) * (size_t)m * m, hipMemcpyDeviceToHost, h->stream) !=
             hipSuccess ||
         hipStreamSynchronize(h->stream) != hipSuccess)
       return false;
     return info == 0;
   };
   if (m < 1) return true;
-  if (m > kHostEig && device()) return true;
+  if (m > kHostEig && bse::herm_tridiag && device()) return true;
   return bse::herm_eig(m, a, w, z);
 }
 
@@ -1940,7 +1966,7 @@ bse_status bse_destroy(bse_handle h) {
   if (h->stream) (void)hipStreamSynchronize(h->stream);
   void* ptrs[] = {h->a,         h->alo,   h->b,     h->blo,    h->part,     h->mhpart,
                   h->L.blkmap, h->X,     h->Y,     h->omega,  h->dcorr,    h->eig_a,
-                  h->eig_w,    h->eig_e, h->eig_info, h->eig_work};
+                  h->eig_w,    h->eig_e, h->eig_info, h->eig_work, h->eig_v, h->eig_z, h->eig_t};
   for (void* p : ptrs) dfree(h, p);
   if (h->eigh) (void)rocblas_destroy_handle(h->eigh);
   delete h;

@@ -151,3 +151,22 @@ def test_direct_orders(n):
     s = make_solver("ph", ap, bp)
     tgd.check_ph(s, ap, bp, max(1, n // 3))
     s.close()
+
+
+def test_projected_eigensolver_orders():
+    """Block full-H solves whose projected problems (order ncv, complex Hermitian) sit on both sides of
+    the host / device split (128) and around the 64-row workgroups of the device reduction: the same
+    pairs as the dense oracle."""
+    n, k = 300, 6
+    rng = np.random.default_rng(77)
+    A, B = random_herm(rng, n, lam_min=1.0), random_sym(rng, n, 0.5)
+    ap, bp = pack_upper(A), pack_upper(B)
+    ref, _, _ = oracle.ph(ap, bp, k, vectors=False)
+    s = make_solver("ph", ap, bp)
+    for ncv in [128, 130, 192, 194, 258]:
+        print(f"projected order {ncv}", flush=True)
+        om, x, y, st = s.solve(k, 1e-10, variant=3, ncv=ncv, block=2)
+        assert np.max(np.abs(host(om) - ref) / ref) < 1e-10
+        rel = oracle.residual_ph(ap, bp, host(om), host(x).T, host(y).T)
+        assert rel.max() <= 1.01e-10
+    s.close()
