@@ -297,9 +297,9 @@ __device__ inline double wave_sum64(double v) {
   return v;
 }
 
-// Skew-symmetric Householder reduction: two launches per column j (local panel
-// column t), bound by their latency, not by the reads (the trailing matrix is
-// 33 MB at order 2048).  A launch for each of the reflector, the product, the
+// Skew-symmetric Householder reduction while more than kSkewOne rows are left: two
+// launches per column j (local panel column t), bound by their latency, not by the
+// reads (the trailing matrix is 33 MB at order 2048).  A launch for each of the reflector, the product, the
 // corrections, p and the panel update, one row per thread with 256 columns in
 // sequence in the product, took 29 us per column at order 2048; 11.3 us now.
 //
@@ -308,14 +308,9 @@ __device__ inline double wave_sum64(double v) {
 // 13.3 us per column for both).
 constexpr int kSW = 16;
 
-// The reflector of column a = W[j+1:, j]: (I - tau v v^T) a = beta e_1, v_0 = 1,
-// v_i = a_i sc; every wave forms (beta, tau, sc) itself from the npn partial
-// sums of a_i^2, i > j + 1, that the launch before left in pn.
-__device__ inline void reflector(const double* __restrict__ pn, int npn, double alpha, int lane, double& beta,
-                                 double& tau, double& sc) {
-  double s = 0.0;
-  for (int q = lane; q < npn; q += 64) s += pn[q];
-  const double sig2 = wave_sum64(s);
+// The reflector of a column a, (I - tau v v^T) a = beta e_1, v_0 = 1, v_i = a_i sc,
+// from alpha = a_0 and the sum sig2 of the squares of the others.
+__device__ inline void reflector(double sig2, double alpha, double& beta, double& tau, double& sc) {
   if (sig2 == 0.0) {
     beta = alpha;
     tau = 0.0;
@@ -325,6 +320,13 @@ __device__ inline void reflector(const double* __restrict__ pn, int npn, double 
     tau = (beta - alpha) / beta;
     sc = 1.0 / (alpha - beta);
   }
+}
+// The same with sig2 as npn partial sums, by a wave.
+__device__ inline void reflector(const double* __restrict__ pn, int npn, double alpha, int lane, double& beta,
+                                 double& tau, double& sc) {
+  double s = 0.0;
+  for (int q = lane; q < npn; q += 64) s += pn[q];
+  reflector(wave_sum64(s), alpha, beta, tau, sc);
 }
 
 // pn[b] = sum of W[i, j]^2 over the block's rows i >= j + 2 (a panel's first column).
@@ -474,6 +476,132 @@ __global__ void __launch_bounds__(64 * kSW)
       nrm = wave_sum64(nrm);
       if (lane == 0) pn[blockIdx.x] = nrm;
     }
+  }
+}
+
+// Reduction of the last kSkewOne rows, one launch per column j.  The launch takes
+// the reflection pair (v, z = tau p) of column j - 1 (vo, po) to the rest of the
+// matrix, W += v z^T - z v^T, and forms p = W v of column j from the updated
+// entries while it has them: the matrix is read and written once per column and
+// nothing waits for a second launch.  Every workgroup applies the pair to column j
+// and forms the reflector of it for itself (column j is not written in this launch;
+// its v goes there in the next one).
+//
+// Bound by latency below some 1000 rows (4 us per column at order 512) and by the
+// traffic of reading and writing the matrix in the caches above: order 2048 14.9 ms
+// (7.3 us per column) against 23 ms in two launches with the updates blocked by 64
+// columns.  Those read the matrix and write it 64 times less often, which wins
+// above: order 3584 with the last 1536 / 2048 / 2560 / 3072 rows in this form 51.1 /
+// 49.7 / 51.2 / 53.9 ms.  Whole columns go to a wave, or shares of one, so that
+// loads are contiguous and the products end in one sum per column; few columns
+// per wave and small workgroups are the better the shorter the columns (order
+// 2048: 8 waves with 4 columns 14.9, 16 with 8 14.9, four columns per wave 15.5, 2
+// columns per workgroup 18 to 19 ms).
+constexpr int kSkewOne = 2048;
+constexpr int kCW = 8;  // waves of a workgroup
+constexpr int kSC = 4;  // columns of a workgroup
+constexpr int kSN = 2;  // columns of a wave, so that v and z are read from LDS once for both
+constexpr int kSB = 8;  // rows of a lane in flight
+
+// x + v_i z_c - z_i v_c with both products rounded: W stays exactly skew
+__device__ inline double skew_pair(double x, double vi, double zi, double vc, double zc) {
+#pragma clang fp contract(off)
+  const double a = vi * zc, b = zi * vc;
+  return x + (a - b);
+}
+
+__global__ void __launch_bounds__(64 * kCW)
+    skew_column_kernel(double* __restrict__ W, int64_t ld, int m, int j, const double* __restrict__ vo,
+                       const double* __restrict__ po, double* __restrict__ vn, double* __restrict__ pn,
+                       double* __restrict__ tau, double* __restrict__ e) {
+  constexpr int HW = kCW * kSN / kSC;  // waves that share a column
+  __shared__ double vs[kSkewOne], zs[kSkewOne], xs[kSkewOne];
+  __shared__ double red[kCW], dot[kSN][kCW];
+  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+  const int L = m - j;  // rows and columns from j on; r, c below count from j
+  const int c0 = 1 + blockIdx.x * kSC + wave / HW * kSN, r1 = 1 + wave % HW * 64;
+  double* const col = W + (size_t)(j + c0) * ld + j;
+  double w[kSB][kSN];
+  auto load = [&](int rb) {
+#pragma unroll
+    for (int u = 0; u < kSB; ++u)
+#pragma unroll
+      for (int q = 0; q < kSN; ++q) {
+        const int r = rb + u * 64 * HW + lane;
+        w[u][q] = r < L && c0 + q < L ? col[(size_t)q * ld + r] : 0.0;
+      }
+  };
+  load(r1);  // in flight while the reflector is formed
+  const double* cj = W + (size_t)j * ld + j;
+  const double tp = j > 0 ? tau[j - 1] : 0.0, zj = j > 0 ? tp * po[j] : 0.0;
+  double acc = 0.0;
+  for (int r = tid; r < L; r += 64 * kCW) {
+    double x = cj[r];
+    if (j > 0) {
+      const double v = vo[j + r], z = tp * po[j + r];
+      vs[r] = v;
+      zs[r] = z;
+      x = skew_pair(x, v, z, 1.0, zj);
+    }
+    xs[r] = x;
+    if (r >= 2) acc = fma(x, x, acc);
+  }
+  acc = wave_sum_dpp(acc);
+  if (lane == 0) red[wave] = acc;
+  __syncthreads();
+  double sig2 = red[0];
+#pragma unroll
+  for (int q = 1; q < kCW; ++q) sig2 += red[q];
+  double beta, tj, sc;
+  reflector(sig2, L > 1 ? xs[1] : 0.0, beta, tj, sc);
+  if (blockIdx.x == 0) {
+    if (j > 0)
+      for (int r = tid; r < L; r += 64 * kCW) W[(size_t)(j - 1) * ld + j + r] = vs[r];
+    for (int r = 1 + tid; r < L; r += 64 * kCW) vn[j + r] = r == 1 ? 1.0 : xs[r] * sc;
+    if (tid == 0 && L > 1) {
+      e[j] = beta;
+      tau[j] = tj;
+    }
+  }
+  double vc[kSN], zc[kSN], s[kSN];
+#pragma unroll
+  for (int q = 0; q < kSN; ++q) {
+    const bool in = j > 0 && c0 + q < L;
+    vc[q] = in ? vs[c0 + q] : 0.0;
+    zc[q] = in ? zs[c0 + q] : 0.0;
+    s[q] = 0.0;
+  }
+  for (int rb = r1; rb < L; rb += kSB * 64 * HW) {
+    if (rb != r1) load(rb);
+#pragma unroll
+    for (int u = 0; u < kSB; ++u) {
+      const int r = rb + u * 64 * HW + lane;
+      if (r >= L) continue;
+      const double x = r == 1 ? 1.0 : xs[r] * sc;
+      const double v = j > 0 ? vs[r] : 0.0, z = j > 0 ? zs[r] : 0.0;
+#pragma unroll
+      for (int q = 0; q < kSN; ++q) {
+        if (c0 + q >= L) continue;
+        double t = w[u][q];
+        if (j > 0) {
+          t = skew_pair(t, v, z, vc[q], zc[q]);
+          col[(size_t)q * ld + r] = t;
+        }
+        s[q] = fma(t, x, s[q]);
+      }
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < kSN; ++q) {
+    s[q] = wave_sum_dpp(s[q]);
+    if (lane == 0) dot[q][wave] = s[q];
+  }
+  __syncthreads();
+  if (tid < kSC) {  // column c of the workgroup: p_c = -(column c) . v
+    const int c = 1 + blockIdx.x * kSC + tid;
+    double t = 0.0;
+    for (int q = 0; q < HW; ++q) t += dot[tid % kSN][tid / kSN * HW + q];
+    if (c < L) pn[j + c] = -t;
   }
 }
 
@@ -654,11 +782,12 @@ hipError_t skew_tridiag(double* W, int64_t ld, int64_t m, double* Vp, double* Zp
   // behind the partial products: sc of the current reflector, the norm partials of the next one
   double* scp = part + (size_t)((m - 1 + 255) / 256) * m;
   double* pn = scp + 1;
-  for (int64_t j0 = 0; j0 + 1 < m; j0 += nb) {
-    const int tend = (int)(m - 1 - j0 < nb ? m - 1 - j0 : nb);
+  int64_t j0 = 0;
+  for (; m - j0 > kSkewOne; j0 += nb) {
+    const int tend = nb;
     const int64_t r0 = j0 + tend;
     int npn = (int)((m - j0 - 2 + 255) / 256);
-    if (npn > 0) hipLaunchKernelGGL(skew_norm_kernel, dim3((unsigned)npn), dim3(256), 0, s, W, ld, m, j0, pn);
+    hipLaunchKernelGGL(skew_norm_kernel, dim3((unsigned)npn), dim3(256), 0, s, W, ld, m, j0, pn);
     for (int t = 0; t < tend; ++t) {
       const int64_t j = j0 + t, L = m - j - 1;
       const int nrow = (int)((L + 63) / 64), nchunk = (int)((L + 255) / 256);
@@ -668,14 +797,22 @@ hipError_t skew_tridiag(double* W, int64_t ld, int64_t m, double* Vp, double* Zp
                          dots, tau, scp, Vp, Zp, ldp, pn);
       npn = nrow;
     }
+    // trailing W += Vp Zp^T - Zp Vp^T (rows and columns >= r0)
     const int64_t rest = m - r0;
-    if (rest > 0) {
-      // trailing W += Vp Zp^T - Zp Vp^T (rows and columns >= r0)
-      double* c = W + (size_t)r0 * ld + r0;
-      hipError_t err = dense_gemm(0, 1, rest, rest, tend, 1.0, Vp + r0, ldp, Zp + r0, ldp, 1.0, c, ld, 0, s);
-      if (err == hipSuccess) err = dense_gemm(0, 1, rest, rest, tend, -1.0, Zp + r0, ldp, Vp + r0, ldp, 1.0, c, ld, 0, s);
-      if (err != hipSuccess) return err;
-    }
+    double* c = W + (size_t)r0 * ld + r0;
+    hipError_t err = dense_gemm(0, 1, rest, rest, tend, 1.0, Vp + r0, ldp, Zp + r0, ldp, 1.0, c, ld, 0, s);
+    if (err == hipSuccess) err = dense_gemm(0, 1, rest, rest, tend, -1.0, Zp + r0, ldp, Vp + r0, ldp, 1.0, c, ld, 0, s);
+    if (err != hipSuccess) return err;
+  }
+  // the matrix that is left, which all pairs so far have been applied to; v and
+  // p of the last column and of this one in two columns of Vp and Zp in turn
+  double* Wr = W + (size_t)j0 * ld + j0;
+  const int mr = (int)(m - j0);
+  for (int j = 0; j < mr; ++j) {
+    const int L = mr - j - 1;
+    double *v0 = Vp + ((j + 1) & 1) * ldp, *p0 = Zp + ((j + 1) & 1) * ldp, *v1 = Vp + (j & 1) * ldp, *p1 = Zp + (j & 1) * ldp;
+    hipLaunchKernelGGL(skew_column_kernel, dim3((unsigned)(L > 0 ? (L + kSC - 1) / kSC : 1)), dim3(64 * kCW), 0, s, Wr,
+                       ld, mr, j, v0, p0, v1, p1, tau + j0, e + j0);
   }
   return hipGetLastError();
 }

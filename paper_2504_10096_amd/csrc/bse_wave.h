@@ -47,6 +47,15 @@ __device__ __forceinline__ double bank_pair_add(double a, double b) {
   const int yh = __builtin_amdgcn_update_dpp(__double2hiint(b), __double2hiint(a), 0x12c, 0xf, 0x5, false);
   return __hiloint2double(xh, xl) + __hiloint2double(yh, yl);
 }
+// Sum of one value over the wavefront, in every lane.
+__device__ __forceinline__ double wave_sum_dpp(double v) {
+  v += dpp_f64<0x128>(v);  // row_ror:8
+  v += dpp_f64<0x141>(v);  // row_half_mirror
+  v += dpp_f64<0xB1>(v);   // lane xor 1
+  v += dpp_f64<0x4E>(v);   // lane xor 2
+  v = swap16_add(v, v);
+  return swap32_add(v, v);
+}
 // Sums of N = 4, 8 or 16 values over the wavefront: every lane returns the sum
 // of value wave_sum_index<N>(lane).
 template <int N>

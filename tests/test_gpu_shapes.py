@@ -153,6 +153,20 @@ def test_direct_orders(n):
     s.close()
 
 
+# orders 2 n whose reduction changes its form at 2048 remaining rows: after one panel with 1986 and
+# with exactly 2048 left; tolerance as above
+@pytest.mark.parametrize("n", [1025, 1056])
+def test_direct_orders_two_forms(n):
+    import test_gpu_direct as tgd
+    print(f"direct orders, two forms n={n}", flush=True)
+    rng = np.random.default_rng(5000 + n)
+    A, B = random_herm(rng, n, lam_min=1.0), random_sym(rng, n, 0.5)
+    ap, bp = pack_upper(A), pack_upper(B)
+    s = make_solver("ph", ap, bp)
+    tgd.check_ph(s, ap, bp, 6)
+    s.close()
+
+
 def test_projected_eigensolver_orders():
     """Block full-H solves whose projected problems (order ncv, complex Hermitian) sit on both sides of
     the host / device split (128) and around the 64-row workgroups of the device reduction: the same
