@@ -5,6 +5,7 @@
 #include <stdint.h>
 
 #include "bse_internal.h"
+#include "bse_wave.h"
 
 namespace bse {
 namespace {
@@ -17,46 +18,88 @@ namespace {
 // and with p = A v, g = v^H A v, w = tau p - |tau|^2 g / 2 v the transformed
 // trailing matrix is A - v w^H - w v^H.
 //
-// A chain of m columns with two sums over the whole column each (the norm, g), so
-// two launches per column and nothing else: the time is their latency (the
-// matrix sits in the caches; order 224: 0.8 MB).  The library's blocked
-// reduction takes six launches per column: order 224 4.33 ms, 608 11.1 ms, against
-// 2.09 and 7.7 ms here.  A is kept in full, so products and updates read columns only.
-constexpr int kW = 16;  // waves per workgroup
-constexpr int kRows = 64;
+// A chain of m columns with two sums over the whole column each (the norm, g): the
+// time is latency (the matrix sits in the caches; order 224: 0.8 MB).  One launch
+// per column: it takes the pair (v, w) of column j - 1 to the rest of the matrix
+// and forms p = A v of column j from the updated entries while it has them.  Every
+// workgroup applies the pair to column j and forms its reflector for itself
+// (column j is not written in this launch).  A is kept in full, so that a wave reads
+// columns only.  Order 224 takes 1.07 ms, 608 3.5; in two launches per column (product,
+// then update) 2.09 and 7.7, by the library's blocked reduction with six 4.33 and
+// 11.1.  8 waves with 8 columns: 1.13 and 3.9 ms, two columns per wave 1.21 and 3.8.
+constexpr int kW = 8;  // waves of a workgroup
+constexpr int kC = 4;  // columns of a workgroup
+constexpr int kN = 1;  // columns of a wave
+constexpr int kB = 4;  // rows of a lane in flight
 
-__device__ inline double wsum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
 __device__ inline double2 cmul(double2 a, double2 b) {
   return make_double2(fma(a.x, b.x, -a.y * b.y), fma(a.x, b.y, a.y * b.x));
 }
 
-// pn[b] = sum of |A[i, 0]|^2 over the block's rows i >= 2.
-__global__ void __launch_bounds__(64) heig_norm_kernel(const double2* __restrict__ A, int m, double* __restrict__ pn) {
-  const int i = 2 + blockIdx.x * 64 + threadIdx.x;
-  const double2 a = i < m ? A[i] : make_double2(0.0, 0.0);
-  const double s = wsum(fma(a.x, a.x, a.y * a.y));
-  if (threadIdx.x == 0) pn[blockIdx.x] = s;
+// x - v_i w_c^* - w_i v_c^*
+__device__ inline double2 pair_sub(double2 x, double2 vi, double2 wi, double2 vc, double2 wc) {
+  x.x -= fma(vi.x, wc.x, vi.y * wc.y) + fma(wi.x, vc.x, wi.y * vc.y);
+  x.y -= fma(vi.y, wc.x, -vi.x * wc.y) + fma(wi.y, vc.x, -wi.x * vc.y);
+  return x;
 }
 
-// First launch of column j: 64 rows i > j per workgroup.  The reflector (every
-// wave forms it from the npn norm partials), its v in column j of V, p = A v and
-// the workgroup's share of g; workgroup 0 records d, e, tau.
+// Column j: po, go (ngo shares of g) of column j - 1, pn, gn those of column j.
 __global__ void __launch_bounds__(64 * kW)
-    heig_mv_kernel(const double2* __restrict__ A, int m, int j, const double* __restrict__ pn, int npn,
-                   double2* __restrict__ V, double2* __restrict__ p, double* __restrict__ gpart,
-                   double* __restrict__ d, double* __restrict__ e, double2* __restrict__ tau) {
-  extern __shared__ double2 vs[];  // v_c, c = j + 1 .. m - 1, then the waves' sums
-  __shared__ double2 red[kW][kRows];
+    heig_column_kernel(double2* __restrict__ A, int m, int j, double2* __restrict__ V, const double2* __restrict__ po,
+                       double2* __restrict__ pn, const double* __restrict__ go, int ngo, double* __restrict__ gn,
+                       double* __restrict__ d, double* __restrict__ e, double2* __restrict__ tau) {
+  constexpr int HW = kW * kN / kC;  // waves that share a column
+  __shared__ double2 vs[kHermTridiagMax], ws[kHermTridiagMax], xs[kHermTridiagMax];
+  __shared__ double red[kW];
+  __shared__ double2 dot[kN][kW];
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-  const double2* a = A + (size_t)j * m;
-  double s = 0.0;
-  for (int q = lane; q < npn; q += 64) s += pn[q];
-  const double sig2 = wsum(s);
-  const double2 al = a[j + 1];
+  const int L = m - j;  // rows and columns from j on; r, c below count from j
+  const int c0 = 1 + blockIdx.x * kC + wave / HW * kN, r1 = 1 + wave % HW * 64;
+  double2* const col = A + (size_t)(j + c0) * m + j;
+  double2 a[kB][kN];
+  auto load = [&](int rb) {
+#pragma unroll
+    for (int u = 0; u < kB; ++u)
+#pragma unroll
+      for (int q = 0; q < kN; ++q) {
+        const int r = rb + u * 64 * HW + lane;
+        a[u][q] = r < L && c0 + q < L ? col[(size_t)q * m + r] : make_double2(0.0, 0.0);
+      }
+  };
+  load(r1);  // in flight while the reflector is formed
+  const double2* cj = A + (size_t)j * m + j;
+  double2 tp = make_double2(0.0, 0.0), w0 = tp;
+  double h = 0.0;
+  if (j > 0) {
+    tp = tau[j - 1];
+    double s = 0.0;
+    for (int q = lane; q < ngo; q += 64) s += go[q];
+    h = 0.5 * fma(tp.x, tp.x, tp.y * tp.y) * wave_sum_dpp(s);
+    w0 = cmul(tp, po[j]);
+    w0.x -= h;  // v_0 = 1
+  }
+  double acc = 0.0;
+  for (int r = tid; r < L; r += 64 * kW) {
+    double2 x = cj[r];
+    if (j > 0) {
+      const double2 v = V[(size_t)(j - 1) * m + j + r];
+      double2 w = cmul(tp, po[j + r]);
+      w.x = fma(-h, v.x, w.x);
+      w.y = fma(-h, v.y, w.y);
+      vs[r] = v;
+      ws[r] = w;
+      x = pair_sub(x, v, w, make_double2(1.0, 0.0), w0);
+    }
+    xs[r] = x;
+    if (r >= 2) acc += fma(x.x, x.x, x.y * x.y);
+  }
+  acc = wave_sum_dpp(acc);
+  if (lane == 0) red[wave] = acc;
+  __syncthreads();
+  double sig2 = red[0];
+#pragma unroll
+  for (int q = 1; q < kW; ++q) sig2 += red[q];
+  const double2 al = L > 1 ? xs[1] : make_double2(0.0, 0.0);
   double beta = al.x;
   double2 tj = make_double2(0.0, 0.0), sc = tj;
   if (sig2 != 0.0 || al.y != 0.0) {
@@ -65,116 +108,71 @@ __global__ void __launch_bounds__(64 * kW)
     const double dr = al.x - beta, den = fma(dr, dr, al.y * al.y);  // 1 / (a_0 - beta)
     sc = make_double2(dr / den, -al.y / den);
   }
-  if (blockIdx.x == 0 && tid == 0) {
-    d[j] = a[j].x;
-    e[j] = beta;
-    tau[j] = tj;
-  }
-  const int L = m - j - 1;
-  for (int c = tid; c < L; c += 64 * kW) vs[c] = c == 0 ? make_double2(1.0, 0.0) : cmul(a[j + 1 + c], sc);
-  __syncthreads();
-  const int r = blockIdx.x * kRows + lane, i = j + 1 + r;
-  const bool in = r < L;
-  const int c0 = L * wave / kW, c1 = L * (wave + 1) / kW;
-  double sx = 0.0, sy = 0.0;
-  if (in) {
-    const double2* row = A + (size_t)(j + 1) * m + i;
-    int c = c0;
-    for (; c + 8 <= c1; c += 8) {
-      double2 w[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) w[u] = row[(size_t)(c + u) * m];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) {
-        const double2 v = vs[c + u];
-        sx = fma(w[u].x, v.x, fma(-w[u].y, v.y, sx));
-        sy = fma(w[u].x, v.y, fma(w[u].y, v.x, sy));
+  auto refl = [&](int r) { return r == 1 ? make_double2(1.0, 0.0) : cmul(xs[r], sc); };
+  if (blockIdx.x == 0) {
+    for (int r = 1 + tid; r < L; r += 64 * kW) V[(size_t)j * m + j + r] = refl(r);
+    if (tid == 0) {
+      d[j] = xs[0].x;
+      if (L > 1) {
+        e[j] = beta;
+        tau[j] = tj;
       }
     }
-    for (; c < c1; ++c) {
-      const double2 w = row[(size_t)c * m], v = vs[c];
-      sx = fma(w.x, v.x, fma(-w.y, v.y, sx));
-      sy = fma(w.x, v.y, fma(w.y, v.x, sy));
+  }
+  double2 vc[kN], wc[kN], s[kN];
+#pragma unroll
+  for (int q = 0; q < kN; ++q) {
+    const bool in = j > 0 && c0 + q < L;
+    vc[q] = in ? vs[c0 + q] : make_double2(0.0, 0.0);
+    wc[q] = in ? ws[c0 + q] : make_double2(0.0, 0.0);
+    s[q] = make_double2(0.0, 0.0);
+  }
+  for (int rb = r1; rb < L; rb += kB * 64 * HW) {
+    if (rb != r1) load(rb);
+#pragma unroll
+    for (int u = 0; u < kB; ++u) {
+      const int r = rb + u * 64 * HW + lane;
+      if (r >= L) continue;
+      const double2 x = refl(r);
+      const double2 v = j > 0 ? vs[r] : x, w = j > 0 ? ws[r] : x;
+#pragma unroll
+      for (int q = 0; q < kN; ++q) {
+        if (c0 + q >= L) continue;
+        double2 t = a[u][q];
+        if (j > 0) {
+          t = pair_sub(t, v, w, vc[q], wc[q]);
+          if (r == c0 + q) t.y = 0.0;
+          col[(size_t)q * m + r] = t;
+        }
+        s[q].x = fma(t.x, x.x, fma(t.y, x.y, s[q].x));  // t^* x
+        s[q].y = fma(t.x, x.y, fma(-t.y, x.x, s[q].y));
+      }
     }
   }
-  red[wave][lane] = make_double2(sx, sy);
+#pragma unroll
+  for (int q = 0; q < kN; ++q) {
+    s[q].x = wave_sum_dpp(s[q].x);
+    s[q].y = wave_sum_dpp(s[q].y);
+    if (lane == 0) dot[q][wave] = s[q];
+  }
   __syncthreads();
   if (wave != 0) return;
-  double2 t = red[0][lane];
-#pragma unroll
-  for (int w = 1; w < kW; ++w) {
-    t.x += red[w][lane].x;
-    t.y += red[w][lane].y;
-  }
   double g = 0.0;
-  if (in) {
-    const double2 v = vs[r];
-    V[(size_t)j * m + i] = v;
-    p[i] = t;
-    g = fma(v.x, t.x, v.y * t.y);  // Re conj(v) p
-  }
-  g = wsum(g);
-  if (lane == 0) gpart[blockIdx.x] = g;
-}
-
-// Second launch of column j: A -= v w^H + w v^H on 64 x 64 tiles of the trailing
-// matrix (wave w the columns w, w + 16, ...); the tiles of column j + 1 leave its
-// norm partials.
-__global__ void __launch_bounds__(64 * kW)
-    heig_update_kernel(double2* __restrict__ A, int m, int j, int nrow, const double2* __restrict__ V,
-                       const double2* __restrict__ p, const double* __restrict__ gpart,
-                       const double2* __restrict__ tau, double* __restrict__ pn) {
-  __shared__ double2 wc[kRows], vc[kRows];
-  const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
-  const double2 tj = tau[j];
-  double s = 0.0;
-  for (int q = lane; q < nrow; q += 64) s += gpart[q];
-  const double h = 0.5 * fma(tj.x, tj.x, tj.y * tj.y) * wsum(s);
-  const int L = m - j - 1;
-  const double2* v0 = V + (size_t)j * m + j + 1;
-  auto pair = [&](int r, double2& v, double2& w) {
-    v = w = make_double2(0.0, 0.0);
-    if (r < L) {
-      v = v0[r];
-      w = cmul(tj, p[j + 1 + r]);
-      w.x = fma(-h, v.x, w.x);
-      w.y = fma(-h, v.y, w.y);
-    }
-  };
-  const int r = blockIdx.x * kRows + lane, cb = blockIdx.y * kRows;
-  if (wave == 0) {
-    double2 v, w;
-    pair(cb + lane, v, w);
-    vc[lane] = v;
-    wc[lane] = w;
-  }
-  double2 v, w;
-  pair(r, v, w);
-  __syncthreads();
-  double nrm = 0.0;
-  if (r < L) {
+  const int c = 1 + blockIdx.x * kC + lane;
+  if (lane < kC && c < L) {
+    double2 t = dot[lane % kN][lane / kN * HW];
 #pragma unroll
-    for (int u = 0; u < kRows / kW; ++u) {
-      const int k = wave + kW * u, c = cb + k;
-      if (c >= L) break;
-      double2* q = A + (size_t)(j + 1 + c) * m + j + 1 + r;
-      const double2 vk = vc[k], wk = wc[k];
-      double2 x = *q;
-      x.x -= fma(v.x, wk.x, v.y * wk.y) + fma(w.x, vk.x, w.y * vk.y);
-      x.y -= fma(v.y, wk.x, -v.x * wk.y) + fma(w.y, vk.x, -w.x * vk.y);
-      if (c == r) x.y = 0.0;
-      *q = x;
-      if (c == 0 && r >= 2) nrm = fma(x.x, x.x, x.y * x.y);
+    for (int q = 1; q < HW; ++q) {
+      const double2 u = dot[lane % kN][lane / kN * HW + q];
+      t.x += u.x;
+      t.y += u.y;
     }
+    pn[j + c] = t;
+    const double2 v = refl(c);
+    g = fma(v.x, t.x, v.y * t.y);  // Re v^* p
   }
-  if (blockIdx.y == 0 && wave == 0) {
-    nrm = wsum(nrm);
-    if (lane == 0) pn[blockIdx.x] = nrm;
-  }
-}
-
-__global__ void heig_last_kernel(const double2* __restrict__ A, int m, double* __restrict__ d) {
-  d[m - 1] = A[(size_t)m * m - 1].x;
+  g = wave_sum_dpp(g);
+  if (lane == 0) gn[blockIdx.x] = g;
 }
 
 }  // namespace
@@ -182,20 +180,16 @@ __global__ void heig_last_kernel(const double2* __restrict__ A, int m, double* _
 hipError_t herm_tridiag(int m, double2* A, double2* V, double* d, double* e, double2* tau, double2* work,
                         hipStream_t s) {
   if (m < 2 || m > kHermTridiagMax) return hipErrorInvalidValue;
-  double2* p = work;
-  double* gpart = (double*)(work + m);  // m values, then the norm partials
-  double* pn = gpart + m;
-  int npn = (m - 2 + 63) / 64;
-  if (npn > 0) hipLaunchKernelGGL(heig_norm_kernel, dim3((unsigned)npn), dim3(64), 0, s, A, m, pn);
-  for (int j = 0; j + 1 < m; ++j) {
-    const int L = m - j - 1, nrow = (L + kRows - 1) / kRows;
-    hipLaunchKernelGGL(heig_mv_kernel, dim3((unsigned)nrow), dim3(64 * kW), sizeof(double2) * L, s, A, m, j, pn, npn,
-                       V, p, gpart, d, e, tau);
-    hipLaunchKernelGGL(heig_update_kernel, dim3((unsigned)nrow, (unsigned)nrow), dim3(64 * kW), 0, s, A, m, j, nrow,
-                       V, p, gpart, tau, pn);
-    npn = nrow;
+  // p and the shares of g, of the last column and of this one in turn
+  double2* p[2] = {work, work + m};
+  double* g[2] = {(double*)(work + 2 * (size_t)m), (double*)(work + 2 * (size_t)m) + m};
+  int ng = 0;
+  for (int j = 0; j < m; ++j) {
+    const int L = m - j - 1, nwg = L > 0 ? (L + kC - 1) / kC : 1;
+    hipLaunchKernelGGL(heig_column_kernel, dim3((unsigned)nwg), dim3(64 * kW), 0, s, A, m, j, V, p[(j + 1) & 1],
+                       p[j & 1], g[(j + 1) & 1], ng, g[j & 1], d, e, tau);
+    ng = nwg;
   }
-  hipLaunchKernelGGL(heig_last_kernel, dim3(1), dim3(1), 0, s, A, m, d);
   return hipGetLastError();
 }
 

@@ -215,7 +215,7 @@ void zlhsolve(int s, const double2* l, double2* x, int c);
 // column-major, leading dimension m, destroyed; 2 <= m <= kHermTridiagMax) to
 // real tridiagonal form, A = Q T Q^H (bse_heig.hip): d, e the diagonals of T,
 // Q = H_0 ... H_{m-2} with H_j = I - tau_j v_j v_j^H, v_j in rows j + 1 .. of
-// column j of V (one first).  work: 2 m complex entries.  Weak: a build of the
+// column j of V (one first).  work: 3 m complex entries.  Weak: a build of the
 // driver without device code has none and solves on the host.
 constexpr int kHermTridiagMax = 2048;
 __attribute__((weak)) hipError_t herm_tridiag(int m, double2* A, double2* V, double* d, double* e, double2* tau,

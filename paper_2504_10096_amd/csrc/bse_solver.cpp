@@ -119,10 +119,11 @@ bse_status fail(bse_handle h, bse_status s, const std::string& msg) {
 // dominate (ms, device with the library's reduction / host QR of
 // bse_smalleig.cpp with 16 / 4 / 1 threads, copies included: order 48 1.1 / 0.31 /
 // 0.35 / 0.29, 64 1.5 / 0.49 / 0.63 / 0.64, 96 2.1 / 0.96 / 1.4 / 2.0, 128 3.2 /
-// 1.8 / 2.6 / 4.5, 192 5.0 / 4.5 / 7.9 / 14).  With herm_tridiag order 144 takes
-// 2.4 ms (3.45 with the library's reduction), 224 4.0 (6.2), 608 12.5 (16.0); the
-// host takes 6.3 ms at order 224, 53 at 560.  Atomics are off in the rocBLAS calls, so repeated solves stay bitwise identical.  The buffers grow with the
-// largest order seen and stay with the handle.  Where rocBLAS cannot create
+// 1.8 / 2.6 / 4.5, 192 5.0 / 4.5 / 7.9 / 14).  With herm_tridiag order 224 takes
+// 3.0 ms (6.2 with the library's reduction, of which the reduction 1.1 and 4.3); the
+// host takes 6.3 ms at order 224, 53 at 560.  Atomics are off in the rocBLAS calls,
+// so repeated solves stay bitwise identical.  The buffers grow with the largest
+// order seen and stay with the handle.  Where rocBLAS cannot create
 // a handle (no device), or the call reports an error or no convergence, the
 // host QR solves the same problem.  Returns false only if that fails too.
 constexpr int kHostEig = 128;
@@ -172,7 +173,7 @@ bool herm_eig_proj(bse_handle h, int m, double2* a, double* w, double2* z) {
           dmalloc(h, &h->eig_info, sizeof(rocblas_int)) != hipSuccess ||
           dmalloc(h, &h->eig_v, sizeof(double2) * (size_t)m * m) != hipSuccess ||
           dmalloc(h, &h->eig_z, sizeof(double2) * (size_t)m * m) != hipSuccess ||
-          dmalloc(h, &h->eig_t, sizeof(double2) * 3 * (size_t)m) != hipSuccess)
+          dmalloc(h, &h->eig_t, sizeof(double2) * 4 * (size_t)m) != hipSuccess)
         return false;
       // rocSOLVER's workspace for this order, from the handle's memory
       size_t ws = 0;
