@@ -40,8 +40,7 @@ FP64_VALU_PEAK_TFLOPS = 78.6
 
 PMC_FILES = {"mv_stream_kernel<512, 3, 1>": "pmc_mv_stream_kernel_ph_n100000.txt",
              "mh_stream_kernel<512, 3, 2>": "pmc_mh_stream_kernel_x2_ph_n100000.txt",
-             "mh_stream_kernel<512, 3, 3>": "pmc_mh_stream_kernel_x3_ph_n100000.txt",
-             "mh_stream_kernel<512, 3, 4>": "pmc_mh_stream_kernel_x4_ph_n100000.txt"}
+             "mfma_pass_kernel<512, 3, 3, 2>": "pmc_mfma_pass_kernel_x4_ph_n100000.txt"}
 
 
 def counter_traffic(kernel_name):
@@ -481,8 +480,11 @@ def main():
     traffic = tb = None
     hblock = ph and args.variant == 3
     if hblock:
-        kernel_label = f"mh_stream_kernel ({kernel_dtype}, {st['block']} full-H vectors)"
+        on_mfma = st["block"] >= 3  # the matrix-core kernel; one instance for 3 and 4 vectors, counted for 4
+        kernel_label = f"{'mfma_pass' if on_mfma else 'mh_stream'}_kernel ({kernel_dtype}, {st['block']} full-H vectors)"
         counted = f"mh_stream_kernel<512, 3, {st['block']}>"
+        if on_mfma:
+            counted = "mfma_pass_kernel<512, 3, 3, 2>" if st["block"] == 4 else None
     elif st["block"] <= 1:
         kernel_label, counted = f"mv_stream_kernel ({kernel_dtype})", "mv_stream_kernel<512, 3, 1>"
     else:
