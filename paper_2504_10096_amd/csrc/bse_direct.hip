@@ -227,35 +227,44 @@ __global__ void __launch_bounds__(256)
     }
 }
 
-// Cholesky of the nb x nb (nb <= 64) diagonal block at (j0, j0), lower
-// triangle, in LDS; a pivot that is not positive (or NaN) sets *flag.
+// Cholesky of the diagonal block A11 (nb <= 64 columns from j0), lower triangle; a
+// pivot that is not positive (or NaN) sets *flag.  A chain of 64 columns, bound by the
+// latency of a pivot's root and quotients and of one barrier per column: lane r holds row r,
+// wave w the columns w, w + 4, ... in registers (a block of fewer columns is
+// filled up with the identity), and a finished column goes to the other waves
+// through LDS.  The block in LDS with three barriers per column and an index
+// division per entry took 83 us, 22 us here.
 __global__ void __launch_bounds__(256)
     potrf_diag_kernel(double* __restrict__ A, int64_t ld, int64_t j0, int nb, int* __restrict__ flag) {
-  __shared__ double S[64][65];  // S[c][r] = block (r, c)
-  const int t = threadIdx.x;
-  for (int e = t; e < nb * nb; e += 256) {
-    const int c = e / nb, r = e % nb;
-    S[c][r] = r >= c ? A[(size_t)(j0 + c) * ld + j0 + r] : 0.0;
+  __shared__ double L[2][64];
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), r = threadIdx.x & 63;
+  double a[16];
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    const int c = 4 * k + wave;
+    a[k] = r >= nb || c >= nb || r < c ? (r == c ? 1.0 : 0.0) : A[(size_t)(j0 + c) * ld + j0 + r];
   }
-  __syncthreads();
-  for (int c = 0; c < nb; ++c) {
-    const double piv = S[c][c];
-    __syncthreads();
-    if (t == 0 && !(piv > 0.0)) atomicExch(flag, 1);
-    const double d = sqrt(piv);
-    for (int r = c + 1 + t; r < nb; r += 256) S[c][r] /= d;
-    if (t == 0) S[c][c] = d;
-    __syncthreads();
-    const int w = nb - c - 1;
-    for (int e = t; e < w * w; e += 256) {
-      const int r = c + 1 + e % w, cc = c + 1 + e / w;
-      if (r >= cc) S[cc][r] -= S[c][r] * S[c][cc];
+#pragma unroll
+  for (int c = 0; c < 64; ++c) {
+    const int k0 = c >> 2;
+    if (wave == (c & 3)) {
+      const double piv = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(a[k0]), c),
+                                          __builtin_amdgcn_readlane(__double2loint(a[k0]), c));
+      if (r == 0 && !(piv > 0.0)) atomicExch(flag, 1);
+      const double d = sqrt(piv);
+      a[k0] = r > c ? a[k0] / d : d;  // rows above the diagonal are never read
+      L[c & 1][r] = a[k0];
     }
     __syncthreads();
+    const double lr = L[c & 1][r];
+#pragma unroll
+    for (int k = k0; k < 16; ++k)
+      if (k > k0 || wave > (c & 3)) a[k] = fma(-lr, L[c & 1][4 * k + wave], a[k]);
   }
-  for (int e = t; e < nb * nb; e += 256) {
-    const int c = e / nb, r = e % nb;
-    if (r >= c) A[(size_t)(j0 + c) * ld + j0 + r] = S[c][r];
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    const int c = 4 * k + wave;
+    if (r < nb && r >= c) A[(size_t)(j0 + c) * ld + j0 + r] = a[k];
   }
 }
 
