@@ -493,9 +493,13 @@ __global__ void __launch_bounds__(64 * W)
 // per stored block, lane = row, wave w the CPW columns [w CPW, (w + 1) CPW) of
 // the block.  MODE: T64_A rows A x, T64_K A x + sb B conj(x) through the real
 // 2 x 2 block of the entry pair (as in mk_block_kernel), T64_E A x + B y with
-// an explicit y, T64_H the full-H product of NV / 2 vectors in the sum /
-// difference basis: half-vector 2p is u = x + conj(y) and half-vector 2p + 1 is
-// -i w with w = x - conj(y), since K2 w = i K1 (-i w); both go through K1.
+// an explicit y, T64_H the full-H product of NV / 2 vectors [x; y]: output 2p is
+// A x + B y, output 2p + 1 the conjugate of the bottom, A conj(y) + B conj(x).
+// Both are summed from A and B themselves.  In the sum / difference basis of the
+// larger blocks (u = x + conj(y), w = x - conj(y), halves of K1 u +- K2 w) the
+// products are half as many, but each half is accurate only to eps (|A| + |B|)
+// (|x| + |y|): with y = 0, |A| = 13 and |B| = 0.25 the bottom B conj(x) had an
+// error of 3.8e-14 of its largest entry at N = 400, 2.3e-16 this way.
 //
 // What bounds it: below N = 1500 or so the latency of one block's loads and
 // column sums, above it the loads; with the column sums as one six-step
@@ -504,13 +508,16 @@ __global__ void __launch_bounds__(64 * W)
 // and 4 apart) each halve the number of registers instead of summing the same
 // value in every lane, so 16 values take 57 instructions.  All loads of a wave's
 // columns are issued before the first is used (8 columns ahead where A and B
-// take 32 bytes per entry pair, 4 with eight half-vectors, to fit the registers:
-// 95.9 against 107.9 us for four vectors of H in complex128 at N = 4096).
+// take 32 bytes per entry pair, 4 with eight half-vectors, to fit the registers;
+// held to two waves per SIMD there with 13 registers spilled, 104 -> 86 us for four
+// vectors of H in complex128 at N = 4096).
 // Eight waves of 8 columns instead of four of 16 gained 3 % at N <= 1024 and
 // lost up to 45 % above.  Times of a pass with its sum, before and after (us):
 //   N = 1024 complex128: A x 16.0 -> 6.5, H x four vectors 68 -> 16
 //   N = 4096 complex128: K1 64 -> 45 (268 MB), A x four 202 -> 40
-//   N = 4096 hi: K1 53 -> 27 (134 MB), H x four vectors 330 -> 67
+//   N = 4096 hi: K1 53 -> 27 (134 MB), H x four vectors 330 -> 77
+// (H: 67 in the sum / difference basis; 2001, complex128, three vectors 101 -> 30,
+// 28 there).
 enum { T64_A = 0, T64_K = 1, T64_E = 2, T64_H = 3 };
 
 template <int AR>
@@ -548,9 +555,7 @@ __device__ __forceinline__ double2 t64_input(const double2* __restrict__ V, int6
                                              int64_t i) {
   if (i >= n) return make_double2(0.0, 0.0);
   if constexpr (MODE == T64_H) {
-    const double2 x = V[(size_t)(q >> 1) * ldv + i], y = V[(size_t)(q >> 1) * ldv + ldh + i];
-    if (!(q & 1)) return make_double2(x.x + y.x, x.y - y.y);  // u
-    return make_double2(x.y + y.y, y.x - x.x);                // -i w
+    return V[(size_t)(q >> 1) * ldv + (q & 1 ? ldh : 0) + i];  // x, y
   } else {
     if (MODE == T64_E && q == 1) {
       const double2 y = vb[i];
@@ -565,7 +570,7 @@ __device__ __forceinline__ double2 t64_input(const double2* __restrict__ V, int6
 // q ldv.  Partials as in the streaming kernels: rowpart[o][blk][64],
 // colpart[o][blk][64], o = 0 .. NV - 1.
 template <int AR, int MODE, int NV>
-__global__ void __launch_bounds__(kThreads)
+__global__ void __launch_bounds__(kThreads, NV == 8 ? 2 : 1)
     tile64_kernel(const void* __restrict__ a0, const void* __restrict__ a1, const void* __restrict__ b0,
                   const void* __restrict__ b1, const int2* __restrict__ blkmap, int64_t nblk, int64_t n,
                   const double2* __restrict__ V, int64_t ldv, int64_t ldh, int conja,
@@ -614,14 +619,8 @@ __global__ void __launch_bounds__(kThreads)
 #pragma unroll
   for (int q = 0; q < NV; ++q) rr[q] = ri[q] = T(0);
   const T tsb = (T)sb;
-  // this lane's place among the 16 sums of a column group, and the component
-  // it stores (the odd half-vectors of T64_H hold K1 (-i w) = -i K2 w)
-  const int idx = wave_sum_index<16>(lane);
-  const int sq = (idx % VP) >> 1;
-  const bool swapped = MODE == T64_H && (sq & 1);
-  const int scomp = (idx & 1) ^ (swapped ? 1 : 0);
-  const double ssign = swapped && (idx & 1) ? -1.0 : 1.0;
-  double* cdst = csum[wave] + (idx / VP) * VP + 2 * sq + scomp;
+  // this lane's place among the 16 sums of a column group
+  double* cdst = csum[wave] + wave_sum_index<16>(lane);
   wave_lds_sync();
 
   double vals[16];
@@ -643,8 +642,46 @@ __global__ void __launch_bounds__(kThreads)
     }
 #pragma unroll
     for (int q = 0; q < NV; ++q) sr[q] = si[q] = T(0);
-    if constexpr (MODE == T64_K || MODE == T64_H) {
-      const T bs = MODE == T64_K ? tsb * br : br, bt = MODE == T64_K ? tsb * bi : bi;  // sb = 1 or -1
+    if constexpr (MODE == T64_H) {
+#pragma unroll
+      for (int q = 0; q < NV; q += 2) {
+        // row r: A_rc x_c + B_rc y_c, A_rc conj(y_c) + B_rc conj(x_c)
+        mac(rr[q], ar, xc[q]);
+        mac(rr[q], -ai, yc[q]);
+        mac(rr[q], br, xc[q + 1]);
+        mac(rr[q], -bi, yc[q + 1]);
+        mac(ri[q], ar, yc[q]);
+        mac(ri[q], ai, xc[q]);
+        mac(ri[q], br, yc[q + 1]);
+        mac(ri[q], bi, xc[q + 1]);
+        mac(rr[q + 1], ar, xc[q + 1]);
+        mac(rr[q + 1], ai, yc[q + 1]);
+        mac(rr[q + 1], br, xc[q]);
+        mac(rr[q + 1], bi, yc[q]);
+        mac(ri[q + 1], ai, xc[q + 1]);
+        mac(ri[q + 1], -ar, yc[q + 1]);
+        mac(ri[q + 1], bi, xc[q]);
+        mac(ri[q + 1], -br, yc[q]);
+        // column c: conj(A_rc) x_r + B_rc y_r, conj(A_rc) conj(y_r) + B_rc conj(x_r)
+        mac(sr[q], ar, xr[q]);
+        mac(sr[q], ai, xi[q]);
+        mac(sr[q], br, xr[q + 1]);
+        mac(sr[q], -bi, xi[q + 1]);
+        mac(si[q], ar, xi[q]);
+        mac(si[q], -ai, xr[q]);
+        mac(si[q], br, xi[q + 1]);
+        mac(si[q], bi, xr[q + 1]);
+        mac(sr[q + 1], ar, xr[q + 1]);
+        mac(sr[q + 1], -ai, xi[q + 1]);
+        mac(sr[q + 1], br, xr[q]);
+        mac(sr[q + 1], bi, xi[q]);
+        mac(si[q + 1], -ar, xi[q + 1]);
+        mac(si[q + 1], -ai, xr[q + 1]);
+        mac(si[q + 1], bi, xr[q]);
+        mac(si[q + 1], -br, xi[q]);
+      }
+    } else if constexpr (MODE == T64_K) {
+      const T bs = tsb * br, bt = tsb * bi;  // sb = 1 or -1
       const T kp = ar + bs, kq = ar - bs, ks = ai + bt, kt = bt - ai;
 #pragma unroll
       for (int q = 0; q < NV; ++q) {
@@ -688,8 +725,7 @@ __global__ void __launch_bounds__(kThreads)
       vals[(c % CG) * VP + j] = v;
     }
     if (c % CG == CG - 1) {
-      const double t = wave_sum_n<16>(vals);
-      cdst[(c - (CG - 1)) * VP] = ssign * t;  // the four lanes of a group store the same value
+      cdst[(c - (CG - 1)) * VP] = wave_sum_n<16>(vals);  // the four lanes of a group store the same value
     }
     // one column at a time: interleaved, the columns' entries and sums would
     // not fit the registers
@@ -707,11 +743,7 @@ __global__ void __launch_bounds__(kThreads)
 
   __syncthreads();
 #pragma unroll
-  for (int q = 0; q < NV; ++q) {
-    const double vx = (double)rr[q], vy = (double)ri[q];
-    lds[(wave * NV + q) * 64 + lane] =
-        (MODE == T64_H && (q & 1)) ? make_double2(-vy, vx) : make_double2(vx, vy);
-  }
+  for (int q = 0; q < NV; ++q) lds[(wave * NV + q) * 64 + lane] = make_double2((double)rr[q], (double)ri[q]);
   __syncthreads();
   for (int e = threadIdx.x; e < NV * 64; e += 64 * WAVES) {
     double2 t = lds[e];
@@ -1001,7 +1033,7 @@ __host__ __device__ constexpr int mh_rows(int nh) { return nh >= 3 ? 128 : 256; 
 // stored pair (a, b), the column (transposed) use as its transpose with the
 // conjugate of A.  The four sums are formed once per entry pair, so a vector
 // costs 16 FMAs per pair instead of the 32 of the four complex products.
-// Outputs 2q: K1 u_q, 2q+1: K2 w_q (mh_reduce_kernel, sd = 1, forms T and C).
+// Outputs 2q: K1 u_q, 2q+1: K2 w_q (mh_reduce_kernel, form 2, forms T and C).
 // One workgroup per block takes its R / mh_rows(NH) row slices in turn.
 // Row partials: rowpart[o][blk][R]; column partials: colpart[o][blk][R].
 template <int R, int AR, int NH>
@@ -1212,8 +1244,9 @@ __global__ void __launch_bounds__(kThreads)
 }
 
 // Multi-vector passes on FP64 matrix cores (R >= 128): NV <= 4 NG half-vectors
-// (MODE as in tile64_kernel: T64_A, T64_K, or T64_H with u and -i w = -i (x -
-// conj(y)) of NV / 2 full-H vectors, both through K1).
+// (MODE as in tile64_kernel: T64_A, T64_K, or T64_H in the sum / difference basis:
+// u = x + conj(y) and -i w = -i (x - conj(y)) of NV / 2 full-H vectors, both
+// through K1 since K2 w = i K1 (-i w)).
 //
 // What bounds it: with FMAs the four-vector full-H read on hi was bound by
 // their issue at two waves per SIMD (2.75 ms at N = 32768, where its 8.6 GB take
@@ -1514,23 +1547,24 @@ hipError_t launch_mfma(int nv, const Layout& L, const MatPtrs& m, const double2*
   return hipGetLastError();
 }
 
-// Sum of the partials of a multi-vector pass (sd == 0: output q to column q of
-// MV) or of a full-H product (sd != 0: outputs 2q, 2q+1 are K1 u_q and K2 w_q;
-// the workgroup of vector q sums both and writes the top (K1 u + K2 w) / 2 and
-// the conjugated bottom (K1 u - K2 w) / 2, the bottom times bsign: 1 for M v,
-// -1 for H v).  Grid (ceil(n / 64), vectors).
+// Sum of the partials of a multi-vector pass (form 0: output q to column q of
+// MV) or of a full-H product, where the workgroup of vector q sums outputs 2q and
+// 2q + 1 and writes the top and the conjugated bottom, the bottom times bsign: 1
+// for M v, -1 for H v.  Form 1 (block edge 64): the outputs are the two halves.
+// Form 2: they are K1 u_q and K2 w_q, top (K1 u + K2 w) / 2, conjugated bottom
+// (K1 u - K2 w) / 2.  Grid (ceil(n / 64), vectors).
 template <int W>
 __global__ void __launch_bounds__(64 * W)
     mh_reduce_kernel(const double2* __restrict__ rowpart, const double2* __restrict__ colpart, int R, int NS,
                      int nb, int64_t nblk, int64_t n, double2* __restrict__ MV, int64_t ldv, int64_t ldh,
                      double bsign, const double* __restrict__ dc, double dsg,
-                     const double2* __restrict__ X, int64_t ldx, int64_t ldhx, int sd) {
+                     const double2* __restrict__ X, int64_t ldx, int64_t ldhx, int form) {
   __shared__ double2 sh[W][64];
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int64_t i0 = (int64_t)blockIdx.x * 64, i = i0 + lane;
   const int P = (int)(i0 / R), r = (int)(i0 % R) + lane;
   const size_t rs = (size_t)nblk * R, cs = rs * NS;
-  if (sd) {
+  if (form) {
     const int q = blockIdx.y;
     double s1x = 0.0, s1y = 0.0, s2x = 0.0, s2y = 0.0;
     part_range<W>(rowpart + 2 * q * rs, colpart + 2 * q * cs, R, NS, nb, P, r, wave, s1x, s1y);
@@ -1538,8 +1572,14 @@ __global__ void __launch_bounds__(64 * W)
     const double2 k1 = wave_order_sum<W>(sh, wave, lane, s1x, s1y);
     const double2 k2 = wave_order_sum<W>(sh, wave, lane, s2x, s2y);
     if (wave != 0 || i >= n) return;
-    double tx = 0.5 * (k1.x + k2.x), ty = 0.5 * (k1.y + k2.y);  // top
-    double cx = 0.5 * (k1.x - k2.x), cy = 0.5 * (k1.y - k2.y);  // conjugated bottom
+    double tx = k1.x, ty = k1.y;  // top
+    double cx = k2.x, cy = k2.y;  // conjugated bottom
+    if (form == 2) {
+      tx = 0.5 * (k1.x + k2.x);
+      ty = 0.5 * (k1.y + k2.y);
+      cx = 0.5 * (k1.x - k2.x);
+      cy = 0.5 * (k1.y - k2.y);
+    }
     if (dc) {
       const double f = dsg * dc[i];
       const double2 x = X[(size_t)q * ldx + i];
@@ -1570,14 +1610,14 @@ __global__ void __launch_bounds__(64 * W)
 
 void launch_mh_reduce(const Layout& L, int ny, int ns, const double2* rowpart, const double2* colpart, double2* MV,
                       int64_t ldv, int64_t ldh, double bsign, const MatPtrs& m, const double2* X,
-                      int64_t ldx, int64_t ldhx, int sd, hipStream_t s) {
+                      int64_t ldx, int64_t ldhx, int form, hipStream_t s) {
   const dim3 grid((unsigned)((L.n + 63) / 64), (unsigned)ny);
   if (reduce_wide(L))
     hipLaunchKernelGGL(mh_reduce_kernel<16>, grid, dim3(1024), 0, s, rowpart, colpart, L.R, ns, L.nb, L.nblk, L.n,
-                       MV, ldv, ldh, bsign, m.dc, m.dsign, X, ldx, ldhx, sd);
+                       MV, ldv, ldh, bsign, m.dc, m.dsign, X, ldx, ldhx, form);
   else
     hipLaunchKernelGGL(mh_reduce_kernel<4>, grid, dim3(256), 0, s, rowpart, colpart, L.R, ns, L.nb, L.nblk, L.n, MV,
-                       ldv, ldh, bsign, m.dc, m.dsign, X, ldx, ldhx, sd);
+                       ldv, ldh, bsign, m.dc, m.dsign, X, ldx, ldhx, form);
 }
 
 template <int R, int AR>
@@ -2889,7 +2929,7 @@ hipError_t mh_apply(const Layout& L, Arith ar, const MatPtrs& m, int nh, const d
   }
   const double2* rowpart = part;
   const double2* colpart = part + (size_t)2 * nh * L.nblk * L.R;
-  launch_mh_reduce(L, nh, 1, rowpart, colpart, MV, ldv, ldh, bsign, m, V, ldv, ldh, 1, s);
+  launch_mh_reduce(L, nh, 1, rowpart, colpart, MV, ldv, ldh, bsign, m, V, ldv, ldh, L.R == 64 ? 1 : 2, s);
   return hipGetLastError();
 }
 

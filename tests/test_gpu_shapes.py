@@ -184,3 +184,34 @@ def test_projected_eigensolver_orders():
         rel = oracle.residual_ph(ap, bp, host(om), host(x).T, host(y).T)
         assert rel.max() <= 1.01e-10
     s.close()
+
+
+# products of full-H vectors on block edge 64: one block, a ragged edge, the two splits of the sums of the
+# partials, several vectors per read and a remainder
+@pytest.mark.parametrize("n", [1, 65, 400, 961, 2001])
+@pytest.mark.parametrize("storage", ["c128", "hilo"])
+def test_full_h_halves(n, storage):
+    """Each half of H [x; y] = [A x + B y; -(conj(B) x + conj(A) y)] against its own largest entry, where
+    the halves differ in size (eigenvectors have |y| << |x|, a lone excitation y = 0): a half that is
+    formed from A, B, x and y themselves is a sum of 4 N products, some eps sqrt(N) of the largest entry
+    (2001: 1e-14); a sum and difference of the halves would leave eps (|A| + |B|)(|x| + |y|) instead,
+    1e-11 of the smaller half here (|B| = 1e-3)."""
+    print(f"full-H halves n={n} storage={storage}", flush=True)
+    rng = np.random.default_rng(6000 + n)
+    A, B = random_herm(rng, n), random_sym(rng, n, 1e-3)
+    ap, bp = pack_upper(A), pack_upper(B)
+    ap32, bp32 = hi_operator(ap, bp)
+    s = make_solver("ph", ap, bp, storage)
+    for prec in ["fp64"] + (["hi64"] if storage == "hilo" else []):
+        pa, pb = (ap32, bp32) if prec == "hi64" else (ap, bp)
+        for fx, fy in [(1.0, 0.0), (1.0, 0.02), (0.0, 1.0), (1.0, 1.0)]:
+            for nvec in [1, 2, 3, 4, 5]:
+                x = rng.standard_normal((nvec, 2 * n)) + 1j * rng.standard_normal((nvec, 2 * n))
+                x[:, :n] *= fx
+                x[:, n:] *= fy
+                got = host(s.apply("H", dev(x), precision=prec))
+                ref = oracle.apply_dense("H", pa, x, pb)
+                for half in [slice(0, n), slice(n, 2 * n)]:
+                    err = np.max(np.abs(got[:, half] - ref[:, half])) / np.max(np.abs(ref[:, half]))
+                    assert err < 1e-14, (prec, fx, fy, nvec, half, err)
+    s.close()
