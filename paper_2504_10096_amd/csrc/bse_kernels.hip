@@ -1325,11 +1325,19 @@ __global__ void __launch_bounds__(64 * mfma_waves(R), 2)
   const int lane = threadIdx.x & 63;
   const int l0 = lane & 3, lb = (lane >> 2) & 3, l2 = lane >> 4;
   const int64_t row0 = (int64_t)pq.x * R + wave * RT, col0 = (int64_t)pq.y * R;
-  // half-vector q at index i; past the ends the last one (the stored entries
-  // there are zero, the outputs not written)
+  // half-vector q at index i; past the ends the last one (past nv the outputs are
+  // not written)
   auto input = [&](int q, int64_t i) -> double2 {
     return V[(size_t)(q < nv ? q : nv - 1) * ldv + (i < n ? i : n - 1)];
   };
+  // and zero past n: the stored entries there are zero, but zero times an infinite
+  // last entry is not.  Selected where it is used, so that the load stays in
+  // flight.  (H: staged with zeros over the padded length, nothing is past n)
+  auto inside = [&](bool in, double2 v) {
+    if constexpr (MODE == T64_H) return v;
+    return in ? v : make_double2(0.0, 0.0);
+  };
+  const int cleft = (int)(n - col0 < R ? n - col0 : R);  // columns of the block below n
 
   // row-side operands B[k = l2][j = l0] of block lb: row pair lb + 4 l2
   double xr[SUB][VW][NG], xi[SUB][VW][NG], dr[SUB][VW][NG], di[SUB][VW][NG];
@@ -1339,7 +1347,8 @@ __global__ void __launch_bounds__(64 * mfma_waves(R), 2)
     for (int e = 0; e < VW; ++e)
 #pragma unroll
       for (int g = 0; g < NG; ++g) {
-        const double2 x = input(4 * g + l0, row0 + s * 16 * VW + (lb + 4 * l2) * VW + e);
+        const int64_t i = row0 + s * 16 * VW + (lb + 4 * l2) * VW + e;
+        const double2 x = inside(i < n, input(4 * g + l0, i));
         xr[s][e][g] = x.x;
         xi[s][e][g] = x.y;
         dr[s][e][g] = 0.0;
@@ -1362,7 +1371,10 @@ __global__ void __launch_bounds__(64 * mfma_waves(R), 2)
       if constexpr (HASB) raw_load<AR>(b0, b1, lbase + (size_t)st * 4 * R + s * 16 * VW, rb[S][s]);
     }
 #pragma unroll
-    for (int g = 0; g < NG; ++g) xc[S][g] = input(4 * g + l0, col0 + st * 4 + l2);
+    for (int g = 0; g < NG; ++g) {
+      const int q = 4 * g + l0, c = st * 4 + l2;
+      xc[S][g] = (V + (size_t)(q < nv ? q : nv - 1) * ldv + col0)[c < cleft ? c : cleft - 1];
+    }
   };
   double2* const tw = &trn[wave][0][0][0];
   const int wr = (lane >> 4) * TLD + (lane & 15);  // this lane's place as written
@@ -1462,8 +1474,10 @@ __global__ void __launch_bounds__(64 * mfma_waves(R), 2)
     fetch(st + AHEAD < STEPS ? st + AHEAD : STEPS - 1, std::integral_constant<int, (S + AHEAD) % 4>());
     __builtin_amdgcn_sched_barrier(0);  // the loads stay ahead of their use
     double pr[NG], pi[NG];
+    double2 x[NG];  // the column-side operands of the step
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
+      x[g] = inside(st * 4 + l2 < cleft, xc[S][g]);
       pr[g] = cr[g];
       pi[g] = ci[g];
       cr[g] = ci[g] = 0.0;
@@ -1480,15 +1494,15 @@ __global__ void __launch_bounds__(64 * mfma_waves(R), 2)
       const Coef &c = rc[X], &t = tc[X];
 #pragma unroll
       for (int g = 0; g < NG; ++g) {
-        dr[s][e][g] = mfma4(c.kp, xc[S][g].x, dr[s][e][g]);
-        di[s][e][g] = mfma4(c.ks, xc[S][g].x, di[s][e][g]);
+        dr[s][e][g] = mfma4(c.kp, x[g].x, dr[s][e][g]);
+        di[s][e][g] = mfma4(c.ks, x[g].x, di[s][e][g]);
         cr[g] = mfma4(t.kp, xr[s][e][g], cr[g]);
         ci[g] = mfma4(t.kt, xr[s][e][g], ci[g]);
       }
 #pragma unroll
       for (int g = 0; g < NG; ++g) {
-        dr[s][e][g] = mfma4(c.kt, xc[S][g].y, dr[s][e][g]);
-        di[s][e][g] = mfma4(c.kq, xc[S][g].y, di[s][e][g]);
+        dr[s][e][g] = mfma4(c.kt, x[g].y, dr[s][e][g]);
+        di[s][e][g] = mfma4(c.kq, x[g].y, di[s][e][g]);
         cr[g] = mfma4(t.ks, xi[s][e][g], cr[g]);
         ci[g] = mfma4(t.kq, xi[s][e][g], ci[g]);
       }

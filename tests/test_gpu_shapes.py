@@ -215,3 +215,32 @@ def test_full_h_halves(n, storage):
                     err = np.max(np.abs(got[:, half] - ref[:, half])) / np.max(np.abs(ref[:, half]))
                     assert err < 1e-14, (prec, fx, fy, nvec, half, err)
     s.close()
+
+
+# four vectors per read on the larger block edges, N not a multiple of the edge
+@pytest.mark.parametrize("block,n", [(128, 300), (256, 300), (512, 600)])
+@pytest.mark.parametrize("storage", ["c128", "hilo"])
+def test_infinite_last_entry(block, n, storage, monkeypatch):
+    """An infinite last entry of one of four vectors: the rows of the earlier panels take it times their
+    entry of the last column and nothing else that is infinite (the padding past N enters as zero), the
+    other vectors stay finite."""
+    print(f"infinite last entry n={n} block={block} storage={storage}", flush=True)
+    rng = np.random.default_rng(7000 + n)
+    A, B = random_herm(rng, n), random_sym(rng, n, 0.5)
+    ap, bp = pack_upper(A), pack_upper(B)
+    ap32, bp32 = hi_operator(ap, bp)
+    s = make_solver("ph", ap, bp, storage, block, monkeypatch)
+    top = (n - 1) // block * block  # rows of the panels before the last one
+    for prec in ["fp64"] + (["hi64"] if storage == "hilo" else []):
+        pa, pb = (ap32, bp32) if prec == "hi64" else (ap, bp)
+        for op, sb in [("A", 0.0), ("K1", 1.0), ("K2", -1.0)]:
+            x = rng.standard_normal((4, n)) + 1j * rng.standard_normal((4, n))
+            ref = oracle.apply_dense(op, pa, x, pb)
+            x[1, n - 1] = np.inf
+            got = host(s.apply(op, dev(x), precision=prec))
+            k = A[:top, n - 1] + sb * B[:top, n - 1]
+            assert np.array_equal(got[1, :top].real, np.sign(k.real) * np.inf), (op, prec)
+            assert np.array_equal(got[1, :top].imag, np.sign(k.imag) * np.inf), (op, prec)
+            rest = [0, 2, 3]
+            assert np.max(np.abs(got[rest] - ref[rest])) < 1e-13 * np.max(np.abs(ref[rest])), (op, prec)
+    s.close()
