@@ -202,6 +202,10 @@ bool sym_eig(int m, double* a, double* w, double* z);
 // converge.
 bool herm_eig(int m, double2* a, double* w, double2* z);
 
+// The same on the device (m >= 2; blocks until the results are on the host).
+// Returns false where the device path cannot be set up or reports an error.
+bool herm_eig_device(bse_handle_s* h, int m, const double2* a, double* w, double2* z);
+
 // Host FP64 Cholesky and triangular solves for the projected pencil (s x s,
 // column-major complex): zchol overwrites the lower triangle of a Hermitian
 // positive definite a with L (a = L L^H; false if a pivot is not positive);

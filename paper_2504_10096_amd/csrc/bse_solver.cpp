@@ -60,7 +60,9 @@ struct bse_handle_s {
   // memory; eig_state -1: not available here, the host QR runs instead)
   rocblas_handle eigh = nullptr;
   int eig_state = 0;
-  int eig_cap = 0;  // largest order the buffers below hold
+  int eig_cap = 0;    // largest order the buffers below hold
+  int eig_order = 0;  // the order that the workspace eig_work was last asked for
+  size_t eig_ws = 0;  // its bytes
   void *eig_a = nullptr, *eig_w = nullptr, *eig_e = nullptr, *eig_info = nullptr, *eig_work = nullptr,
        *eig_v = nullptr, *eig_z = nullptr, *eig_t = nullptr;
 };
@@ -132,80 +134,103 @@ constexpr int kHostEig = 128;
 // the tridiagonal matrix in eig_w, eig_e and the back-transformation through the
 // reflectors in eig_v, eig_t into eig_z; above the orders of herm_tridiag the
 // whole problem, eig_a to eig_z (the same buffer there).
-bool solve_tridiag(bse_handle h, int m) {
+// query: the calls only report their workspace to the handle's size query (as
+// "size increased" or "unchanged", not as success), and every one has to.
+bool solve_tridiag(bse_handle h, int m, bool query = false) {
+  auto ok = [&](rocblas_status e) {
+    return query ? e == rocblas_status_size_increased || e == rocblas_status_size_unchanged
+                 : e == rocblas_status_success;
+  };
   auto* z = static_cast<rocblas_double_complex*>(h->eig_z);
   auto* w = static_cast<double*>(h->eig_w);
   auto* e = static_cast<double*>(h->eig_e);
   auto* info = static_cast<rocblas_int*>(h->eig_info);
   if (m > bse::kHermTridiagMax)
-    return rocsolver_zheevd(h->eigh, rocblas_evect_original, rocblas_fill_upper, m, z, m, w, e, info) ==
-           rocblas_status_success;
-  return rocsolver_zstedc(h->eigh, rocblas_evect_tridiagonal, m, w, e, z, m, info) == rocblas_status_success &&
-         rocsolver_zunmtr(h->eigh, rocblas_side_left, rocblas_fill_lower, rocblas_operation_none, m, m,
-                          static_cast<rocblas_double_complex*>(h->eig_v), m,
-                          static_cast<rocblas_double_complex*>(h->eig_t), z, m) == rocblas_status_success;
+    return ok(rocsolver_zheevd(h->eigh, rocblas_evect_original, rocblas_fill_upper, m, z, m, w, e, info));
+  return ok(rocsolver_zstedc(h->eigh, rocblas_evect_tridiagonal, m, w, e, z, m, info)) &&
+         ok(rocsolver_zunmtr(h->eigh, rocblas_side_left, rocblas_fill_lower, rocblas_operation_none, m, m,
+                             static_cast<rocblas_double_complex*>(h->eig_v), m,
+                             static_cast<rocblas_double_complex*>(h->eig_t), z, m));
 }
 
-bool herm_eig_proj(bse_handle h, int m, double2* a, double* w, double2* z) {
-  auto device = [&]() -> bool {
-    if (h->eig_state == 0) {
-      h->eig_state = -1;
-      if (rocblas_create_handle(&h->eigh) != rocblas_status_success) {
-        h->eigh = nullptr;
-        return false;
-      }
-      if (rocblas_set_stream(h->eigh, h->stream) != rocblas_status_success ||
-          rocblas_set_atomics_mode(h->eigh, rocblas_atomics_not_allowed) != rocblas_status_success)
-        return false;
-      h->eig_state = 1;
+}  // namespace
+
+namespace bse {
+
+bool herm_eig_device(bse_handle h, int m, const double2* a, double* w, double2* z) {
+  if (h->eig_state == 0) {
+    h->eig_state = -1;
+    if (rocblas_create_handle(&h->eigh) != rocblas_status_success) {
+      h->eigh = nullptr;
+      return false;
     }
-    if (h->eig_state != 1) return false;
-    if (m > h->eig_cap) {
-      for (void** p : {&h->eig_a, &h->eig_w, &h->eig_e, &h->eig_info, &h->eig_work, &h->eig_v, &h->eig_z,
-                       &h->eig_t}) {
-        dfree(h, *p);
-        *p = nullptr;
-      }
-      h->eig_cap = 0;
-      if (dmalloc(h, &h->eig_a, sizeof(double2) * (size_t)m * m) != hipSuccess ||
-          dmalloc(h, &h->eig_w, sizeof(double) * m) != hipSuccess ||
-          dmalloc(h, &h->eig_e, sizeof(double) * m) != hipSuccess ||
-          dmalloc(h, &h->eig_info, sizeof(rocblas_int)) != hipSuccess ||
-          dmalloc(h, &h->eig_v, sizeof(double2) * (size_t)m * m) != hipSuccess ||
-          dmalloc(h, &h->eig_z, sizeof(double2) * (size_t)m * m) != hipSuccess ||
-          dmalloc(h, &h->eig_t, sizeof(double2) * 4 * (size_t)m) != hipSuccess)
-        return false;
-      // rocSOLVER's workspace for this order, from the handle's memory
-      size_t ws = 0;
-      if (rocblas_start_device_memory_size_query(h->eigh) != rocblas_status_success) return false;
-      (void)solve_tridiag(h, m);
-      if (rocblas_stop_device_memory_size_query(h->eigh, &ws) != rocblas_status_success) return false;
+    if (rocblas_set_stream(h->eigh, h->stream) != rocblas_status_success ||
+        rocblas_set_atomics_mode(h->eigh, rocblas_atomics_not_allowed) != rocblas_status_success)
+      return false;
+    h->eig_state = 1;
+  }
+  if (h->eig_state != 1) return false;
+  if (m > h->eig_cap) {
+    for (void** p : {&h->eig_a, &h->eig_w, &h->eig_e, &h->eig_info, &h->eig_v, &h->eig_z, &h->eig_t}) {
+      dfree(h, *p);
+      *p = nullptr;
+    }
+    h->eig_cap = 0;
+    if (dmalloc(h, &h->eig_a, sizeof(double2) * (size_t)m * m) != hipSuccess ||
+        dmalloc(h, &h->eig_w, sizeof(double) * m) != hipSuccess ||
+        dmalloc(h, &h->eig_e, sizeof(double) * m) != hipSuccess ||
+        dmalloc(h, &h->eig_info, sizeof(rocblas_int)) != hipSuccess ||
+        dmalloc(h, &h->eig_v, sizeof(double2) * (size_t)m * m) != hipSuccess ||
+        dmalloc(h, &h->eig_z, sizeof(double2) * (size_t)m * m) != hipSuccess ||
+        dmalloc(h, &h->eig_t, sizeof(double2) * 4 * (size_t)m) != hipSuccess)
+      return false;
+    h->eig_cap = m;
+  }
+  if (m != h->eig_order) {
+    // rocSOLVER's workspace for this order (not a monotonic function of it), from
+    // the handle's memory
+    size_t ws = 0;
+    h->eig_order = 0;
+    if (rocblas_start_device_memory_size_query(h->eigh) != rocblas_status_success) return false;
+    const bool asked = solve_tridiag(h, m, true);
+    if (rocblas_stop_device_memory_size_query(h->eigh, &ws) != rocblas_status_success || !asked) return false;
+    if (ws > h->eig_ws || !h->eig_work) {
+      dfree(h, h->eig_work);
+      h->eig_work = nullptr;
       if (dmalloc(h, &h->eig_work, ws ? ws : 1) != hipSuccess) return false;
+      h->eig_ws = ws;
       if (rocblas_set_workspace(h->eigh, h->eig_work, ws) != rocblas_status_success) return false;
-      h->eig_cap = m;
     }
-    const bool own = m <= bse::kHermTridiagMax;
-    double2* in = static_cast<double2*>(own ? h->eig_a : h->eig_z);
-    if (hipMemcpyAsync(in, a, sizeof(double2) * (size_t)m * m, hipMemcpyHostToDevice, h->stream) != hipSuccess)
+    h->eig_order = m;
+  }
+  const bool own = m <= bse::kHermTridiagMax;
+  double2* in = static_cast<double2*>(own ? h->eig_a : h->eig_z);
+  if (hipMemcpyAsync(in, a, sizeof(double2) * (size_t)m * m, hipMemcpyHostToDevice, h->stream) != hipSuccess)
+    return false;
+  if (own) {
+    double2* t = static_cast<double2*>(h->eig_t);
+    if (bse::herm_tridiag(m, in, static_cast<double2*>(h->eig_v), static_cast<double*>(h->eig_w),
+                          static_cast<double*>(h->eig_e), t, t + m, h->stream) != hipSuccess)
       return false;
-    if (own) {
-      double2* t = static_cast<double2*>(h->eig_t);
-      if (bse::herm_tridiag(m, in, static_cast<double2*>(h->eig_v), static_cast<double*>(h->eig_w),
-                            static_cast<double*>(h->eig_e), t, t + m, h->stream) != hipSuccess)
-        return false;
-    }
-    if (!solve_tridiag(h, m)) return false;
-    rocblas_int info = -1;
-    if (hipMemcpyAsync(&info, h->eig_info, sizeof(info), hipMemcpyDeviceToHost, h->stream) != hipSuccess ||
-        hipMemcpyAsync(w, h->eig_w, sizeof(double) * m, hipMemcpyDeviceToHost, h->stream) != hipSuccess ||
-        hipMemcpyAsync(z, h->eig_z, sizeof(double2) * (size_t)m * m, hipMemcpyDeviceToHost, h->stream) !=
-            hipSuccess ||
-        hipStreamSynchronize(h->stream) != hipSuccess)
-      return false;
-    return info == 0;
-  };
+  }
+  if (!solve_tridiag(h, m)) return false;
+  rocblas_int info = -1;
+  if (hipMemcpyAsync(&info, h->eig_info, sizeof(info), hipMemcpyDeviceToHost, h->stream) != hipSuccess ||
+      hipMemcpyAsync(w, h->eig_w, sizeof(double) * m, hipMemcpyDeviceToHost, h->stream) != hipSuccess ||
+      hipMemcpyAsync(z, h->eig_z, sizeof(double2) * (size_t)m * m, hipMemcpyDeviceToHost, h->stream) !=
+          hipSuccess ||
+      hipStreamSynchronize(h->stream) != hipSuccess)
+    return false;
+  return info == 0;
+}
+
+}  // namespace bse
+
+namespace {
+
+bool herm_eig_proj(bse_handle h, int m, double2* a, double* w, double2* z) {
   if (m < 1) return true;
-  if (m > kHostEig && bse::herm_tridiag && device()) return true;
+  if (m > kHostEig && bse::herm_tridiag && bse::herm_eig_device(h, m, a, w, z)) return true;
   return bse::herm_eig(m, a, w, z);
 }
 

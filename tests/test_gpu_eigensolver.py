@@ -1,0 +1,77 @@
+"""The device solution of the projected complex Hermitian eigenproblems by itself (a solve falls back
+to the host QR if it fails, so the solver's results do not show which of the two ran).
+
+Tolerance: the Householder reduction, the divide and conquer and the back-transformation are backward
+stable, residual and loss of orthogonality within a modest multiple of m eps; m eps (of the largest
+eigenvalue for the residual) is asked for, floor 64 eps.
+"""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2504_10096_amd as bse
+
+pytestmark = pytest.mark.gpu
+
+EPS = np.finfo(np.float64).eps
+
+
+def device_eig(s, a):
+    """(w, z) of bse::herm_eig_device on the handle of s; fails if the device path did not run."""
+    f = bse.load_library()._ZN3bse15herm_eig_deviceEP12bse_handle_siPK15HIP_vector_typeIdLj2EEPdPS3_
+    f.argtypes = [ctypes.c_void_p, ctypes.c_int] + 3 * [ctypes.c_void_p]
+    f.restype = ctypes.c_bool
+    m = a.shape[0]
+    at = np.ascontiguousarray(a.T, dtype=np.complex128)  # column-major
+    w, zt = np.zeros(m), np.zeros((m, m), complex)
+    assert f(s._h, m, at.ctypes.data, w.ctypes.data, zt.ctypes.data)
+    return w, zt.T
+
+
+def check(a, w, z):
+    m = len(w)
+    tol = max(64, m) * EPS
+    assert np.all(np.diff(w) >= 0)
+    ad, zd = (torch.as_tensor(np.ascontiguousarray(v)).cuda() for v in (a, z))
+    wd = torch.as_tensor(w).cuda()
+    r = torch.linalg.vector_norm(ad @ zd - zd * wd, dim=0).max()
+    assert float(r) <= tol * np.abs(w).max()
+    g = zd.mH.contiguous() @ zd - torch.eye(m, device="cuda")
+    assert float(g.abs().max()) <= tol
+
+
+def herm(rng, m):
+    a = rng.standard_normal((m, m)) + 1j * rng.standard_normal((m, m))
+    return a + a.conj().T
+
+
+@pytest.fixture(scope="module")
+def handle():
+    s = bse.Solver("tda", 8)
+    yield s
+    s.close()
+
+
+# odd and even orders, one and several batches of 512 rows per lane of the reduction, its largest
+# order (2048) and the library's whole solution above; the buffers grow and are used again for less
+@pytest.mark.parametrize("m", [2, 3, 48, 129, 131, 257, 511, 512, 513, 514, 608, 1025, 2047, 2048, 2049, 130])
+def test_orders(handle, m):
+    print(f"device eigensolver order {m}", flush=True)
+    a = herm(np.random.default_rng(m), m)
+    w, z = device_eig(handle, a)
+    check(a, w, z)
+    if m <= 608:
+        ref = np.linalg.eigvalsh(a)
+        assert np.abs(w - ref).max() <= max(64, m) * EPS * np.abs(ref).max()
+
+
+# the reduction and the library's whole solution
+@pytest.mark.parametrize("m", [300, 2060])
+def test_repeats_are_bitwise_equal(handle, m):
+    print(f"device eigensolver repeats order {m}", flush=True)
+    a = herm(np.random.default_rng(9), m)
+    w0, z0 = device_eig(handle, a)
+    w1, z1 = device_eig(handle, a)
+    assert np.array_equal(w0, w1) and np.array_equal(z0, z1)
