@@ -14,7 +14,10 @@ namespace {
 // above row j + 1 and one there.  The reflector of a = A[j+1:, j] maps it to a
 // real multiple of the first unit vector (H_j^H a = beta e_1):
 //   beta = -sign(Re a_0) ||a||, tau = (beta - a_0)* / beta taken as
-//   ((beta - Re a_0) / beta, -Im a_0 / beta), v = a / (a_0 - beta),
+//   ((beta - Re a_0) / beta, -Im a_0 / beta), v = a / (a_0 - beta)
+// (a zero column has v = e_1, tau = 2: tau is never 0, not even where nothing is
+// to be reduced: the library's blocked back-transformation divides by it and
+// returns NaN),
 // and with p = A v, g = v^H A v, w = tau p - |tau|^2 g / 2 v the transformed
 // trailing matrix is A - v w^H - w v^H.
 //
@@ -100,10 +103,11 @@ __global__ void __launch_bounds__(64 * kW)
 #pragma unroll
   for (int q = 1; q < kW; ++q) sig2 += red[q];
   const double2 al = L > 1 ? xs[1] : make_double2(0.0, 0.0);
-  double beta = al.x;
-  double2 tj = make_double2(0.0, 0.0), sc = tj;
-  if (sig2 != 0.0 || al.y != 0.0) {
-    beta = -copysign(sqrt(fma(al.x, al.x, fma(al.y, al.y, sig2))), al.x);
+  double beta = -al.x;
+  double2 tj = make_double2(2.0, 0.0), sc = make_double2(0.0, 0.0);
+  const double nrm2 = fma(al.x, al.x, fma(al.y, al.y, sig2));
+  if (nrm2 != 0.0) {
+    beta = -copysign(sqrt(nrm2), al.x);
     tj = make_double2((beta - al.x) / beta, -al.y / beta);
     const double dr = al.x - beta, den = fma(dr, dr, al.y * al.y);  // 1 / (a_0 - beta)
     sc = make_double2(dr / den, -al.y / den);

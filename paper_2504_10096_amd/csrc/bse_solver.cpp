@@ -221,6 +221,10 @@ bool herm_eig_device(bse_handle h, int m, const double2* a, double* w, double2* 
           hipSuccess ||
       hipStreamSynchronize(h->stream) != hipSuccess)
     return false;
+  // the library's own reduction leaves tau = 0 where nothing is to be reduced, of
+  // which its blocked back-transformation makes NaN in every vector
+  for (int i = 0; !own && i < m; ++i)
+    if (!std::isfinite(z[i].x) || !std::isfinite(z[i].y)) return false;
   return info == 0;
 }
 

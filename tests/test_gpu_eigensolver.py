@@ -20,14 +20,20 @@ EPS = np.finfo(np.float64).eps
 
 def device_eig(s, a):
     """(w, z) of bse::herm_eig_device on the handle of s; fails if the device path did not run."""
+    ok, w, z = call(s, a)
+    assert ok
+    return w, z
+
+
+def call(s, a):
     f = bse.load_library()._ZN3bse15herm_eig_deviceEP12bse_handle_siPK15HIP_vector_typeIdLj2EEPdPS3_
     f.argtypes = [ctypes.c_void_p, ctypes.c_int] + 3 * [ctypes.c_void_p]
     f.restype = ctypes.c_bool
     m = a.shape[0]
     at = np.ascontiguousarray(a.T, dtype=np.complex128)  # column-major
     w, zt = np.zeros(m), np.zeros((m, m), complex)
-    assert f(s._h, m, at.ctypes.data, w.ctypes.data, zt.ctypes.data)
-    return w, zt.T
+    ok = f(s._h, m, at.ctypes.data, w.ctypes.data, zt.ctypes.data)
+    return ok, w, zt.T
 
 
 def check(a, w, z):
@@ -65,6 +71,35 @@ def test_orders(handle, m):
     if m <= 608:
         ref = np.linalg.eigvalsh(a)
         assert np.abs(w - ref).max() <= max(64, m) * EPS * np.abs(ref).max()
+
+
+@pytest.mark.parametrize("kind,m", [("diagonal", 150), ("real", 150), ("degenerate", 150), ("blocks", 150),
+                                    ("arrowhead", 150), ("diagonal", 2048)])
+def test_structures(handle, kind, m):
+    """Columns with nothing to reduce, repeated eigenvalues, and the restart's own shape."""
+    print(f"device eigensolver {kind} order {m}", flush=True)
+    rng = np.random.default_rng(3)
+    a = herm(rng, m)
+    if kind == "diagonal":
+        a = np.diag(np.diag(a).real).astype(complex)
+    elif kind == "real":
+        a = a.real.astype(complex)
+    elif kind == "degenerate":
+        q, _ = np.linalg.qr(a)
+        a = (q * np.repeat([1.0, 2.0, 3.0], m // 3)) @ q.conj().T
+        a = 0.5 * (a + a.conj().T)
+    elif kind == "blocks":
+        a[70:, :70] = 0.0
+        a[:70, 70:] = 0.0
+    else:  # diagonal, one full row and column, tridiagonal after it
+        b = np.diag(np.diag(a).real).astype(complex)
+        b[60, :61] = a[60, :61]
+        b[:61, 60] = a[:61, 60]
+        for i in range(60, m - 1):
+            b[i + 1, i], b[i, i + 1] = a[i + 1, i], a[i, i + 1]
+        a = b
+    w, z = device_eig(handle, a)
+    check(a, w, z)
 
 
 # the reduction and the library's whole solution
