@@ -15,9 +15,9 @@ namespace {
 // real multiple of the first unit vector (H_j^H a = beta e_1):
 //   beta = -sign(Re a_0) ||a||, tau = (beta - a_0)* / beta taken as
 //   ((beta - Re a_0) / beta, -Im a_0 / beta), v = a / (a_0 - beta)
-// (a zero column has v = e_1, tau = 2: tau is never 0, not even where nothing is
-// to be reduced: the library's blocked back-transformation divides by it and
-// returns NaN),
+// (a column whose squares may underflow counts as zero and has v = e_1, tau = 2:
+// kEigTiny.  tau is never 0, not even where nothing is to be reduced: the
+// library's blocked back-transformation divides by it and returns NaN),
 // and with p = A v, g = v^H A v, w = tau p - |tau|^2 g / 2 v the transformed
 // trailing matrix is A - v w^H - w v^H.
 //
@@ -106,7 +106,7 @@ __global__ void __launch_bounds__(64 * kW)
   double beta = -al.x;
   double2 tj = make_double2(2.0, 0.0), sc = make_double2(0.0, 0.0);
   const double nrm2 = fma(al.x, al.x, fma(al.y, al.y, sig2));
-  if (nrm2 != 0.0) {
+  if (nrm2 >= kEigTiny) {
     beta = -copysign(sqrt(nrm2), al.x);
     tj = make_double2((beta - al.x) / beta, -al.y / beta);
     const double dr = al.x - beta, den = fma(dr, dr, al.y * al.y);  // 1 / (a_0 - beta)

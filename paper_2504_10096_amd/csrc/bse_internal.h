@@ -206,6 +206,15 @@ bool herm_eig(int m, double2* a, double* w, double2* z);
 // Returns false where the device path cannot be set up or reports an error.
 bool herm_eig_device(bse_handle_s* h, int m, const double2* a, double* w, double2* z);
 
+// Both eigensolvers square the entries of a column.  Exponent e such that the
+// entries times 2^-e have squares within range (0 if the entries themselves have:
+// the largest between 2^-100 and 2^100), and the least squared norm of a column
+// that is reduced: below it the squares may underflow, which would leave a
+// reflector that is not unitary, and the column counts as zero (its entries are
+// below 2^-360 of the largest).
+int eig_exponent(size_t n, const double2* a);
+constexpr double kEigTiny = 0x1p-920;
+
 // Host FP64 Cholesky and triangular solves for the projected pencil (s x s,
 // column-major complex): zchol overwrites the lower triangle of a Hermitian
 // positive definite a with L (a = L L^H; false if a pivot is not positive);

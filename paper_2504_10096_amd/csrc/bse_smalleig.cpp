@@ -271,8 +271,8 @@ void herm_tridiagonalize(int m, cplx* a, double* d, cplx* e, cplx* q) {
   for (int k = 0; k + 2 < m; ++k) {
     double xn = 0.0;
     for (int i = k + 1; i < m; ++i) xn += std::norm(A(i, k));
+    if (xn < kEigTiny) continue;
     xn = sqrt(xn);
-    if (xn == 0.0) continue;
     const cplx x0 = A(k + 1, k);
     const double ax0 = std::abs(x0);
     const cplx ph = ax0 > 0.0 ? x0 / ax0 : cplx(1.0, 0.0);
@@ -347,10 +347,26 @@ bool tridiag_qr(int m, double* d, double* e, std::vector<Rot>& rots) {
 
 }  // namespace
 
+int eig_exponent(size_t n, const double2* a) {
+  const double* v = reinterpret_cast<const double*>(a);
+  double mx[8] = {};
+  size_t t = 0;
+  for (; t + 8 <= 2 * n; t += 8)
+    for (int q = 0; q < 8; ++q) mx[q] = fabs(v[t + q]) > mx[q] ? fabs(v[t + q]) : mx[q];
+  for (; t < 2 * n; ++t) mx[0] = std::max(mx[0], fabs(v[t]));
+  const double top = *std::max_element(mx, mx + 8);
+  if (top == 0.0 || (top > 0x1p-100 && top < 0x1p100)) return 0;
+  int e = 0;
+  (void)frexp(top, &e);
+  return std::max(e, -1000);  // (2^1000 still a number)
+}
+
 bool herm_eig(int m, double2* a, double* w, double2* z) {
   if (m <= 0) return true;
   std::vector<cplx> ac((size_t)m * m), qh((size_t)m * m);
-  for (size_t t = 0; t < (size_t)m * m; ++t) ac[t] = cplx(a[t].x, a[t].y);
+  const int ex = eig_exponent((size_t)m * m, a);
+  const double sc = ldexp(1.0, -ex);
+  for (size_t t = 0; t < (size_t)m * m; ++t) ac[t] = cplx(sc * a[t].x, sc * a[t].y);
   std::vector<double> d(m), e(m, 0.0);
   std::vector<cplx> ec(m, 0.0);
   if (m == 1) {
@@ -376,7 +392,7 @@ bool herm_eig(int m, double2* a, double* w, double2* z) {
   std::iota(ord.begin(), ord.end(), 0);
   std::stable_sort(ord.begin(), ord.end(), [&](int x, int y) { return d[x] < d[y]; });
   for (int c = 0; c < m; ++c) {
-    w[c] = d[ord[c]];
+    w[c] = ldexp(d[ord[c]], ex);
     const cplx* zc = &qh[(size_t)ord[c] * m];
     for (int i = 0; i < m; ++i) z[(size_t)c * m + i] = make_double2(zc[i].real(), zc[i].imag());
   }

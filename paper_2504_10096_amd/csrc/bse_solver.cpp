@@ -203,6 +203,17 @@ bool herm_eig_device(bse_handle h, int m, const double2* a, double* w, double2* 
     }
     h->eig_order = m;
   }
+  const int ex = eig_exponent((size_t)m * m, a);
+  std::vector<double2> scaled;
+  if (ex != 0) {
+    const double f = ldexp(1.0, -ex);
+    scaled.assign(a, a + (size_t)m * m);
+    for (double2& v : scaled) {
+      v.x *= f;
+      v.y *= f;
+    }
+    a = scaled.data();
+  }
   const bool own = m <= bse::kHermTridiagMax;
   double2* in = static_cast<double2*>(own ? h->eig_a : h->eig_z);
   if (hipMemcpyAsync(in, a, sizeof(double2) * (size_t)m * m, hipMemcpyHostToDevice, h->stream) != hipSuccess)
@@ -225,6 +236,7 @@ bool herm_eig_device(bse_handle h, int m, const double2* a, double* w, double2* 
   // which its blocked back-transformation makes NaN in every vector
   for (int i = 0; !own && i < m; ++i)
     if (!std::isfinite(z[i].x) || !std::isfinite(z[i].y)) return false;
+  for (int c = 0; ex != 0 && c < m; ++c) w[c] = ldexp(w[c], ex);
   return info == 0;
 }
 

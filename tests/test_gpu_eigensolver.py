@@ -102,6 +102,31 @@ def test_structures(handle, kind, m):
     check(a, w, z)
 
 
+@pytest.mark.parametrize("scale", [1e-300, 1e-158, 1.0, 1e153, 1e300])
+@pytest.mark.parametrize("col", [1.0, 1e-155, 1e-160, 1e-165, 1e-165j])
+def test_range(handle, scale, col):
+    """Squares of a column that under- or overflow: no quotient of zeros (col 1e-165j) and no
+    reflector that is not unitary (1e-160)."""
+    print(f"device eigensolver scale {scale} column {col}", flush=True)
+    m = 150
+    a = herm(np.random.default_rng(5), m)
+    a[1:, 0] *= col
+    a[0, 1:] = a[1:, 0].conj()
+    w, z = device_eig(handle, scale * a)
+    check(a, w / scale, z)
+
+
+def test_library_solution_of_a_diagonal_matrix(handle):
+    """Above order 2048 the whole solution is the library's: right, or refused (the host QR solves it
+    then), never vectors that are not numbers."""
+    m = 2060
+    print(f"device eigensolver diagonal order {m}", flush=True)
+    a = np.diag(np.random.default_rng(8).standard_normal(m)).astype(complex)
+    ok, w, z = call(handle, a)
+    if ok:
+        check(a, w, z)
+
+
 # the reduction and the library's whole solution
 @pytest.mark.parametrize("m", [300, 2060])
 def test_repeats_are_bitwise_equal(handle, m):

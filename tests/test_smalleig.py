@@ -151,3 +151,23 @@ def test_tridiag0_lowest_positive(driver, m, k, clustered):
     assert np.abs(w - ref).max() <= 1e-13 * scale
     assert np.abs(z.T @ z - np.eye(k)).max() <= 1e-10
     assert np.abs(S @ z - z * w).max() <= 1e-11 * scale
+
+
+@pytest.mark.parametrize("scale", [1e-300, 1e-170, 1e-158, 1e-140, 1.0, 1e153, 1e300])
+@pytest.mark.parametrize("col", [1.0, 1e-155, 1e-160, 1e-165])
+def test_herm_eig_range(driver, scale, col):
+    """Matrices, and columns of a matrix, whose squares under- or overflow: a reflector formed from
+    such squares is not unitary (column 1e-160: vectors orthonormal to 1e-6 only)."""
+    m = 48
+    rng = np.random.default_rng(11)
+    a = rng.standard_normal((m, m)) + 1j * rng.standard_normal((m, m))
+    a = a + a.conj().T
+    a[1:, 0] *= col
+    a[0, 1:] *= col
+    w, z = run(driver, "h", scale * a)
+    ref = np.linalg.eigvalsh(a)
+    top = np.abs(ref).max()
+    assert np.all(np.diff(w) >= 0)
+    assert np.abs(w / scale - ref).max() <= 1e-13 * top
+    assert np.abs(z.conj().T @ z - np.eye(m)).max() <= 1e-13
+    assert np.abs(a @ z - z * (w / scale)).max() <= 1e-12 * top
