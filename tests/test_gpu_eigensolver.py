@@ -135,3 +135,33 @@ def test_repeats_are_bitwise_equal(handle, m):
     w0, z0 = device_eig(handle, a)
     w1, z1 = device_eig(handle, a)
     assert np.array_equal(w0, w1) and np.array_equal(z0, z1)
+
+
+def pack(a):
+    return np.concatenate([a[: j + 1, j] for j in range(len(a))]).astype(np.complex128)
+
+
+# orders around the block of the library's back-transformation and the host / device split, and above
+# the device reduction
+@pytest.mark.parametrize("kind,n", [("real", 66), ("real", 129), ("real", 300), ("diagonal", 66), ("diagonal", 300),
+                                    ("diagonal", 2060)])
+def test_direct_tda_without_imaginary_parts(kind, n):
+    """The dense TDA solve of real and of diagonal blocks, of which the library's whole solution makes
+    vectors that are not numbers."""
+    print(f"direct tda {kind} n={n}", flush=True)
+    rng = np.random.default_rng(n)
+    a = np.diag(rng.uniform(1.0, 5.0, n))
+    if kind == "real":
+        g = rng.standard_normal((n, n))
+        a = a + 0.05 * (g + g.T)
+    k = 5
+    s = bse.Solver("tda", n)
+    s.set_packed("A", torch.as_tensor(pack(a)).cuda())
+    om, x, _, st = s.direct(k)
+    s.close()
+    om, x = om.cpu().numpy(), x.cpu().numpy().T
+    ref = np.linalg.eigvalsh(a)
+    tol = max(64, n) * EPS * np.abs(ref).max()
+    assert np.abs(om - ref[:k]).max() <= tol
+    assert np.linalg.norm(a @ x - x * om, axis=0).max() <= tol
+    assert np.abs(x.conj().T @ x - np.eye(k)).max() <= max(64, n) * EPS
