@@ -202,6 +202,10 @@ bool sym_eig(int m, double* a, double* w, double* z);
 // converge.
 bool herm_eig(int m, double2* a, double* w, double2* z);
 
+// Threads of the host eigensolvers: OMP_NUM_THREADS if set, else the hardware
+// count, at most 16.
+int host_threads();
+
 // The same on the device (m >= 2; blocks until the results are on the host).
 // Returns false where the device path cannot be set up or reports an error.
 bool herm_eig_device(bse_handle_s* h, int m, const double2* a, double* w, double2* z);

@@ -35,6 +35,12 @@
 
 namespace bse {
 
+int host_threads() {
+  int nt = (int)std::thread::hardware_concurrency();
+  if (const char* e = getenv("OMP_NUM_THREADS")) nt = atoi(e);
+  return std::max(1, std::min(nt, 16));
+}
+
 namespace {
 
 inline double& at(double* a, int m, int i, int j) { return a[(size_t)j * m + i]; }
@@ -43,8 +49,7 @@ inline double& at(double* a, int m, int i, int j) { return a[(size_t)j * m + i];
 // chunks of [0, n) and returns when all are done.  Between regions a worker
 // spins for a while (the reduction issues one region per column, a few
 // microseconds apart) and then sleeps on a condition variable.  The pool
-// lives until the process ends.  Threads: OMP_NUM_THREADS if set, else the
-// hardware count, at most 16.
+// lives until the process ends.
 class Pool {
  public:
   using Fn = std::function<void(int64_t, int64_t)>;
@@ -86,10 +91,7 @@ class Pool {
   }
 
  private:
-  Pool() : pid_(getpid()) {
-    int nt = (int)std::thread::hardware_concurrency();
-    if (const char* e = getenv("OMP_NUM_THREADS")) nt = atoi(e);
-    nthreads_ = std::max(1, std::min(nt, 16));
+  Pool() : pid_(getpid()), nthreads_(host_threads()) {
     for (int t = 1; t < nthreads_; ++t) std::thread([this] { loop(); }).detach();
   }
   void work() {
@@ -117,7 +119,7 @@ class Pool {
     }
   }
   pid_t pid_;
-  int nthreads_ = 1;
+  const int nthreads_;
   std::mutex run_m_, m_;
   std::condition_variable cv_;
   const Fn* job_ = nullptr;
