@@ -18,7 +18,9 @@
 #include <algorithm>
 #include <chrono>
 #include <complex>
+#include <initializer_list>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include <rocblas/rocblas.h>
@@ -60,7 +62,8 @@ struct bse_handle_s {
   // memory; eig_state -1: not available here, the host QR runs instead)
   rocblas_handle eigh = nullptr;
   int eig_state = 0;
-  int eig_cap = 0;    // largest order the buffers below hold
+  int eig_cap = 0;    // largest order the buffers z, w, e below hold,
+  int eig_own = 0;    // and a, v, t (the own reduction's)
   int eig_order = 0;  // the order that the workspace eig_work was last asked for
   size_t eig_ws = 0;  // its bytes
   void *eig_a = nullptr, *eig_w = nullptr, *eig_e = nullptr, *eig_info = nullptr, *eig_work = nullptr,
@@ -175,22 +178,30 @@ bool herm_eig_device(bse_handle h, int m, const double2* a, double* w, double2* 
     h->eig_state = 1;
   }
   if (h->eig_state != 1) return false;
-  if (m > h->eig_cap) {
-    for (void** p : {&h->eig_a, &h->eig_w, &h->eig_e, &h->eig_info, &h->eig_v, &h->eig_z, &h->eig_t}) {
-      dfree(h, *p);
-      *p = nullptr;
+  const bool own = m <= bse::kHermTridiagMax;
+  auto grow = [&](int& cap, std::initializer_list<std::pair<void**, size_t>> bufs) {
+    if (m <= cap) return true;
+    cap = 0;
+    for (auto& b : bufs) {
+      dfree(h, *b.first);
+      *b.first = nullptr;
     }
-    h->eig_cap = 0;
-    if (dmalloc(h, &h->eig_a, sizeof(double2) * (size_t)m * m) != hipSuccess ||
-        dmalloc(h, &h->eig_w, sizeof(double) * m) != hipSuccess ||
-        dmalloc(h, &h->eig_e, sizeof(double) * m) != hipSuccess ||
-        dmalloc(h, &h->eig_info, sizeof(rocblas_int)) != hipSuccess ||
-        dmalloc(h, &h->eig_v, sizeof(double2) * (size_t)m * m) != hipSuccess ||
-        dmalloc(h, &h->eig_z, sizeof(double2) * (size_t)m * m) != hipSuccess ||
-        dmalloc(h, &h->eig_t, sizeof(double2) * 4 * (size_t)m) != hipSuccess)
-      return false;
-    h->eig_cap = m;
-  }
+    for (auto& b : bufs)
+      if (dmalloc(h, b.first, b.second) != hipSuccess) {
+        *b.first = nullptr;
+        return false;
+      }
+    cap = m;
+    return true;
+  };
+  const size_t sq = sizeof(double2) * (size_t)m * m;
+  if (!grow(h->eig_cap, {{&h->eig_z, sq},
+                         {&h->eig_w, sizeof(double) * m},
+                         {&h->eig_e, sizeof(double) * m},
+                         {&h->eig_info, sizeof(rocblas_int)}}))
+    return false;
+  if (own && !grow(h->eig_own, {{&h->eig_a, sq}, {&h->eig_v, sq}, {&h->eig_t, sizeof(double2) * 4 * (size_t)m}}))
+    return false;
   if (m != h->eig_order) {
     // rocSOLVER's workspace for this order (not a monotonic function of it), from
     // the handle's memory
@@ -219,7 +230,6 @@ bool herm_eig_device(bse_handle h, int m, const double2* a, double* w, double2* 
     }
     a = scaled.data();
   }
-  const bool own = m <= bse::kHermTridiagMax;
   double2* in = static_cast<double2*>(own ? h->eig_a : h->eig_z);
   if (hipMemcpyAsync(in, a, sizeof(double2) * (size_t)m * m, hipMemcpyHostToDevice, h->stream) != hipSuccess)
     return false;

@@ -137,6 +137,21 @@ def test_repeats_are_bitwise_equal(handle, m):
     assert np.array_equal(w0, w1) and np.array_equal(z0, z1)
 
 
+def test_no_buffers_of_the_reduction_above_its_orders():
+    """The two m x m buffers of the own reduction come with the first order that it takes."""
+    print("device eigensolver buffers", flush=True)
+    a = np.diag(np.arange(1.0, 2061.0)).astype(complex)
+    s = bse.Solver("tda", 8, allocator="torch")
+    call(s, a)
+    before = torch.cuda.memory_allocated()
+    assert call(s, a[:2048, :2048])[0]
+    assert torch.cuda.memory_allocated() - before >= 2 * 16 * 2048 ** 2
+    before = torch.cuda.memory_allocated()
+    assert call(s, a[:300, :300])[0]
+    assert torch.cuda.memory_allocated() == before
+    s.close()
+
+
 def pack(a):
     return np.concatenate([a[: j + 1, j] for j in range(len(a))]).astype(np.complex128)
 
