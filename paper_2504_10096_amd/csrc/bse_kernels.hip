@@ -1373,7 +1373,10 @@ __global__ void __launch_bounds__(64 * mfma_waves(R), 2)
 #pragma unroll
     for (int g = 0; g < NG; ++g) {
       const int q = 4 * g + l0, c = st * 4 + l2;
-      xc[S][g] = (V + (size_t)(q < nv ? q : nv - 1) * ldv + col0)[c < cleft ? c : cleft - 1];
+      if constexpr (MODE == T64_H)
+        xc[S][g] = input(q, col0 + c);
+      else
+        xc[S][g] = (V + (size_t)(q < nv ? q : nv - 1) * ldv + col0)[c < cleft ? c : cleft - 1];
     }
   };
   double2* const tw = &trn[wave][0][0][0];
