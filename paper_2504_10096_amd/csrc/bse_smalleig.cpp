@@ -36,9 +36,11 @@
 namespace bse {
 
 int host_threads() {
-  int nt = (int)std::thread::hardware_concurrency();
-  if (const char* e = getenv("OMP_NUM_THREADS")) nt = atoi(e);
-  return std::max(1, std::min(nt, 16));
+  static const int nt = [] {  // (asking the system takes some tens of microseconds)
+    const char* e = getenv("OMP_NUM_THREADS");
+    return std::max(1, std::min(e ? atoi(e) : (int)std::thread::hardware_concurrency(), 16));
+  }();
+  return nt;
 }
 
 namespace {
