@@ -67,6 +67,29 @@ def counter_traffic(kernel_name):
     return float(fields["traffic_bytes_per_launch"])
 
 
+def block_edge(n):
+    """Edge of the stored blocks (choose_block of bse_kernels.hip, and its override)."""
+    env = os.environ.get("BSE_BLOCK_EDGE", "")
+    if env in ("64", "128", "256", "512"):
+        return int(env)
+    return next((r for r in (512, 256, 128) if -(-n // r) * (-(-n // r) + 1) // 2 >= 1024), 64)
+
+
+def pass_kernel(edge, dtype, op, nv):
+    """Name of the kernel that reads the triangles (launch_mv, launch_mh and launch_mk of
+    bse_kernels.hip): dtype 'c64' (hi triangles, FP64 arithmetic), 'hi+lo' or 'c128', op 'A', 'K' or
+    'H' (the fused full-H product), nv vectors."""
+    if edge == 64:
+        return "tile64_kernel"
+    if op == "H":
+        return "mfma_pass_kernel" if nv >= 3 and (edge >= 256 or dtype == "c64") else "mh_stream_kernel"
+    if nv == 1:
+        return "mv_stream_kernel"
+    if nv >= 4 and (edge >= 256 or dtype == "c128" or (dtype == "c64" and op == "A")):
+        return "mfma_pass_kernel"
+    return "mk_block_kernel"
+
+
 def log(*a):
     print(*a, file=sys.stderr, flush=True)
 
@@ -479,16 +502,14 @@ def main():
     # over the same launch duration; null unless this run's dominant kernel is the one counted
     traffic = tb = None
     hblock = ph and args.variant == 3
-    if hblock:
-        on_mfma = st["block"] >= 3  # the matrix-core kernel; one instance for 3 and 4 vectors, counted for 4
-        kernel_label = f"{'mfma_pass' if on_mfma else 'mh_stream'}_kernel ({kernel_dtype}, {st['block']} full-H vectors)"
-        counted = f"mh_stream_kernel<512, 3, {st['block']}>"
-        if on_mfma:
-            counted = "mfma_pass_kernel<512, 3, 3, 2>" if st["block"] == 4 else None
-    elif st["block"] <= 1:
-        kernel_label, counted = f"mv_stream_kernel ({kernel_dtype})", "mv_stream_kernel<512, 3, 1>"
-    else:
-        kernel_label, counted = f"mk_block_kernel ({kernel_dtype}, {st['block']} vectors)", None
+    nv = max(1, st["block"])
+    kernel = pass_kernel(block_edge(n), kernel_dtype, "H" if hblock else "K" if ph else "A", nv)
+    kernel_label = f"{kernel} ({kernel_dtype}" + (f", {nv} {'full-H ' if hblock else ''}vectors)"
+                                                  if hblock or nv > 1 else ")")
+    # the instances whose traffic was counted (the matrix-core kernel's for four vectors)
+    counted = {("mh_stream_kernel", 2): "mh_stream_kernel<512, 3, 2>",
+               ("mfma_pass_kernel", 4): "mfma_pass_kernel<512, 3, 3, 2>" if hblock else None,
+               ("mv_stream_kernel", 1): "mv_stream_kernel<512, 3, 1>"}.get((kernel, nv))
     if ph and storage == "hilo" and precision == "mixed" and counted and ms_launch > 0 and n == 100000:
         tb = counter_traffic(counted)
         traffic = tb / (ms_launch * 1e-3) / 1e9 if tb else None
