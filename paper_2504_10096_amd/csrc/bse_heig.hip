@@ -32,7 +32,6 @@ namespace {
 // 11.1.  8 waves with 8 columns: 1.13 and 3.9 ms, two columns per wave 1.21 and 3.8.
 constexpr int kW = 8;  // waves of a workgroup
 constexpr int kC = 4;  // columns of a workgroup
-constexpr int kN = 1;  // columns of a wave
 constexpr int kB = 4;  // rows of a lane in flight
 
 __device__ inline double2 cmul(double2 a, double2 b) {
@@ -51,23 +50,21 @@ __global__ void __launch_bounds__(64 * kW)
     heig_column_kernel(double2* __restrict__ A, int m, int j, double2* __restrict__ V, const double2* __restrict__ po,
                        double2* __restrict__ pn, const double* __restrict__ go, int ngo, double* __restrict__ gn,
                        double* __restrict__ d, double* __restrict__ e, double2* __restrict__ tau) {
-  constexpr int HW = kW * kN / kC;  // waves that share a column
+  constexpr int HW = kW / kC;  // waves that share a column
   __shared__ double2 vs[kHermTridiagMax], ws[kHermTridiagMax], xs[kHermTridiagMax];
   __shared__ double red[kW];
-  __shared__ double2 dot[kN][kW];
+  __shared__ double2 dot[kW];
   const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
   const int L = m - j;  // rows and columns from j on; r, c below count from j
-  const int c0 = 1 + blockIdx.x * kC + wave / HW * kN, r1 = 1 + wave % HW * 64;
+  const int c0 = 1 + blockIdx.x * kC + wave / HW, r1 = 1 + wave % HW * 64;
   double2* const col = A + (size_t)(j + c0) * m + j;
-  double2 a[kB][kN];
+  double2 a[kB];
   auto load = [&](int rb) {
 #pragma unroll
-    for (int u = 0; u < kB; ++u)
-#pragma unroll
-      for (int q = 0; q < kN; ++q) {
-        const int r = rb + u * 64 * HW + lane;
-        a[u][q] = r < L && c0 + q < L ? col[(size_t)q * m + r] : make_double2(0.0, 0.0);
-      }
+    for (int u = 0; u < kB; ++u) {
+      const int r = rb + u * 64 * HW + lane;
+      a[u] = r < L && c0 < L ? col[r] : make_double2(0.0, 0.0);
+    }
   };
   load(r1);  // in flight while the reflector is formed
   const double2* cj = A + (size_t)j * m + j;
@@ -123,51 +120,38 @@ __global__ void __launch_bounds__(64 * kW)
       }
     }
   }
-  double2 vc[kN], wc[kN], s[kN];
-#pragma unroll
-  for (int q = 0; q < kN; ++q) {
-    const bool in = j > 0 && c0 + q < L;
-    vc[q] = in ? vs[c0 + q] : make_double2(0.0, 0.0);
-    wc[q] = in ? ws[c0 + q] : make_double2(0.0, 0.0);
-    s[q] = make_double2(0.0, 0.0);
-  }
+  const bool in = j > 0 && c0 < L;
+  const double2 vc = in ? vs[c0] : make_double2(0.0, 0.0), wc = in ? ws[c0] : make_double2(0.0, 0.0);
+  double2 s = make_double2(0.0, 0.0);
   for (int rb = r1; rb < L; rb += kB * 64 * HW) {
     if (rb != r1) load(rb);
 #pragma unroll
     for (int u = 0; u < kB; ++u) {
       const int r = rb + u * 64 * HW + lane;
-      if (r >= L) continue;
+      if (r >= L || c0 >= L) continue;
       const double2 x = refl(r);
-      const double2 v = j > 0 ? vs[r] : x, w = j > 0 ? ws[r] : x;
-#pragma unroll
-      for (int q = 0; q < kN; ++q) {
-        if (c0 + q >= L) continue;
-        double2 t = a[u][q];
-        if (j > 0) {
-          t = pair_sub(t, v, w, vc[q], wc[q]);
-          if (r == c0 + q) t.y = 0.0;
-          col[(size_t)q * m + r] = t;
-        }
-        s[q].x = fma(t.x, x.x, fma(t.y, x.y, s[q].x));  // t^* x
-        s[q].y = fma(t.x, x.y, fma(-t.y, x.x, s[q].y));
+      double2 t = a[u];
+      if (j > 0) {
+        t = pair_sub(t, vs[r], ws[r], vc, wc);
+        if (r == c0) t.y = 0.0;
+        col[r] = t;
       }
+      s.x = fma(t.x, x.x, fma(t.y, x.y, s.x));  // t^* x
+      s.y = fma(t.x, x.y, fma(-t.y, x.x, s.y));
     }
   }
-#pragma unroll
-  for (int q = 0; q < kN; ++q) {
-    s[q].x = wave_sum_dpp(s[q].x);
-    s[q].y = wave_sum_dpp(s[q].y);
-    if (lane == 0) dot[q][wave] = s[q];
-  }
+  s.x = wave_sum_dpp(s.x);
+  s.y = wave_sum_dpp(s.y);
+  if (lane == 0) dot[wave] = s;
   __syncthreads();
   if (wave != 0) return;
   double g = 0.0;
   const int c = 1 + blockIdx.x * kC + lane;
   if (lane < kC && c < L) {
-    double2 t = dot[lane % kN][lane / kN * HW];
+    double2 t = dot[lane * HW];
 #pragma unroll
     for (int q = 1; q < HW; ++q) {
-      const double2 u = dot[lane % kN][lane / kN * HW + q];
+      const double2 u = dot[lane * HW + q];
       t.x += u.x;
       t.y += u.y;
     }

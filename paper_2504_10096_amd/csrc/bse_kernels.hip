@@ -489,7 +489,7 @@ __global__ void __launch_bounds__(64 * W)
 
 // ------------------------------------------- small matrices: 64 x 64 blocks
 //
-// Every product of a pass on block edge 64 (N below about 5800): one workgroup
+// Every product of a pass on block edge 64 (N up to 5632): one workgroup
 // per stored block, lane = row, wave w the CPW columns [w CPW, (w + 1) CPW) of
 // the block.  MODE: T64_A rows A x, T64_K A x + sb B conj(x) through the real
 // 2 x 2 block of the entry pair (as in mk_block_kernel), T64_E A x + B y with
@@ -1521,8 +1521,7 @@ __global__ void __launch_bounds__(64 * mfma_waves(R), 2)
     if (st > 0 && st % SPC == 0) chunk_out(st / SPC - 1);
   };
   fetch(0, std::integral_constant<int, 0>());
-  if constexpr (AHEAD >= 2) fetch(1, std::integral_constant<int, 1>());
-  if constexpr (AHEAD >= 3) fetch(2, std::integral_constant<int, 2>());
+  if constexpr (AHEAD == 2) fetch(1, std::integral_constant<int, 1>());
   exchange(std::integral_constant<int, 0>(), std::integral_constant<int, 0>(), std::integral_constant<int, 0>());
   for (int st = 0; st < STEPS; st += 4) {
     step(st, std::integral_constant<int, 0>());
@@ -1555,12 +1554,9 @@ hipError_t launch_mfma(int nv, const Layout& L, const MatPtrs& m, const double2*
   double2* rowpart = part;
   double2* colpart = part + (size_t)nv * L.nblk * R;
   const dim3 grid((unsigned)L.nblk), wg(64 * mfma_waves(R));
-  if (nv <= 4)
-    hipLaunchKernelGGL((mfma_pass_kernel<R, AR, MODE, 1>), grid, wg, 0, s, m.a, m.alo, m.b, m.blo, L.blkmap, L.nblk,
-                       nx, V, ldv, nv, sb, rowpart, colpart);
-  else if constexpr (MODE == T64_H)
-    hipLaunchKernelGGL((mfma_pass_kernel<R, AR, MODE, 2>), grid, wg, 0, s, m.a, m.alo, m.b, m.blo, L.blkmap, L.nblk,
-                       nx, V, ldv, nv, sb, rowpart, colpart);
+  constexpr int NG = MODE == T64_H ? 2 : 1;  // six or eight half-vectors, else four vectors
+  hipLaunchKernelGGL((mfma_pass_kernel<R, AR, MODE, NG>), grid, wg, 0, s, m.a, m.alo, m.b, m.blo, L.blkmap, L.nblk,
+                     nx, V, ldv, nv, sb, rowpart, colpart);
   return hipGetLastError();
 }
 
@@ -1651,7 +1647,9 @@ hipError_t launch_mh(int nh, const Layout& L, const MatPtrs& m, const double2* V
     const bool mfma = mh_on_mfma(R, AR, nh);
     hipLaunchKernelGGL(hsd_stage_kernel, dim3((unsigned)((pl + kThreads - 1) / kThreads), (unsigned)nh),
                        dim3(kThreads), 0, s, V, ldv, ldh, L.n, pl, (int)mfma, uw);
-    if (mfma) return launch_mfma<R, AR, T64_H>(2 * nh, L, m, uw, pl, pl, 1.0, part, s);
+    if constexpr (mh_on_mfma(R, AR, 4)) {
+      if (mfma) return launch_mfma<R, AR, T64_H>(2 * nh, L, m, uw, pl, pl, 1.0, part, s);
+    }
     const dim3 grid((unsigned)L.nblk);
     if (nh == 1)
       hipLaunchKernelGGL((mh_stream_kernel<R, AR, 1>), grid, dim3(kThreads), 0, s, m.a, m.alo, m.b, m.blo,
