@@ -202,8 +202,8 @@ bool sym_eig(int m, double* a, double* w, double* z);
 // converge.
 bool herm_eig(int m, double2* a, double* w, double2* z);
 
-// Threads of the host eigensolvers: OMP_NUM_THREADS if set, else the hardware
-// count, at most 16.
+// Threads of the host eigensolvers, the caller's own included: three quarters of
+// OMP_NUM_THREADS if set, else of the hardware count, of at most 16.
 int host_threads();
 
 // The same on the device (m >= 2; blocks until the results are on the host).

@@ -35,10 +35,19 @@
 
 namespace bse {
 
+// A quarter of the CPUs is left to the rest of the process (the caller, the HIP
+// runtime): every worker has to check in after each region, some 100 to 600 of them
+// in an eigenproblem, so one that the system has taken off its CPU holds up all.
+// With 16 threads on a share of 16 CPUs a projected problem inside a solve took
+// (ms, 16 / 12 / 8 threads) 1.7 to 2.9 / 0.85 / 0.8 at order 80, 4 to 6 / 2.3 / 2.3
+// at 128, 12 / 1.5 / 1.45 for the real one of 128; the solves PH, N = 12000, k = 8
+// (variant 3) 459 to 588 / 402 / 402, N = 10000, k = 64 (variant 0) 1150 to 1260 / 753
+// / 752.  By itself, with nothing else running, the 16 are the fastest.
 int host_threads() {
   static const int nt = [] {  // (asking the system takes some tens of microseconds)
     const char* e = getenv("OMP_NUM_THREADS");
-    return std::max(1, std::min(e ? atoi(e) : (int)std::thread::hardware_concurrency(), 16));
+    const int cpus = std::max(1, std::min(e ? atoi(e) : (int)std::thread::hardware_concurrency(), 16));
+    return cpus - cpus / 4;
   }();
   return nt;
 }

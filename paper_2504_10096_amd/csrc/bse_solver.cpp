@@ -118,25 +118,20 @@ bse_status fail(bse_handle h, bse_status s, const std::string& msg) {
 
 // Complex Hermitian eigenproblem of order m (column-major a, overwritten;
 // ascending w, orthonormal vectors z), the projected problems of the
-// restarts and of the refinement.  On the device above order host_eig_max when it
+// restarts and of the refinement.  On the device above order kHostEig when it
 // can be set up: the reduction to tridiagonal form by herm_tridiag, its
 // eigenpairs by rocSOLVER's divide and conquer.  At small orders the launches
-// dominate (ms, device / host QR of bse_smalleig.cpp with 16, 8, 4, 2 and 1
-// threads, copies included):
-//    48  1.40 / 0.29  0.35  0.36  0.34  0.29      112  1.73 / 1.32  1.84  2.12  2.61  3.09
-//    80  1.32 / 0.73  0.96  0.99  1.10  1.18      128  1.98 / 1.74  2.38  2.81  3.61  4.51
-//    96  1.53 / 1.00  1.34  1.41  1.67  1.96      160  2.27 / 2.91  3.93  5.08  6.66  8.58
-// They cross at 136 with 16 threads, 115 with 8, 100 with 4 and 85 with one: the
-// host up to 128 with all 16, up to 96 with fewer.  (A solve of PH, N = 3000, k =
-// 20, whose projected problems are of order 128: limit 96 / 128 with one thread 160 /
-// 226 ms, with 4 160 / 178, with 16 within the 145 to 162 that repeats scatter.)
+// dominate (ms inside a solve, device / host QR of bse_smalleig.cpp with 12, 8, 4 and
+// 1 threads: order 48 1.25 / 0.30 0.27 0.28 0.30, 64 1.75 / 0.51 0.50 0.60 0.59, 80 1.36 /
+// 0.88 0.83 1.00 1.13, 96 1.55 / 1.21 1.20 1.40 1.83, 128 1.98 / 2.3 2.3 2.7 4.1).
+// The limit does not depend on the threads, so that the results do not either.
 // With the library's reduction the device took 2.1 ms at order 96, 3.2 at 128 and
 // 6.2 at 224 (3.1 now); the host takes 53 ms at order 560.  Atomics are off in the rocBLAS calls,
 // so repeated solves stay bitwise identical.  The buffers grow with the largest
 // order seen and stay with the handle.  Where rocBLAS cannot create
 // a handle (no device), or the call reports an error or no convergence, the
 // host QR solves the same problem.  Returns false only if that fails too.
-int host_eig_max() { return bse::host_threads() >= 16 ? 128 : 96; }
+constexpr int kHostEig = 96;
 
 // The library's part of a projected eigenproblem of order m: the eigenpairs of
 // the tridiagonal matrix in eig_w, eig_e and the back-transformation through the
@@ -261,7 +256,7 @@ namespace {
 
 bool herm_eig_proj(bse_handle h, int m, double2* a, double* w, double2* z) {
   if (m < 1) return true;
-  if (m > host_eig_max() && bse::herm_tridiag && bse::herm_eig_device(h, m, a, w, z)) return true;
+  if (m > kHostEig && bse::herm_tridiag && bse::herm_eig_device(h, m, a, w, z)) return true;
   return bse::herm_eig(m, a, w, z);
 }
 
