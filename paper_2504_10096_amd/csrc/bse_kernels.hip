@@ -415,7 +415,9 @@ __global__ void __launch_bounds__(kThreads)
 // of two full-H vectors there: 219 us before, 178 us with 16 waves per 64 rows.
 // W = 16 up to kReduceWide rows, where 64-row workgroups of four waves do not
 // fill the chip, if each wave has a term (nb >= 16); W = 4 otherwise (N = 320,
-// six terms: 11.5 us per small pass with four waves, 12.8 us with 16).
+// six terms: 11.5 us per small pass with four waves, 12.8 us with 16).  From 18001 to
+// 40000 rows the two differ by less than runs of one do (four full-H vectors on
+// hi: 580 to 585 us at 18001, 2831 to 2838 at 40000, with either).
 constexpr int64_t kReduceWide = 32768;
 inline bool reduce_wide(const Layout& L) { return L.n <= kReduceWide && L.nb >= 16; }
 template <int W>
@@ -1254,7 +1256,7 @@ __global__ void __launch_bounds__(kThreads)
 // against 58 for a pure FMA loop in a quarter of the instructions; its four
 // independent 4 x 4 blocks take four vectors on the right, so eight
 // half-vectors are two instructions with nothing padded (the 16 x 16 form would
-// run half empty).  1.85 ms here, of which the products alone take 0.95 (matrix
+// run half empty).  1.85 to 1.95 ms here, of which the products alone take 0.95 (matrix
 // instructions and FP64 vector instructions share one unit: together they ran
 // at 72 TFLOP/s, so conversions and sums are worth removing).
 //
