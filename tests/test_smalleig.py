@@ -171,3 +171,40 @@ def test_herm_eig_range(driver, scale, col):
     assert np.abs(w / scale - ref).max() <= 1e-13 * top
     assert np.abs(z.conj().T @ z - np.eye(m)).max() <= 1e-13
     assert np.abs(a @ z - z * (w / scale)).max() <= 1e-12 * top
+
+
+@pytest.mark.parametrize("m", [3, 24, 48, 96])
+def test_herm_eig_accuracy(driver, m):
+    """Against Rayleigh quotients in extended precision.  A device solver of this kind leaves the
+    eigenvalues 2 eps |A| off and residuals of 4 eps |A|; a thick restart adds the errors of what it
+    keeps up, so the host solver may not be worse (QR steps by themselves: 9 and 11 eps |A| at order 48)."""
+    eps = np.finfo(float).eps
+    for seed in range(3):
+        rng = np.random.default_rng(1000 * m + seed)
+        q, _ = np.linalg.qr(rng.standard_normal((m, m)) + 1j * rng.standard_normal((m, m)))
+        a = (q * np.sort(rng.uniform(1.0, 14.0, m))) @ q.conj().T
+        a = 0.5 * (a + a.conj().T)
+        w, z = run(driver, "h", a)
+        al, zl = a.astype(np.clongdouble), np.linalg.eigh(a)[1].astype(np.clongdouble)
+        ref = (np.einsum("ij,ij->j", zl.conj(), al @ zl) / np.einsum("ij,ij->j", zl.conj(), zl)).real
+        top = float(ref[-1])
+        assert np.all(np.diff(w) >= 0)
+        assert np.abs(w - ref).max() <= 2 * eps * top
+        zl = z.astype(np.clongdouble)
+        assert np.sqrt((np.abs(al @ zl - zl * w) ** 2).sum(0)).max() <= 4 * eps * top
+        assert np.abs(zl.conj().T @ zl - np.eye(m)).max() <= 16 * eps
+
+
+def test_herm_eig_close_pairs(driver):
+    """Clusters and repeated eigenvalues: nothing is divided by a small gap."""
+    m = 60
+    rng = np.random.default_rng(12)
+    lam = np.concatenate([np.full(10, 1.0), 2.0 + 1e-15 * np.arange(10), 3.0 + 1e-10 * np.arange(20),
+                          4.0 + 1e-6 * np.arange(20)])
+    q, _ = np.linalg.qr(rng.standard_normal((m, m)) + 1j * rng.standard_normal((m, m)))
+    a = (q * lam) @ q.conj().T
+    a = 0.5 * (a + a.conj().T)
+    w, z = run(driver, "h", a)
+    assert np.abs(w - np.linalg.eigvalsh(a)).max() <= 1e-13
+    assert np.abs(z.conj().T @ z - np.eye(m)).max() <= 1e-14
+    assert np.abs(a @ z - z * w).max() <= 1e-13
