@@ -231,14 +231,9 @@ void qr_step(int lo, int hi, double* d, double* e, std::vector<Rot>& rots) {
     }
     if (k > lo) e[k - 1] = r;
     const double p = d[k], qq = d[k + 1], ek = e[k];
-    // p c^2 - 2 e c s + q s^2, p s^2 + 2 e c s + q c^2 and (p - q) c s + e (c^2 - s^2)
-    // with c^2 + s^2 = 1 used exactly: what one diagonal entry loses the other gains.
-    // Multiplied out, the rounding of c^2 + s^2 scales the entries once per step, and
-    // the error grows with the order (eigenvalues at order 96: 3.8e-14 off, 1.4e-14 so).
-    const double u = (qq - p) * s - 2.0 * ek * c, del = s * u;
-    d[k] = p + del;
-    d[k + 1] = qq - del;
-    e[k] = -(c * u + ek);
+    d[k] = p * c * c - 2.0 * ek * c * s + qq * s * s;
+    d[k + 1] = p * s * s + 2.0 * ek * c * s + qq * c * c;
+    e[k] = (p - qq) * c * s + ek * (c * c - s * s);
     if (k + 1 < hi) {
       bulge = -s * e[k + 1];
       e[k + 1] = c * e[k + 1];
@@ -380,10 +375,10 @@ inline void axpy(int m, double xr, double xi, const double* ar, const double* ai
 //
 // The reduction and the QR steps lose some eps |A| per sweep, which a thick restart
 // carries on into every later projected matrix.  Orders 48 / 96, eigenvalues up to 14,
-// mean over 8 matrices: eigenvalues off by 1.4e-14 / 1.4e-14 without this and 1.3e-15 /
-// 1.4e-15 with it (the library's device solver: 5.8e-15 / 5.7e-15), residuals 2.1e-14 /
-// 2.8e-14 and 7.1e-15 / 9.7e-15 (1.2e-14 / 1.3e-14), orthonormality 2.5e-15 / 3.9e-15
-// and 1.3e-15 / 1.8e-15 (1.4e-15 / 1.9e-15).  Three m x m products, in planes so that
+// mean over 8 matrices: eigenvalues off by 2.7e-14 / 4.1e-14 without this and 1.3e-15 /
+// 1.5e-15 with it (the library's device solver: 5.8e-15 / 5.7e-15), residuals 3.4e-14 /
+// 4.9e-14 and 6.5e-15 / 1.0e-14 (1.2e-14 / 1.3e-14), orthonormality 2.7e-15 / 4.7e-15
+// and 1.0e-15 / 1.7e-15 (1.4e-15 / 1.9e-15).  Three m x m products, in planes so that
 // they are real loops over contiguous rows: order 48 0.29 -> 0.32 ms with 12 threads.
 void refine_pairs(int m, const double2* a, double sc, cplx* z, double* d) {
   const size_t mm = (size_t)m * m;
@@ -483,7 +478,7 @@ bool herm_eig(int m, double2* a, double* w, double2* z) {
   for (int j = 0; j < m; ++j)
     for (int i = 0; i < m; ++i) qh[(size_t)j * m + i] *= delta[j];
   apply_rotations(m, qh.data(), rots);
-  refine_pairs(m, a, sc, qh.data(), d.data());
+  if (m <= 1024) refine_pairs(m, a, sc, qh.data(), d.data());  // (84 MB at 1024; above only where the device fails)
   std::vector<int> ord(m);
   std::iota(ord.begin(), ord.end(), 0);
   std::stable_sort(ord.begin(), ord.end(), [&](int x, int y) { return d[x] < d[y]; });
