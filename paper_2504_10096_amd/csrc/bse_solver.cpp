@@ -19,6 +19,7 @@
 #include <chrono>
 #include <complex>
 #include <initializer_list>
+#include <new>
 #include <string>
 #include <utility>
 #include <vector>
@@ -2724,8 +2725,14 @@ bse_status bse_direct(bse_handle h, int32_t k, double* omega, void* x, void* y, 
       // a real matrix or a zero column: the library's reduction leaves tau = 0
       // and its blocked back-transformation makes NaN of it in every vector
       // (orders above 65).  The solver of the projected problems takes these.
-      std::vector<double2> a(sq), z(sq);
+      std::vector<double2> a, z;
       std::vector<double> w(n2);
+      try {
+        a.resize(sq);
+        z.resize(sq);
+      } catch (const std::bad_alloc&) {
+        return fail(h, BSE_ERR_OUT_OF_MEMORY, "host memory of the Hermitian eigensolver");
+      }
       HIP_TRY(h, bse::direct_dense(h->L, hilo, mp, Z, nullptr, n, s));
       HIP_TRY(h, hipMemcpyAsync(a.data(), Z, sizeof(double2) * sq, hipMemcpyDeviceToHost, s));
       HIP_TRY(h, hipStreamSynchronize(s));
