@@ -274,6 +274,13 @@ void apply_rotations(int m, T* q, const std::vector<Rot>& rots) {
   });
 }
 
+// Columns below which the complex reduction runs its two loops per column in the
+// calling thread: a region over the pool costs 1.5 us, 5 us on a busy host, and one
+// of 80 columns has 6400 products each.  TDA N = 1024, k = 16 (order 48, in a loop) 13.0 to
+// 15.0 -> 11.5 to 12.3 ms, N = 16384, k = 32 213 to 219 -> 200 to 203, PH N = 12000, k = 8
+// (order 80) 417 to 423 -> 406 to 409; 64 columns within 1 % of that, 48 1 to 3 % above.
+constexpr int kSerial = 80;
+
 // Complex Hermitian a (column-major, m x m) = Q T Q^H, T tridiagonal with
 // real diagonal d and complex subdiagonal e; q receives Q.
 using cplx = std::complex<double>;
@@ -299,7 +306,7 @@ void herm_tridiagonalize(int m, cplx* a, double* d, cplx* e, cplx* q) {
     for (int i = k + 1; i < m; ++i) v[i] /= vn;
     // A <- H A H, H = I - 2 v v^H: p = A v, g = v^H p (real), q = p - g v,
     // A -= 2 (v q^H + q v^H)
-    par(m - k, 16, [&](int64_t t0, int64_t t1) {  // p_i = sum_j conj(A(j, i)) v_j (A Hermitian)
+    par(m - k, m - k <= kSerial ? kSerial : 16, [&](int64_t t0, int64_t t1) {  // p_i = sum_j conj(A(j, i)) v_j (A Hermitian)
       for (int64_t t = t0; t < t1; ++t) {
         const int i = k + (int)t;
         const cplx* ai = &A(0, i);
@@ -311,7 +318,7 @@ void herm_tridiagonalize(int m, cplx* a, double* d, cplx* e, cplx* q) {
     cplx g = 0.0;
     for (int i = k + 1; i < m; ++i) g += std::conj(v[i]) * p[i];
     for (int i = k; i < m; ++i) p[i] -= g.real() * v[i];
-    par(m - k, 16, [&](int64_t t0, int64_t t1) {
+    par(m - k, m - k <= kSerial ? kSerial : 16, [&](int64_t t0, int64_t t1) {
       for (int64_t t = t0; t < t1; ++t) {
         const int j = k + (int)t;
         for (int i = k; i < m; ++i) A(i, j) -= 2.0 * (v[i] * std::conj(p[j]) + p[i] * std::conj(v[j]));
@@ -379,7 +386,8 @@ inline void axpy(int m, double xr, double xi, const double* ar, const double* ai
 // 1.5e-15 with it (the library's device solver: 5.8e-15 / 5.7e-15), residuals 3.4e-14 /
 // 4.9e-14 and 6.5e-15 / 1.0e-14 (1.2e-14 / 1.3e-14), orthonormality 2.7e-15 / 4.7e-15
 // and 1.0e-15 / 1.7e-15 (1.4e-15 / 1.9e-15).  Three m x m products, in planes so that
-// they are real loops over contiguous rows: order 48 0.29 -> 0.32 ms with 12 threads.
+// they are real loops over contiguous rows: 0.04 ms at order 48, 0.09 at 87 with 12
+// threads.
 void refine_pairs(int m, const double2* a, double sc, cplx* z, double* d) {
   const size_t mm = (size_t)m * m;
   std::vector<double> buf(10 * mm, 0.0);

@@ -123,8 +123,8 @@ bse_status fail(bse_handle h, bse_status s, const std::string& msg) {
 // can be set up: the reduction to tridiagonal form by herm_tridiag, its
 // eigenpairs by rocSOLVER's divide and conquer.  At small orders the launches
 // dominate (ms, device / host QR of bse_smalleig.cpp with 12, 6, 3, 2 and 1 threads, copies
-// included: order 48 1.40 / 0.32 0.41 0.46 0.47 0.43, 64 1.92 / 0.57 0.74 0.78 0.85 0.97, 80 1.32 /
-// 0.86 1.16 1.34 1.54 1.81, 96 1.53 / 1.19 1.65 1.97 2.34 3.04, 128 1.98 / 2.70 3.18 4.20 5.27 7.24;
+// included: order 48 1.40 / 0.25 0.29 0.32 0.38 0.43, 64 1.92 / 0.49 0.56 0.63 0.71 0.95, 80 1.32 /
+// 0.80 0.92 1.13 1.35 1.80, 96 1.53 / 1.17 1.43 1.71 2.14 3.02, 128 1.98 / 2.30 2.97 3.73 4.82 7.13;
 // both are accurate to some eps |A|).
 // With the library's reduction the device took 2.1 ms at order 96, 3.2 at 128 and
 // 6.2 at 224 (3.1 now); the host takes 53 ms at order 560.  Atomics are off in the rocBLAS calls,
@@ -134,7 +134,7 @@ bse_status fail(bse_handle h, bse_status s, const std::string& msg) {
 // host QR solves the same problem.  Returns false only if that fails too.
 int host_eig_max() {
   const int t = bse::host_threads();
-  return t >= 8 ? 96 : t >= 3 ? 80 : 64;
+  return t >= 6 ? 96 : t >= 3 ? 80 : 64;
 }
 
 // The library's part of a projected eigenproblem of order m: the eigenpairs of
